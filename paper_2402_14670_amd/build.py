@@ -14,7 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblf_hip.so")
 SOURCES = [os.path.join(CSRC, "lf_api.cpp"), os.path.join(CSRC, "lf_serve.cpp"), os.path.join(CSRC, "lf_kernels.hip")]
-HEADERS = [os.path.join(CSRC, "lf_internal.h"), os.path.join(ROOT, "include", "lf.h")]
+HEADERS = [os.path.join(CSRC, "lf_internal.h"), os.path.join(CSRC, "lf_pair.h"), os.path.join(ROOT, "include", "lf.h")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("LF_OFFLOAD_ARCH", "gfx950")
 

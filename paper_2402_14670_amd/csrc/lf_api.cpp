@@ -27,11 +27,19 @@ thread_local std::string g_create_error;
 struct Batch {
     void *dmem = nullptr;
     size_t bytes = 0;
+    void *idx = nullptr;            // bucket indexes (none under a device budget), beside the block
+    size_t idx_bytes = 0;
     lfk::DevBatch dev{};
     uint32_t n_events = 0, n_tracks = 0, n_hits = 0;
     std::vector<uint32_t> trk_off;  // host copy, for per-event launches
     size_t out_off = 0, out_bytes = 0;   // the result arrays: one run of the allocation
 };
+
+// Least number of result slots for two tracks per wavefront.  Smaller batches
+// leave most of the chip idle, and one track per wavefront takes less time
+// from its first load to its result (200 tracks: 14.6 us against 16.5, 3,200:
+// 17.0 against 18.4; 4,800: 20.3 against 19.9, 10,000: 31.4 against 24.3).
+constexpr uint32_t PAIR_MIN = 4096;
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -156,7 +164,7 @@ struct lf_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     void *fixed = nullptr;             // this device's fixed scratch (lf_find_tracks_noalloc)
-    lfk::ExecCfg exec{2, 4, 0, 0};
+    lfk::ExecCfg exec{2, 4, 0, 0, 0, 0};
     std::map<uint64_t, Batch> batches;
     uint64_t next_id = 1;
     std::string err;
@@ -167,6 +175,8 @@ struct lf_ctx {
     // that fits it (not counted in `used`)
     void *spare = nullptr;
     size_t spare_bytes = 0;
+    void *spare_idx = nullptr;         // likewise the last freed bucket indexes
+    size_t spare_idx_bytes = 0;
 };
 
 namespace {
@@ -219,14 +229,40 @@ hipError_t take_block(lf_ctx *c, size_t need, void **p, size_t *got) {
     return hipMalloc(p, need);
 }
 
-// Frees a batch's block: kept as the spare (the previous spare is freed).
+// Memory for a batch's bucket indexes, kept and reused as the blocks are;
+// nullptr when it cannot be had (searches then start from whole buckets).
+void *take_idx(lf_ctx *c, size_t need, size_t *got) {
+    if (c->spare_idx && c->spare_idx_bytes >= need && c->spare_idx_bytes / 2 <= need) {
+        void *p = c->spare_idx;
+        *got = c->spare_idx_bytes;
+        c->spare_idx = nullptr;
+        c->spare_idx_bytes = 0;
+        return p;
+    }
+    if (c->spare_idx) (void)hipFree(c->spare_idx);
+    c->spare_idx = nullptr;
+    c->spare_idx_bytes = 0;
+    void *p = nullptr;
+    if (hipMalloc(&p, need) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    *got = need;
+    return p;
+}
+
+// Frees a batch's block and indexes: kept as the spare (the previous spare is freed).
 // The device is synchronised first, as a free would be, so that no queued
 // work on any stream still uses the block when an upload reuses it.
-void drop_block(lf_ctx *c, void *p, size_t bytes) {
+void drop_block(lf_ctx *c, const Batch &b) {
     (void)hipDeviceSynchronize();
     if (c->spare) (void)hipFree(c->spare);
-    c->spare = p;
-    c->spare_bytes = bytes;
+    c->spare = b.dmem;
+    c->spare_bytes = b.bytes;
+    if (!b.idx) return;
+    if (c->spare_idx) (void)hipFree(c->spare_idx);
+    c->spare_idx = b.idx;
+    c->spare_idx_bytes = b.idx_bytes;
 }
 
 bool finitef(float v) { return std::isfinite(v); }
@@ -486,10 +522,20 @@ int lf_create(const lf_geometry *geom, const lf_params *params, size_t device_bu
     int ncu = 0;
     if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, c->device);
     if (e == hipSuccess) e = lfk::fixed_scratch(&c->fixed);
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&c->d_params), sizeof(lfk::KParams));
+    // device copy: the parameters, then the fit table
+    const size_t tab_off = align256(sizeof(lfk::KParams));
+    if (e == hipSuccess)
+        e = hipMalloc(reinterpret_cast<void **>(&c->d_params), tab_off + lfk::FIT_ROWS * sizeof(lfk::FitRow));
     if (e == hipSuccess) {
-        const lfk::KParams k = to_kparams(*geom, *params);
+        lfk::KParams k = to_kparams(*geom, *params);
+        lfk::plane_constants(k);
+        lfk::FitRow *tab = reinterpret_cast<lfk::FitRow *>(reinterpret_cast<char *>(c->d_params) + tab_off);
+        k.fit_tab = tab;
+        c->exec.n_triplets = k.n_triplets;
+        c->exec.pair_min = k.pair_ok ? PAIR_MIN : 0u;
         e = hipMemcpy(c->d_params, &k, sizeof(k), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = lfk::launch_fit_table(c->d_params, tab, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     }
     if (e != hipSuccess) {
         std::string msg = std::string("lf_create: ") + hipGetErrorString(e);
@@ -497,8 +543,7 @@ int lf_create(const lf_geometry *geom, const lf_params *params, size_t device_bu
         return fail(nullptr, LF_ERR_DEVICE, msg);
     }
     c->exec.n_cu = ncu;
-    c->exec.blocks_per_cu = lfk::persistent_blocks_per_cu(params->n_hits_window, params->velo_only ? 2 : (params->seed_fp16 ? 3 : 1),
-                                                          c->exec.waves_per_block);
+    c->exec.blocks_per_cu = lfk::persistent_blocks_per_cu(params->n_hits_window, lfapi::ctx_sides(c), c->exec);
     if (c->exec.blocks_per_cu < 1) c->exec.blocks_per_cu = 1;
     *out = c;
     return LF_OK;
@@ -511,8 +556,7 @@ int lf_set_exec(lf_ctx *c, const lf_exec *x) {
         if (x->waves_per_block != 1 && x->waves_per_block != 2 && x->waves_per_block != 4)
             return fail(c, LF_ERR_INVALID, "lf_set_exec: waves_per_block must be 1, 2 or 4");
         n.waves_per_block = x->waves_per_block;
-        n.blocks_per_cu = lfk::persistent_blocks_per_cu(c->params.n_hits_window, lfapi::ctx_sides(c),
-                                                        n.waves_per_block);
+        n.blocks_per_cu = lfk::persistent_blocks_per_cu(c->params.n_hits_window, lfapi::ctx_sides(c), n);
         if (n.blocks_per_cu < 1) n.blocks_per_cu = 1;
     }
     if (x->items_per_grab) {
@@ -550,6 +594,9 @@ int lf_upload_events(lf_ctx *c, const lf_batch *b, void *hip_stream, uint64_t *b
     }
     hipError_t e = take_block(c, L.total, &bt.dmem, &bt.bytes);
     if (e != hipSuccess) return fail(c, LF_ERR_NOMEM, std::string("lf_upload_events: hipMalloc: ") + hipGetErrorString(e));
+    // the bucket indexes only shorten searches: a context with a device budget
+    // goes without, so that its memory is what the budget counts
+    if (!c->budget && E) bt.idx = take_idx(c, (size_t)E * 24 * sizeof(lfk::BucketIndex), &bt.idx_bytes);
     char *base = static_cast<char *>(bt.dmem);
     lfk::DevBatch &d = bt.dev;
     d.hit_off = reinterpret_cast<const uint32_t *>(base + L.hit_off);
@@ -564,6 +611,7 @@ int lf_upload_events(lf_ctx *c, const lf_batch *b, void *hip_stream, uint64_t *b
     d.tty = reinterpret_cast<const float *>(base + L.tty);
     d.tqop = reinterpret_cast<const float *>(base + L.tqop);
     d.uni = reinterpret_cast<const uint8_t *>(base + L.uni);
+    d.bidx = static_cast<const lfk::BucketIndex *>(bt.idx);
     d.found = reinterpret_cast<uint8_t *>(base + L.found);
     d.nhits = reinterpret_cast<uint8_t *>(base + L.nhits);
     d.hit_idx = reinterpret_cast<int32_t *>(base + L.hit_idx);
@@ -608,11 +656,11 @@ int lf_upload_events(lf_ctx *c, const lf_batch *b, void *hip_stream, uint64_t *b
         }
     }
     if (e == hipSuccess) e = hipMemsetAsync(d.counter, 0, 4 * (size_t)lfk::QUEUE_WORDS, s);
-    if (e == hipSuccess) e = lfk::launch_track_event(d, s);
-    if (e == hipSuccess) e = lfk::launch_event_uniform(d, reinterpret_cast<uint8_t *>(base + L.uni), s);
+    if (e == hipSuccess) e = lfk::launch_event_index(d, c->d_params, reinterpret_cast<uint8_t *>(base + L.uni), s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         (void)hipFree(bt.dmem);
+        if (bt.idx) (void)hipFree(bt.idx);
         return hip_fail(c, e, "lf_upload_events");
     }
     const uint64_t id = c->next_id++;
@@ -666,6 +714,7 @@ int lf_find_tracks_noalloc(lf_ctx *c, const lf_batch *in, uint32_t n_hits, uint3
     d.trk_ev = reinterpret_cast<const uint32_t *>(fx + lfk::FIXED_TRK_EV_OFF);
     d.tx_ = in->trk_x; d.ty_ = in->trk_y; d.ttx = in->trk_tx; d.tty = in->trk_ty; d.tqop = in->trk_qop;
     d.uni = reinterpret_cast<const uint8_t *>(fx + lfk::FIXED_UNI_OFF);
+    d.bidx = E <= lfk::FIXED_IDX_EVENTS ? reinterpret_cast<const lfk::BucketIndex *>(fx + lfk::FIXED_IDX_OFF) : nullptr;
     d.found = out->found; d.nhits = out->n_hits; d.hit_idx = out->hit_idx;
     d.a = out->a; d.b = out->b; d.c = out->c; d.y0 = out->y0; d.ty = out->ty; d.qop = out->qop; d.Q = out->Q;
     d.counter = reinterpret_cast<uint32_t *>(fx + lfk::FIXED_QUEUE_OFF);
@@ -673,9 +722,9 @@ int lf_find_tracks_noalloc(lf_ctx *c, const lf_batch *in, uint32_t n_hits, uint3
     d.n_events = E;
     d.n_tracks = n_tracks;
     hipStream_t s = pick(c, hip_stream);
-    hipError_t e = lfk::launch_zero_words(d.counter, lfk::QUEUE_WORDS, s);
-    if (e == hipSuccess) e = lfk::launch_track_event(d, s);
-    if (e == hipSuccess) e = lfk::launch_event_uniform(d, reinterpret_cast<uint8_t *>(fx + lfk::FIXED_UNI_OFF), s);
+    // (the queue words are the persistent mode's alone)
+    hipError_t e = mode == LF_MODE_PERSISTENT ? lfk::launch_zero_words(d.counter, lfk::QUEUE_WORDS, s) : hipSuccess;
+    if (e == hipSuccess) e = lfk::launch_event_index(d, c->d_params, reinterpret_cast<uint8_t *>(fx + lfk::FIXED_UNI_OFF), s);
     if (e == hipSuccess)
         e = lfk::launch_find(d, c->d_params, c->params.n_hits_window, lfapi::ctx_sides(c), mode, c->exec, nullptr, s);
     if (e != hipSuccess) return hip_fail(c, e, "lf_find_tracks_noalloc");
@@ -823,7 +872,7 @@ int copy_tracks(lf_ctx *c, uint64_t batch_id, lf_tracks_out *out, size_t cap_tra
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(c, e, "lf_fetch_tracks");
     if (release) {
-        drop_block(c, bt.dmem, bt.bytes);
+        drop_block(c, bt);
         c->used -= bt.bytes;
         c->batches.erase(it);
     }
@@ -854,7 +903,7 @@ int lf_release_batch(lf_ctx *c, uint64_t batch_id) {
     if (it == c->batches.end()) return fail(c, LF_ERR_STATE, "lf_release_batch: unknown batch id");
     // work on the batch may still be queued on any stream: wait for the device
     const hipError_t e = hipDeviceSynchronize();
-    drop_block(c, it->second.dmem, it->second.bytes);
+    drop_block(c, it->second);
     c->used -= it->second.bytes;
     c->batches.erase(it);
     if (e != hipSuccess) return hip_fail(c, e, "lf_release_batch");
@@ -879,8 +928,12 @@ void lf_destroy(lf_ctx *c) {
     if (!c) return;
     if (c->stream) (void)hipStreamSynchronize(c->stream);
     (void)hipDeviceSynchronize();
-    for (auto &kv : c->batches) (void)hipFree(kv.second.dmem);
+    for (auto &kv : c->batches) {
+        (void)hipFree(kv.second.dmem);
+        if (kv.second.idx) (void)hipFree(kv.second.idx);
+    }
     if (c->spare) (void)hipFree(c->spare);
+    if (c->spare_idx) (void)hipFree(c->spare_idx);
     if (c->d_params) (void)hipFree(c->d_params);
     if (c->pin) (void)hipHostFree(c->pin);
     if (c->stream) (void)hipStreamDestroy(c->stream);

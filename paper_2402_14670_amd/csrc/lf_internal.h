@@ -11,6 +11,20 @@ constexpr int NL = 12;
 constexpr int MAX_WINDOW = 64;    // n_hits_window upper bound (6-bit window-relative indices)
 constexpr int MAX_TRIPLETS = 32;  // n_triplets upper bound
 
+// Sums and solves of a candidate's fits that depend only on which layers have
+// a hit, for hits on the layer planes: the serial sums over the present layers
+// in ascending order of 1, s, h, s^2, s h, h^2 (x fit) and 1, s, s^2 over the
+// stereo layers (y fit), the x fit's cofactors and determinant, the y fit's
+// determinant, and C(n_hits).
+struct alignas(16) FitRow {
+    float S0, S1, S2, S11;
+    float S12, S22, m00, m01;
+    float m02, det, YS0, YS1;
+    float YS11, D, C, unused;
+};
+
+constexpr uint32_t FIT_ROWS = 1u << NL;   // one for each mask
+
 // Geometry and parameters, passed to every kernel by value.
 struct KParams {
     float z[NL], dxdy[NL];
@@ -31,7 +45,40 @@ struct KParams {
     float F_coef[5][10];
     // Triplet seeding in binary16 (VELO-UT input only)
     int32_t seed_fp16;
+    // What hits on the layer planes make constant (two tracks per wavefront,
+    // lf_pair.h): u = z - z_ref and g(u) of each layer; per seed set (layers
+    // l0, l1, l2): z_l2 - z_l0, 1 / (z_mag - z_l0) (bracket only), and the
+    // triplet model's u1 - u0, u2 - u1, G01 and G12 - G01; fit_tab[mask]
+    // for each 12-bit mask of layers with a hit.  pair_ok: the planes allow
+    // that path (lever arms and set lengths above 1 mm).
+    float lay_u[NL], lay_g[NL];
+    float set_dz[2], set_rlev[2], set_du01[2], set_du12[2], set_G01[2], set_dG[2];
+    int32_t pair_ok;
+    const FitRow *fit_tab;   // [FIT_ROWS] device memory
 };
+
+// Where a sorted search in one hit bucket starts: the bucket's x range cut into
+// IDX_CELLS equal cells, start[c] = first hit (bucket-relative) of cell >= c.
+// cell(x) is non-decreasing in x under rounding, so the hits of smaller cells
+// than cell(key) are below the key and those of larger cells are not: the
+// lower bound of the key lies in [start[c], start[c + 1]], c = cell(key).
+constexpr int IDX_CELLS = 64;
+struct alignas(16) BucketIndex {
+    float lo, scale;
+    // ranges over the bucket: z, max dxdy - min dxdy, max |dxdy|, max |x|
+    float zmin, zmax, dspread, dabs, xabs;
+    uint16_t start[IDX_CELLS + 1], pad;
+};
+static_assert(sizeof(BucketIndex) == 160, "written as 40 words");
+__host__ __device__ inline int index_cell(float x, float lo, float scale) {
+    return (int)fminf(fmaxf((x - lo) * scale, 0.0f), (float)(IDX_CELLS - 1));
+}
+constexpr uint32_t IDX_MAX_BUCKET = 65535;   // hits of a bucket the index can hold
+
+// Flags of an event (DevBatch::uni).
+enum { EV_UNIFORM = 1,    // in every bucket all hits share one z and one dxdy (bit for bit)
+       EV_PLANES = 2,     // and these are the geometry's layer planes (z, and dxdy on stereo layers)
+       EV_NO_INDEX = 4 }; // a bucket is too long for the index
 
 // Device view of one resident batch (SoA, all in HBM).
 struct DevBatch {
@@ -40,7 +87,8 @@ struct DevBatch {
     const uint32_t *trk_off;   // [E+1]
     const uint32_t *trk_ev;    // [T] event of each track
     const float *tx_, *ty_, *ttx, *tty, *tqop;  // [T]
-    const uint8_t *uni;        // [E] 1: in every bucket of the event all hits share one z and one dxdy (bit for bit)
+    const uint8_t *uni;        // [E] EV_* flags
+    const BucketIndex *bidx;   // [24*E], or nullptr: searches start from the whole bucket
     uint8_t *found, *nhits;    // [T]
     int32_t *hit_idx;          // [12*T]
     float *a, *b, *c, *y0, *ty, *qop, *Q;  // [T]
@@ -65,6 +113,10 @@ struct ExecCfg {
     int items_per_grab;
     int blocks_per_cu;
     int n_cu;
+    // batched and persistent mode: least number of result slots for two
+    // tracks per wavefront (0: never, the geometry's planes do not allow it)
+    uint32_t pair_min;
+    int n_triplets;   // of the context's parameters
 };
 
 // One event of a serving batch: its blob in pinned host memory (device
@@ -88,8 +140,6 @@ struct BatchIn {
 // states copied, trk_ev filled.  desc is in device memory.
 hipError_t launch_gather(const GatherDesc *desc, uint32_t n_events, const BatchIn &out, hipStream_t s);
 
-// Fills trk_ev from trk_off (one thread per track).
-hipError_t launch_track_event(const DevBatch &b, hipStream_t s);
 // Result slots of a batch of pool events evs[0..n_events) (slots [toff[e],
 // toff[e+1]) for event e, n_slots = toff[n_events], read on the device):
 // map[i] = the pool track slot i follows.  All arrays in device memory.
@@ -103,26 +153,35 @@ hipError_t launch_track_map(const uint32_t *evs, const uint32_t *toff, uint32_t 
 // layer), 3 for VELO-UT input with the binary16 seeding build.
 hipError_t launch_find(const DevBatch &b, const KParams *P, int n_hits_window, int n_sides, int mode,
                        const ExecCfg &cfg, const uint32_t *trk_off_host, hipStream_t s);
-// Writes the per-event flag of DevBatch::uni into uni[E] (one block per
-// event; the batch's hits must be in place).
-hipError_t launch_event_uniform(const DevBatch &b, uint8_t *uni, hipStream_t s);
+// What the hot path needs to know of each event beside its hits (one block per
+// event; the batch's hits and offsets must be in place): the flags uni[E], the
+// bucket indexes b.bidx (if not nullptr) and trk_ev.
+hipError_t launch_event_index(const DevBatch &b, const KParams *P, uint8_t *uni, hipStream_t s);
+// Fills the parts of k that follow from its geometry (lay_*, set_*, pair_ok).
+void plane_constants(KParams &k);
+// Fills the FIT_ROWS rows of the fit table of P (both in device memory).
+hipError_t launch_fit_table(const KParams *P, FitRow *rows, hipStream_t s);
 // Counting launch: one wavefront per track, adds the work counters of every
 // track into b.stats (which must be zeroed first).
 hipError_t launch_count(const DevBatch &b, const KParams *P, int n_hits_window, int n_sides, hipStream_t s);
 // Fills the result slots with a poison pattern (kernel, no memset).
 hipError_t launch_poison(const DevBatch &b, hipStream_t s);
 // Resident blocks per compute unit of the persistent kernel (0 on error).
-int persistent_blocks_per_cu(int n_hits_window, int n_sides, int waves_per_block);
+int persistent_blocks_per_cu(int n_hits_window, int n_sides, const ExecCfg &cfg);
 
 // Fixed scratch of the non-allocating entry point: one array in the code
 // object's device memory per GPU, holding the persistent mode's queue words,
-// the per-event uniform flags and the event of each track.
+// the per-event flags, the event of each track and the bucket indexes of
+// batches of up to FIXED_IDX_EVENTS events (larger ones go without).
 constexpr uint32_t FIXED_MAX_EVENTS = 1u << 20;
 constexpr uint32_t FIXED_MAX_TRACKS = 1u << 22;
 constexpr size_t FIXED_QUEUE_OFF = 0;                       // QUEUE_WORDS x u32
 constexpr size_t FIXED_UNI_OFF = 4 * (size_t)QUEUE_WORDS;   // FIXED_MAX_EVENTS x u8
 constexpr size_t FIXED_TRK_EV_OFF = FIXED_UNI_OFF + FIXED_MAX_EVENTS;   // FIXED_MAX_TRACKS x u32
-constexpr size_t FIXED_BYTES = FIXED_TRK_EV_OFF + 4 * (size_t)FIXED_MAX_TRACKS;
+constexpr uint32_t FIXED_IDX_EVENTS = 8192;
+constexpr size_t FIXED_IDX_OFF = FIXED_TRK_EV_OFF + 4 * (size_t)FIXED_MAX_TRACKS;   // 24 x FIXED_IDX_EVENTS x BucketIndex
+constexpr size_t FIXED_BYTES = FIXED_IDX_OFF + 24 * (size_t)FIXED_IDX_EVENTS * sizeof(BucketIndex);
+static_assert(FIXED_IDX_OFF % 16 == 0, "the indexes are 16-byte aligned");
 // Device address of the current device's copy of the fixed scratch, looked
 // up once per device (the first call on a device must run with it current).
 hipError_t fixed_scratch(void **out);

@@ -1,7 +1,9 @@
 // lf_kernels.hip -- Looking Forward track following, gfx950 kernels.
 //
-// One wavefront (64 lanes) carries one upstream input track through every
-// step of the method (arXiv 2402.14670, "Algorithm logic"):
+// One wavefront (64 lanes) carries one upstream input track -- or, in large
+// batches of VELO-UT input seeded in binary32, each half of it one of two
+// (lf_pair.h) -- through every step of the method (arXiv 2402.14670,
+// "Algorithm logic"):
 //
 //   windows    the kick (linear, or the sqrt-normalised pt-kick with the
 //              momentum parametrisation F), then 36 lanes: (layer, bound)
@@ -10,7 +12,7 @@
 //   staging    the <= 12 x n_hits_window window hits are read coalesced from
 //              HBM into this wave's LDS slice: x, z and dxdy per hit; x only
 //              where LDS bounds the occupancy, and in events whose buckets
-//              each hold one z and one dxdy (flagged by k_event_uniform).
+//              each hold one z and one dxdy (flagged by k_event_index).
 //   doublets   one first-layer hit of a seed set per lane; the range of
 //              third-layer hits that can pass the magnet filter is
 //              bracketed by a sorted search, each pair in it tested with the
@@ -36,6 +38,7 @@
 // queue words and per-event and per-track indexes.
 #include <cstddef>
 #include <mutex>
+#include <type_traits>
 
 #include "lf_internal.h"
 
@@ -43,6 +46,7 @@ namespace lfk {
 namespace {
 
 constexpr int WAVE = 64;
+constexpr int HALF = 32;              // lanes per track of the two-track kernel
 constexpr int QCAP = 128;             // doublet queue: < 64 pending + one pass of 64
 constexpr int NSLOT = 9;              // extension work per candidate: 3 x layers + 6 u/v layers
 constexpr float INV1024 = 0.0009765625f;            // 2^-10, exact
@@ -64,6 +68,14 @@ __device__ __forceinline__ int opaque_lane_id() {
     int l = (int)__lane_id();
     asm volatile("" : "+v"(l));
     return l;
+}
+
+// The parameters, likewise opaque: nothing read or computed from them is kept
+// in registers from one track of a loop to the next.
+__device__ __forceinline__ const KParams *opaque_params(const KParams *P) {
+    uint64_t a = reinterpret_cast<uint64_t>(P);
+    asm volatile("" : "+s"(a));
+    return (const KParams *)(__attribute__((address_space(4))) const KParams *)a;
 }
 
 // Element i of a device array of less than 4 GiB (the host checks the batch
@@ -617,7 +629,9 @@ struct Track {
         const float T = tx_in + dtx;
         const float kd = P->kappa * dtx;
         ebase = (uint32_t)__builtin_amdgcn_readlane((int)ho, 0);
-        uni = B.uni[ev] != 0;
+        const uint32_t evf = B.uni[ev];
+        uni = (evf & EV_UNIFORM) != 0;
+        const bool indexed = B.bidx != nullptr && !(evf & EV_NO_INDEX);
         // x tolerance of the x-layer windows
         float xtol;
         if constexpr (NS == 2) {
@@ -642,6 +656,10 @@ struct Track {
                 const uint32_t b0 = (uint32_t)__shfl((int)ho, 2 * l + zone);
                 const uint32_t b1 = (uint32_t)__shfl((int)ho, 2 * l + zone + 1);
                 const float zl = __shfl(gz, l), dxl = __shfl(gd, l);
+                // the bucket's index, fetched while the bounds are computed
+                const BucketIndex *bi = B.bidx + ((size_t)ev * 24 + (uint32_t)(2 * l + zone));
+                float ilo = 0.0f, iscale = 0.0f;
+                if (indexed) { ilo = bi->lo; iscale = bi->scale; }
                 if (lane < 3 * NL) {
                     const int k = lane - 3 * l;
                     const float ye = y_in + ty_in * (zl - P->z_in);
@@ -682,6 +700,12 @@ struct Track {
                     // lower bound (x < key) for x_min and the centre, upper bound
                     // (x <= key) for x_max, which for finite x is x < next_up(key)
                     const float kk = k == 2 ? next_up(key) : key;
+                    if (indexed) {
+                        const uint16_t *st = &bi->start[index_cell(kk, ilo, iscale)];
+                        const uint32_t s0 = st[0], s1 = st[1];
+                        lo = b0 + s0;
+                        n = s1 - s0;
+                    }
                     while (n > 0) {
                         const uint32_t half = n >> 1;
                         const float v = ld32(B.hx, lo + half);
@@ -1417,6 +1441,8 @@ struct Track {
     }
 };
 
+#include "lf_pair.h"
+
 template <int NW, int NS, int WPB, bool H16 = false>
 __global__ __launch_bounds__(WPB * WAVE) void k_plain(DevBatch B, const KParams *__restrict__ P, uint32_t ev) {
     __shared__ WaveLds<NW, NS> lds[WPB];
@@ -1458,6 +1484,38 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NS =
     }
 }
 
+// Result slots t0 and t0 + 1 (if < n): the two-track body.
+template <int NW, int MT>
+__device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams *__restrict__ P, PairLds<NW, MT> &lds,
+                                               int lane, uint32_t t0, uint32_t n) {
+    const uint32_t t = t0 + (uint32_t)(lane >> 5);
+    const bool act = t < n;
+    const uint32_t slot = act ? t : t0;
+    const uint32_t tin = B.trk_map ? B.trk_map[slot] : slot;
+    const uint32_t ev = B.trk_ev[tin];
+    const uint32_t evf = B.uni[ev];
+    if (__ballot(!(evf & EV_PLANES)) == 0) {
+        Pair<NW, MT, true> pr{B, P, lds};
+        pr.run(lane, slot, ev, evf, tin, act);
+    } else {
+        Pair<NW, MT, false> pr{B, P, lds};
+        pr.run(lane, slot, ev, evf, tin, act);
+    }
+}
+
+// Batched mode, two tracks per wavefront.  (7 waves per SIMD: 72 registers, a
+// few spilled; 5 to 7 waves measure within 2%.)
+template <int NW, int MT, int WPB>
+__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NW == 32 && MT == 16 ? 7 : 1))) void k_pair(DevBatch B, const KParams *__restrict__ P) {
+    __shared__ PairLds<NW, MT> lds[WPB];
+    const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const uint32_t per = gridDim.x / NXCD;
+    const uint32_t lb = (blockIdx.x % NXCD) * per + blockIdx.x / NXCD;
+    const uint32_t t0 = 2 * (lb * WPB + w), n = B.trk_map ? B.n_map : B.n_tracks;
+    if (t0 >= n) return;
+    pair_of_tracks<NW, MT>(B, P, lds[w], lane_id(), t0, n);
+}
+
 // Persistent: QUEUE_N work queues, QUEUE_SUB per XCD.  XCD x owns a
 // contiguous eighth of the tracks, cut into chunks of `items` tracks; chunk j
 // belongs to the XCD's queue j % QUEUE_SUB, whose k-th claim is chunk
@@ -1476,10 +1534,11 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NS =
 static_assert(QUEUE_N == 2 * WAVE, "the drained-queue scan reads two heads per lane");
 static_assert(QUEUE_N == NXCD * QUEUE_SUB, "QUEUE_SUB queues per XCD");
 
-template <int NW, int NS, int WPB, bool H16 = false>
-__global__ __launch_bounds__(WPB * WAVE) void k_persistent(DevBatch B, const KParams *__restrict__ P,
+// MT != 0: two tracks at a time (lists of MT triplets), else one.
+template <int NW, int NS, int WPB, bool H16 = false, int MT = 0>
+__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NW == 32 && MT == 16 ? 5 : 1))) void k_persistent(DevBatch B, const KParams *__restrict__ P,
                                                             uint32_t items) {
-    __shared__ WaveLds<NW, NS> lds[WPB];
+    __shared__ std::conditional_t<MT != 0, PairLds<NW, MT != 0 ? MT : 16>, WaveLds<NW, NS>> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     uint32_t *q = B.counter;
     const uint32_t T = B.n_tracks;
@@ -1519,13 +1578,17 @@ __global__ __launch_bounds__(WPB * WAVE) void k_persistent(DevBatch B, const KPa
         const uint32_t x = qi / QUEUE_SUB, lo = xlo(x), hi = xlo(x + 1);
         const uint32_t t0 = lo + (k * QUEUE_SUB + qi % QUEUE_SUB) * items;
         const uint32_t t1 = t0 + items < hi ? t0 + items : hi;
-        for (uint32_t t = t0; t < t1; ++t) {
+        for (uint32_t t = t0; t < t1; t += MT != 0 ? 2 : 1) {
             // keep per-track loads inside the loop: hoisting them across tracks
             // costs ~30 VGPRs of loop-carried state and two waves per SIMD
             asm volatile("" ::: "memory");
-            Track<NW, NS, false, H16> tr{B, P, lds[w], 0, {}, 0};
-            tr.ln = opaque_lane_id();
-            tr.run(t, B.trk_ev[t], t);
+            if constexpr (MT != 0) {
+                pair_of_tracks<NW, MT>(B, opaque_params(P), lds[w], opaque_lane_id(), t, t1);
+            } else {
+                Track<NW, NS, false, H16> tr{B, P, lds[w], 0, {}, 0};
+                tr.ln = opaque_lane_id();
+                tr.run(t, B.trk_ev[t], t);
+            }
         }
         k = __builtin_amdgcn_readfirstlane(next);
     }
@@ -1599,49 +1662,170 @@ __global__ void k_track_map(const uint32_t *__restrict__ evs, const uint32_t *__
     map[i] = pool_trk_off[evs[e]] + (i - toff[e]);
 }
 
-__global__ void k_track_event(const uint32_t *__restrict__ trk_off, uint32_t n_events, uint32_t n_tracks,
-                              uint32_t *__restrict__ trk_ev) {
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n_tracks) return;
-    // last event e with trk_off[e] <= t
-    uint32_t lo = 0, n = n_events + 1;
-    while (n > 0) {
-        const uint32_t half = n >> 1;
-        if (trk_off[lo + half] <= t) { lo += half + 1; n -= half + 1; } else { n = half; }
+// One block per event, two buckets per wavefront: the buckets' indexes
+// (BucketIndex) and the event's flags (EV_*).  EV_UNIFORM: in each of the 24
+// buckets every hit has the z and the stereo tangent of the bucket's first hit
+// (bit for bit).  The block also writes its tracks' trk_ev.  Bound by memory
+// latency: an event's x, z and dxdy are read once (12 B per hit) by three
+// dependent loads (offsets, hits, and the next round of a long bucket), so a
+// wavefront issues the first 256 hits of both its buckets before it waits, and
+// writes each record (160 B) with one store.
+constexpr int EVI_WAVES = 12, EVI_ROUNDS = 4;
+__global__ void __launch_bounds__(EVI_WAVES * WAVE) k_event_index(DevBatch B, const KParams *__restrict__ P,
+                                                                  uint8_t *__restrict__ uni,
+                                                                  BucketIndex *__restrict__ bidx,
+                                                                  uint32_t *__restrict__ trk_ev) {
+    __shared__ BucketIndex rec[EVI_WAVES];
+    const uint32_t e = blockIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = lane_id();
+    struct Bucket {
+        uint32_t b0, n;
+        float x[EVI_ROUNDS], z[EVI_ROUNDS], d[EVI_ROUNDS], last;
+    } bk[2];
+    auto load = [&](Bucket &b, uint32_t i0) {   // hits i0 + 64 r + lane (past the end: the last one)
+#pragma unroll
+        for (int r = 0; r < EVI_ROUNDS; ++r) {
+            if (i0 + (uint32_t)(r * WAVE) >= b.n) continue;
+            const uint32_t i = i0 + (uint32_t)(r * WAVE + lane), g = b.b0 + (i < b.n ? i : b.n - 1);
+            b.x[r] = ld32(B.hx, g);
+            b.z[r] = ld32(B.hz, g);
+            b.d[r] = ld32(B.hd, g);
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const uint32_t k = (uint32_t)(w + q * EVI_WAVES);
+        bk[q].b0 = B.hit_off[2 * NL * e + k];
+        bk[q].n = B.hit_off[2 * NL * e + k + 1] - bk[q].b0;
     }
-    trk_ev[t] = lo - 1;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        load(bk[q], 0);
+        bk[q].last = bk[q].n ? ld32(B.hx, bk[q].b0 + bk[q].n - 1) : 0.0f;
+    }
+    int odd = 0;      // 1: a hit differs from its bucket's first; 2: a bucket too long; 4: off its plane
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        Bucket &b = bk[q];
+        const int k = w + q * EVI_WAVES;
+        const uint32_t n = b.n;
+        float lo = 0.0f, scale = 0.0f, xabs = 0.0f, zmin = 0.0f, zmax = 0.0f, dmin = 0.0f, dmax = 0.0f;
+        if (n) {
+            lo = bcast_f(b.x[0], 0);
+            xabs = fmaxf(fabsf(lo), fabsf(b.last));
+            zmin = zmax = bcast_f(b.z[0], 0);
+            dmin = dmax = bcast_f(b.d[0], 0);
+            // (the scale need not be exact: hits and keys are placed by the same one)
+            scale = (float)IDX_CELLS * __builtin_amdgcn_rcpf(b.last - lo);
+            if (!(b.last > lo) || !(scale < INFINITY)) scale = 0.0f;   // one cell
+            if (__float_as_uint(zmin) != __float_as_uint(P->z[k >> 1]) ||
+                (is_uv(k >> 1) && __float_as_uint(dmin) != __float_as_uint(P->dxdy[k >> 1])))
+                odd |= 4;
+        }
+        const uint32_t z0 = __float_as_uint(zmin), d0 = __float_as_uint(dmin);
+        if (n > IDX_MAX_BUCKET) odd |= 2;
+        const bool index = bidx && n <= IDX_MAX_BUCKET;
+        int before = -1;   // cell of the hit before this round's first
+        bool differ = false;
+        for (uint32_t i0 = 0; i0 < n; i0 += EVI_ROUNDS * WAVE) {
+            Bucket next = b;   // the following round of a long bucket, loaded while this one is used
+            if (i0 + EVI_ROUNDS * WAVE < n) load(next, i0 + EVI_ROUNDS * WAVE);
+#pragma unroll
+            for (int r = 0; r < EVI_ROUNDS; ++r) {
+                if (i0 + (uint32_t)(r * WAVE) >= n) continue;
+                const uint32_t i = i0 + (uint32_t)(r * WAVE + lane);
+                if (__float_as_uint(b.z[r]) != z0 || __float_as_uint(b.d[r]) != d0) differ = true;
+                zmin = fminf(zmin, b.z[r]);
+                zmax = fmaxf(zmax, b.z[r]);
+                dmin = fminf(dmin, b.d[r]);
+                dmax = fmaxf(dmax, b.d[r]);
+                if (index) {
+                    const int c = index_cell(b.x[r], lo, scale);
+                    int cp = __shfl_up(c, 1);
+                    if (lane == 0) cp = before;
+                    if (i < n)
+                        for (int p = cp + 1; p <= c; ++p) rec[w].start[p] = (uint16_t)i;
+                    before = __builtin_amdgcn_readlane(c, WAVE - 1);
+                }
+            }
+            b = next;
+        }
+        if (__ballot(differ)) {
+            odd |= 1;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                zmin = fminf(zmin, __shfl_xor(zmin, off));
+                zmax = fmaxf(zmax, __shfl_xor(zmax, off));
+                dmin = fminf(dmin, __shfl_xor(dmin, off));
+                dmax = fmaxf(dmax, __shfl_xor(dmax, off));
+            }
+        }
+        if (bidx) {
+            if (index)
+                for (int p = before + 1 + lane; p <= IDX_CELLS; p += WAVE) rec[w].start[p] = (uint16_t)n;
+            if (lane == 0) {
+                rec[w].lo = lo;
+                rec[w].scale = scale;
+                rec[w].zmin = zmin;
+                rec[w].zmax = zmax;
+                rec[w].dspread = dmax - dmin;
+                rec[w].dabs = fmaxf(fabsf(dmin), fabsf(dmax));
+                rec[w].xabs = xabs;
+            }
+            wave_sync();
+            uint32_t *o = reinterpret_cast<uint32_t *>(bidx + ((size_t)e * 2 * NL + (uint32_t)k));
+            if (lane < (int)sizeof(BucketIndex) / 4) o[lane] = reinterpret_cast<const uint32_t *>(&rec[w])[lane];
+            wave_sync();
+        }
+    }
+    for (uint32_t t = B.trk_off[e] + threadIdx.x, t1 = B.trk_off[e + 1]; t < t1; t += blockDim.x) trk_ev[t] = e;
+    const int any = __syncthreads_or(odd & 1), lng = __syncthreads_or(odd & 2), off = __syncthreads_or(odd & 5);
+    if (threadIdx.x == 0) uni[e] = (uint8_t)((any ? 0 : EV_UNIFORM) | (off ? 0 : EV_PLANES) | (lng ? EV_NO_INDEX : 0));
 }
 
-// One block per event: uni[e] = 1 when, in each of the event's 24 buckets,
-// every hit has the z and the stereo tangent of the bucket's first hit (bit
-// for bit).  Such events need only x staged per hit.  The event's hits are
-// streamed once, each compared with its predecessor; a difference is allowed
-// only where a bucket starts.
-__global__ void __launch_bounds__(1024) k_event_uniform(const uint32_t *__restrict__ hit_off,
-                                                        const float *__restrict__ hz,
-                                                        const float *__restrict__ hd, uint8_t *__restrict__ uni) {
-    __shared__ uint32_t off[2 * NL + 1];
-    const uint32_t e = blockIdx.x;
-    if (threadIdx.x <= 2 * NL) off[threadIdx.x] = hit_off[2 * NL * e + threadIdx.x];
-    __syncthreads();
-    const uint32_t f = off[0], n = off[2 * NL];
-    int odd = 0;
-    for (uint32_t i = f + 1 + threadIdx.x; i < n; i += blockDim.x) {
-        const uint32_t dz = __float_as_uint(hz[i]) ^ __float_as_uint(hz[i - 1]);
-        const uint32_t dd = __float_as_uint(hd[i]) ^ __float_as_uint(hd[i - 1]);
-        if ((dz | dd) == 0) continue;
-        bool start = false;
-        for (int k = 1; k < 2 * NL; ++k) start |= off[k] == i;
-        odd |= !start;
+// The rows of KParams::fit_tab, one thread each, from the parameters already
+// in device memory: the expressions of Track::run's fits at the layer planes,
+// in the same order.
+__global__ void __launch_bounds__(256) k_fit_table(const KParams *__restrict__ P, FitRow *__restrict__ rows) {
+    const uint32_t mask = blockIdx.x * blockDim.x + threadIdx.x;
+    if (mask >= FIT_ROWS) return;
+    float S1 = 0.0f, S2 = 0.0f, S11 = 0.0f, S12 = 0.0f, S22 = 0.0f, YS1 = 0.0f, YS11 = 0.0f;
+    int n = 0, n_uv = 0;
+    for (int l = 0; l < NL; ++l) {
+        if (!((mask >> l) & 1u)) continue;
+        const float u = P->z[l] - P->z_ref;
+        const float s = u * INV1024, h = s * s * (1.0f + P->dRatio * u);
+        S1 = S1 + s;
+        S2 = S2 + h;
+        S11 = S11 + s * s;
+        S12 = S12 + s * h;
+        S22 = S22 + h * h;
+        ++n;
+        if (is_uv(l)) {
+            YS1 = YS1 + s;
+            YS11 = YS11 + s * s;
+            ++n_uv;
+        }
     }
-    odd = __syncthreads_or(odd);
-    if (threadIdx.x == 0) uni[e] = odd ? 0 : 1;
+    FitRow r;
+    r.S0 = (float)n; r.S1 = S1; r.S2 = S2; r.S11 = S11; r.S12 = S12; r.S22 = S22;
+    r.m00 = S11 * S22 - S12 * S12;
+    r.m01 = S1 * S22 - S12 * S2;
+    r.m02 = S1 * S12 - S11 * S2;
+    r.det = r.S0 * r.m00 - S1 * r.m01 + S2 * r.m02;
+    r.YS0 = (float)n_uv; r.YS1 = YS1; r.YS11 = YS11;
+    r.D = r.YS0 * YS11 - YS1 * YS1;
+    r.C = P->C_nhits[n - 9 < 0 ? 0 : (n - 9 > 3 ? 3 : n - 9)];
+    r.unused = 0.0f;
+    rows[mask] = r;
 }
 
 template <int NW, int NS, int WPB, bool H16>
 hipError_t launch_nw_wpb(const DevBatch &b, const KParams *P, int mode, const ExecCfg &cfg,
                          const uint32_t *trk_off_host, hipStream_t s) {
     const dim3 block(WPB * WAVE);
+    const uint32_t n = b.trk_map ? b.n_map : b.n_tracks;
+    const bool pair = cfg.pair_min && n >= cfg.pair_min && b.bidx;
     if (mode == 0) {   // plain: one launch per event
         for (uint32_t e = 0; e < b.n_events; ++e) {
             const uint32_t nt = trk_off_host[e + 1] - trk_off_host[e];
@@ -1653,10 +1837,29 @@ hipError_t launch_nw_wpb(const DevBatch &b, const KParams *P, int mode, const Ex
         const uint32_t need = (b.n_tracks + WPB - 1) / WPB;
         if (grid > need) grid = need;
         if (grid == 0) grid = 1;
+        if constexpr (NS == 1 && !H16) {
+            if (pair) {
+                const uint32_t items = (uint32_t)cfg.items_per_grab;
+                if (cfg.n_triplets <= 16)
+                    hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, 16>), dim3(grid), block, 0, s, b, P, items);
+                else
+                    hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, MAX_TRIPLETS>), dim3(grid), block, 0, s, b, P, items);
+                return hipGetLastError();
+            }
+        }
         hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16>), dim3(grid), block, 0, s, b, P,
                            (uint32_t)cfg.items_per_grab);
     } else {   // batched: one launch, one wavefront per track (or per mapped slot), XCD-ordered
-        const uint32_t need = ((b.trk_map ? b.n_map : b.n_tracks) + WPB - 1) / WPB;
+        if constexpr (NS == 1 && !H16) {
+            if (pair) {
+                const uint32_t pairs = ((n + 1) / 2 + WPB - 1) / WPB;
+                const dim3 g((pairs + NXCD - 1) / NXCD * NXCD);
+                if (cfg.n_triplets <= 16) hipLaunchKernelGGL((k_pair<NW, 16, WPB>), g, block, 0, s, b, P);
+                else hipLaunchKernelGGL((k_pair<NW, MAX_TRIPLETS, WPB>), g, block, 0, s, b, P);
+                return hipGetLastError();
+            }
+        }
+        const uint32_t need = (n + WPB - 1) / WPB;
         const uint32_t grid = (need + NXCD - 1) / NXCD * NXCD;
         if (grid) hipLaunchKernelGGL((k_grid<NW, NS, WPB, false, H16>), dim3(grid), block, 0, s, b, P);
     }
@@ -1799,16 +2002,10 @@ hipError_t launch_track_map(const uint32_t *evs, const uint32_t *toff, uint32_t 
     return hipGetLastError();
 }
 
-hipError_t launch_track_event(const DevBatch &b, hipStream_t s) {
-    if (b.n_tracks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_track_event, dim3((b.n_tracks + 255) / 256), dim3(256), 0, s, b.trk_off, b.n_events,
-                       b.n_tracks, const_cast<uint32_t *>(b.trk_ev));
-    return hipGetLastError();
-}
-
-hipError_t launch_event_uniform(const DevBatch &b, uint8_t *uni, hipStream_t s) {
+hipError_t launch_event_index(const DevBatch &b, const KParams *P, uint8_t *uni, hipStream_t s) {
     if (b.n_events == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_event_uniform, dim3(b.n_events), dim3(1024), 0, s, b.hit_off, b.hz, b.hd, uni);
+    hipLaunchKernelGGL(k_event_index, dim3(b.n_events), dim3(EVI_WAVES * WAVE), 0, s, b, P, uni,
+                       const_cast<BucketIndex *>(b.bidx), const_cast<uint32_t *>(b.trk_ev));
     return hipGetLastError();
 }
 
@@ -1827,29 +2024,60 @@ hipError_t launch_find(const DevBatch &b, const KParams *P, int n_hits_window, i
     return launch_nw<64, 1>(b, P, mode, cfg, trk_off_host, s);
 }
 
+// The expressions of Track::run's triplet model at the layer planes, in the
+// same order (host binary32, compiled without contraction).
+void plane_constants(KParams &k) {
+    auto g = [&](float u) { return u * u * (1.0f + k.dRatio * u); };
+    for (int l = 0; l < NL; ++l) {
+        k.lay_u[l] = k.z[l] - k.z_ref;
+        k.lay_g[l] = g(k.lay_u[l]);
+    }
+    k.pair_ok = 1;
+    for (int s = 0; s < 2; ++s) {
+        const int l0 = s ? 3 : 0, l1 = s ? 7 : 4, l2 = s ? 11 : 8;
+        const float lev = k.z_mag - k.z[l0];
+        k.set_dz[s] = k.z[l2] - k.z[l0];
+        k.set_rlev[s] = 1.0f / lev;
+        k.set_du01[s] = k.lay_u[l1] - k.lay_u[l0];
+        k.set_du12[s] = k.lay_u[l2] - k.lay_u[l1];
+        k.set_G01[s] = (k.lay_g[l1] - k.lay_g[l0]) / k.set_du01[s];
+        const float G12 = (k.lay_g[l2] - k.lay_g[l1]) / k.set_du12[s];
+        k.set_dG[s] = G12 - k.set_G01[s];
+        if (!((lev > 1.0f || lev < -1.0f) && k.set_dz[s] > 1.0f)) k.pair_ok = 0;
+    }
+}
+
+hipError_t launch_fit_table(const KParams *P, FitRow *rows, hipStream_t s) {
+    hipLaunchKernelGGL(k_fit_table, dim3(FIT_ROWS / 256), dim3(256), 0, s, P, rows);
+    return hipGetLastError();
+}
+
 namespace {
-template <int NW, int NS, int WPB, bool H16>
+template <int NW, int NS, int WPB, bool H16, int MT>
 int occ() {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(&k_persistent<NW, NS, WPB, H16>),
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(&k_persistent<NW, NS, WPB, H16, MT>),
                                                      WPB * WAVE, 0) != hipSuccess)
         return 0;
     return n;
 }
 }  // namespace
 
-template <int NW, int NS, bool H16 = false>
+template <int NW, int NS, bool H16 = false, int MT = 0>
 int occ_wpb(int waves_per_block) {
-    if (waves_per_block == 1) return occ<NW, NS, 1, H16>();
-    if (waves_per_block == 2) return occ<NW, NS, 2, H16>();
-    return occ<NW, NS, 4, H16>();
+    if (waves_per_block == 1) return occ<NW, NS, 1, H16, MT>();
+    if (waves_per_block == 2) return occ<NW, NS, 2, H16, MT>();
+    return occ<NW, NS, 4, H16, MT>();
 }
 
-int persistent_blocks_per_cu(int n_hits_window, int n_sides, int waves_per_block) {
-    if (n_sides == 2) return n_hits_window <= 32 ? occ_wpb<32, 2>(waves_per_block) : occ_wpb<64, 2>(waves_per_block);
-    if (n_sides == 3)
-        return n_hits_window <= 32 ? occ_wpb<32, 1, true>(waves_per_block) : occ_wpb<64, 1, true>(waves_per_block);
-    return n_hits_window <= 32 ? occ_wpb<32, 1>(waves_per_block) : occ_wpb<64, 1>(waves_per_block);
+int persistent_blocks_per_cu(int n_hits_window, int n_sides, const ExecCfg &cfg) {
+    const int w = cfg.waves_per_block;
+    if (n_sides == 2) return n_hits_window <= 32 ? occ_wpb<32, 2>(w) : occ_wpb<64, 2>(w);
+    if (n_sides == 3) return n_hits_window <= 32 ? occ_wpb<32, 1, true>(w) : occ_wpb<64, 1, true>(w);
+    if (!cfg.pair_min) return n_hits_window <= 32 ? occ_wpb<32, 1>(w) : occ_wpb<64, 1>(w);
+    if (cfg.n_triplets <= 16)
+        return n_hits_window <= 32 ? occ_wpb<32, 1, false, 16>(w) : occ_wpb<64, 1, false, 16>(w);
+    return n_hits_window <= 32 ? occ_wpb<32, 1, false, MAX_TRIPLETS>(w) : occ_wpb<64, 1, false, MAX_TRIPLETS>(w);
 }
 
 }  // namespace lfk

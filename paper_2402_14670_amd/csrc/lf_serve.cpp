@@ -118,6 +118,8 @@ struct Slot {
     lfk::GatherDesc *stage = nullptr;   // pinned, event descriptors of one batch
     char *out = nullptr;     // pinned, outputs of one batch
     size_t stage_cap = 0, out_cap = 0;
+    lfk::BucketIndex *idx = nullptr;    // host pool: bucket indexes of one batch of up to idx_cap events
+    uint32_t idx_cap = 0;
     bool busy = false;
     size_t ring_at = 0, ring_bytes = 0;
     BatchLayout lay{};
@@ -210,6 +212,7 @@ extern "C" int lf_serve_run(lf_ctx *ctx, const lf_batch *pool_b, uint32_t n_requ
             if (s.stream) (void)hipStreamDestroy(s.stream);
             if (s.stage) (void)hipHostFree(s.stage);
             if (s.out) (void)hipHostFree(s.out);
+            if (s.idx) (void)hipFree(s.idx);
         }
         if (ring_mem) (void)hipFree(ring_mem);
         if (pool_hbm) (void)hipFree(pool_hbm);
@@ -268,7 +271,16 @@ extern "C" int lf_serve_run(lf_ctx *ctx, const lf_batch *pool_b, uint32_t n_requ
         }
         s.stage_cap = cfg.max_batch_events;
         s.out_cap = biggest.out_bytes;
-
+        // (beside the ring: the budget counts the events alone; larger batches go without)
+        if (!dev_pool) {
+            const uint32_t cap = std::min<uint32_t>(cfg.max_batch_events, lfk::FIXED_IDX_EVENTS);
+            if (hipMalloc(reinterpret_cast<void **>(&s.idx), (size_t)cap * 24 * sizeof(lfk::BucketIndex)) == hipSuccess) {
+                s.idx_cap = cap;
+            } else {
+                (void)hipGetLastError();
+                s.idx = nullptr;
+            }
+        }
     }
     // A host pool: the gather kernel reads the pinned blobs over the host
     // link.  A device pool: copied once (before the clock) as one resident
@@ -281,8 +293,15 @@ extern "C" int lf_serve_run(lf_ctx *ctx, const lf_batch *pool_b, uint32_t n_requ
         auto put = [&](size_t n) { size_t at = o; o += a256(n ? n : 1); return at; };
         const size_t o_ho = put(((size_t)PE * 24 + 1) * 4), o_hx = put((size_t)PH * 4), o_hz = put((size_t)PH * 4),
                      o_hd = put((size_t)PH * 4), o_to = put(((size_t)PE + 1) * 4), o_te = put((size_t)PT * 4),
-                     o_tr = put((size_t)PT * 20), o_uni = put(PE);
-        err = hipMalloc(reinterpret_cast<void **>(&pool_hbm), o);
+                     o_tr = put((size_t)PT * 20), o_uni = put(PE), o_idx = o;
+        // the bucket indexes, if the memory can be had
+        const size_t idx = (size_t)PE * 24 * sizeof(lfk::BucketIndex);
+        err = hipMalloc(reinterpret_cast<void **>(&pool_hbm), o + idx);
+        const bool indexed = err == hipSuccess;
+        if (!indexed) {
+            (void)hipGetLastError();
+            err = hipMalloc(reinterpret_cast<void **>(&pool_hbm), o);
+        }
         if (err != hipSuccess) {
             cleanup();
             return lfapi::ctx_fail(ctx, LF_ERR_NOMEM, "lf_serve_run: device pool allocation failed");
@@ -310,10 +329,10 @@ extern "C" int lf_serve_run(lf_ctx *ctx, const lf_batch *pool_b, uint32_t n_requ
         pool_d.tty = pool_d.tx_ + 3 * (size_t)PT;
         pool_d.tqop = pool_d.tx_ + 4 * (size_t)PT;
         pool_d.uni = reinterpret_cast<const uint8_t *>(b + o_uni);
+        pool_d.bidx = indexed ? reinterpret_cast<const lfk::BucketIndex *>(b + o_idx) : nullptr;
         pool_d.n_events = PE;
         pool_d.n_tracks = PT;
-        if (err == hipSuccess) err = lfk::launch_track_event(pool_d, slots[0].stream);
-        if (err == hipSuccess) err = lfk::launch_event_uniform(pool_d, reinterpret_cast<uint8_t *>(b + o_uni), slots[0].stream);
+        if (err == hipSuccess) err = lfk::launch_event_index(pool_d, lfapi::ctx_dparams(ctx), reinterpret_cast<uint8_t *>(b + o_uni), slots[0].stream);
         if (err == hipSuccess) err = hipStreamSynchronize(slots[0].stream);
     } else {
         err = hipHostGetDevicePointer(reinterpret_cast<void **>(&pool_dev), pool.blob, 0);
@@ -402,6 +421,7 @@ extern "C" int lf_serve_run(lf_ctx *ctx, const lf_batch *pool_b, uint32_t n_requ
         d.tty = in.tty;
         d.tqop = in.tqop;
         d.uni = reinterpret_cast<const uint8_t *>(dr + lay.uni);
+        d.bidx = E <= s.idx_cap ? s.idx : nullptr;
         d.found = reinterpret_cast<uint8_t *>(dr + lay.found);
         d.nhits = reinterpret_cast<uint8_t *>(dr + lay.nhits);
         d.hit_idx = reinterpret_cast<int32_t *>(dr + lay.hit_idx);
@@ -416,7 +436,7 @@ extern "C" int lf_serve_run(lf_ctx *ctx, const lf_batch *pool_b, uint32_t n_requ
         hipError_t e = hipMemcpyAsync(dr + lay.desc, s.stage, (size_t)E * sizeof(lfk::GatherDesc),
                                       hipMemcpyHostToDevice, s.stream);
         if (e == hipSuccess) e = lfk::launch_gather(ddesc, E, in, s.stream);
-        if (e == hipSuccess) e = lfk::launch_event_uniform(d, reinterpret_cast<uint8_t *>(dr + lay.uni), s.stream);
+        if (e == hipSuccess) e = lfk::launch_event_index(d, P, reinterpret_cast<uint8_t *>(dr + lay.uni), s.stream);
         if (e == hipSuccess) e = lfk::launch_find(d, P, nhw, n_sides, 1, exec, nullptr, s.stream);
         if (e == hipSuccess)
             e = lfk::launch_digest(d, d.trk_off, E, reinterpret_cast<unsigned long long *>(dr + lay.dig), s.stream);
