@@ -46,12 +46,14 @@ struct KParams {
     // Triplet seeding in binary16 (VELO-UT input only)
     int32_t seed_fp16;
     // What hits on the layer planes make constant (two tracks per wavefront,
-    // lf_pair.h): u = z - z_ref and g(u) of each layer; per seed set (layers
+    // lf_pair.h): u = z - z_ref and g(u) of each layer, and the fits' s = u / 1024
+    // and h = s^2 (1 + dRatio u); per seed set (layers
     // l0, l1, l2): z_l2 - z_l0, 1 / (z_mag - z_l0) (bracket only), and the
     // triplet model's u1 - u0, u2 - u1, G01 and G12 - G01; fit_tab[mask]
     // for each 12-bit mask of layers with a hit.  pair_ok: the planes allow
     // that path (lever arms and set lengths above 1 mm).
-    float lay_u[NL], lay_g[NL];
+    alignas(16) float lay_u[NL];
+    float lay_g[NL], lay_s[NL], lay_h[NL];
     float set_dz[2], set_rlev[2], set_du01[2], set_du12[2], set_G01[2], set_dG[2];
     int32_t pair_ok;
     const FitRow *fit_tab;   // [FIT_ROWS] device memory

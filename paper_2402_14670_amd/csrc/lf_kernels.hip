@@ -1503,10 +1503,10 @@ __device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams 
     }
 }
 
-// Batched mode, two tracks per wavefront.  (7 waves per SIMD: 72 registers, a
-// few spilled; 5 to 7 waves measure within 2%.)
+// Batched mode, two tracks per wavefront.  (6 waves per SIMD: 80 registers; 5
+// and 7 measure within 2%.)
 template <int NW, int MT, int WPB>
-__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NW == 32 && MT == 16 ? 7 : 1))) void k_pair(DevBatch B, const KParams *__restrict__ P) {
+__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NW == 32 && MT == 16 ? 6 : 1))) void k_pair(DevBatch B, const KParams *__restrict__ P) {
     __shared__ PairLds<NW, MT> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const uint32_t per = gridDim.x / NXCD;
@@ -2031,6 +2031,8 @@ void plane_constants(KParams &k) {
     for (int l = 0; l < NL; ++l) {
         k.lay_u[l] = k.z[l] - k.z_ref;
         k.lay_g[l] = g(k.lay_u[l]);
+        k.lay_s[l] = k.lay_u[l] * INV1024;
+        k.lay_h[l] = k.lay_s[l] * k.lay_s[l] * (1.0f + k.dRatio * k.lay_u[l]);
     }
     k.pair_ok = 1;
     for (int s = 0; s < 2; ++s) {

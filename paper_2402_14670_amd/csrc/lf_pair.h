@@ -11,19 +11,23 @@
 // Much of a track's work is the same in every lane (kinematics, list handling)
 // or has fewer items than a wavefront has lanes (about 24 seed pairs, 7 kept
 // triplets, 2.6 fits), so with 32 lanes per track each of those instructions
-// serves two tracks: 1,424 -> 890 vector instructions per track.  What else
-// differs from the one-track body:
+// serves two tracks.  What else differs from the one-track body:
 //  - windows are padded with +inf, so a sorted search needs no length;
 //  - the pairs of all brackets are laid end to end in a queue (92% of them
 //    pass the filters), and filter, middle hit and cut run once per pair;
+//  - a fit takes four lanes, one per station, instead of sixteen, one per
+//    layer: the 2.6 fits of a track fill one pass, and its serial sums need two
+//    steps between lanes instead of a transpose through LDS or eleven steps;
 //  - in events whose hits lie on the layer planes (EV_PLANES) every expression
 //    of the layer z alone is a constant of the context (KParams::lay_*, set_*,
 //    fit_tab), and no z or slope is loaded at all;
 //  - in the others (PL = false) stereo hits are staged moved along their fibre
 //    to the track's y, which is the same for every candidate, and the closest
 //    one is found by a search and a short walk.
-// 200,000 nominal tracks: 0.377 -> 0.244 ms; 160,000 with per-hit z and
-// slopes: 0.445 -> 0.262 ms; 121,500 in dense events: 0.476 -> 0.390 ms.
+// Launches before (one track per wavefront) and now: 200,000 nominal tracks
+// 0.377 -> 0.226 ms (with sixteen lanes per fit 0.244); 160,000 with per-hit z
+// and slopes 0.445 -> 0.250 (0.265); 121,500 in dense events 0.477 -> 0.364
+// (0.391); 4,800 nominal 0.0204 -> 0.0160 (0.0199).
 
 // One track's LDS: the x of its window hits (row l: layer l, NW slots, +inf
 // past the window's end, so that a sorted search needs no length), per layer
@@ -32,14 +36,11 @@ template <int NW, int MT>
 struct alignas(16) HalfLds {
     static constexpr int RS = NW + 1;
     static constexpr int QP = 64;    // queued seed pairs
-    union {
-        struct {
-            uint64_t tk[MT];         // top-n keys, sorted; ~0 past the list
-            int2 win[NL];            // first hit (event-local) and length of each window
-            uint8_t th1[MT];         // middle hit of each kept triplet
-        };
-        float sums[2][3 * 12];       // scratch of the fits' serial sums
-    };
+    uint64_t tk[MT];                 // top-n keys, sorted; ~0 past the list
+    int2 win[NL];                    // first hit (event-local) and length of each window
+    uint8_t th1[MT];                 // middle hit of each kept triplet
+    uint8_t fl[MT];                  // ranks of the candidates to fit
+    float4 fit[2];                   // the best candidate: a, b, c, y0; ty, Q, hits
     float4 lay[NL];                  // u, g(u), dxdy * y_ext (0 on x layers), unused
     union {
         struct {
@@ -56,9 +57,6 @@ struct alignas(16) HalfLds {
     };
     float wx[NL * RS];
     float2 zr[2];                    // z range of each seed set's third bucket (hits off the planes)
-    float T_uv, yr, yin, ty;         // stereo tolerance, input y line at z_ref and z_in, its slope
-    float best[6];                   // the best candidate: a, b, c, y0, ty, Q
-    int32_t best_n;
 };
 
 template <int NW, int MT>
@@ -260,12 +258,7 @@ struct Pair {
         }
         if (j < MT) L.tk[j] = ~0ull;
         const float T_uv0 = P->T_uv_scale * (fabsf(tx_in) + fabsf(ty_in));
-        if (j == 0) {
-            L.T_uv = T_uv0 < P->T_uv_floor ? P->T_uv_floor : T_uv0;
-            L.yr = y_in + ty_in * (P->z_ref - P->z_in);
-            L.yin = y_in;
-            L.ty = ty_in;
-        }
+        const float T_uv = T_uv0 < P->T_uv_floor ? P->T_uv_floor : T_uv0;
         wave_sync();
 
         // ---- stage window hits: round (l, k) brings hits 32 k .. of layer l ----
@@ -385,31 +378,32 @@ struct Pair {
 
         int best_r = -1;    // this half's best candidate
         if (halfmax(nL) > 0) {
-            candidates(lane, nL);
-            best_r = fits(lane, nL);
+            candidates(lane, nL, T_uv);
+            best_r = fits(lane, nL, T_uv, y_in, ty_in);
         }
 
         // ---- output ----
         if (!act) return;
         const bool found = best_r >= 0;
         if (j == 0) {
-            const float bfa = L.best[0], bfb = L.best[1], bfc = L.best[2], bfy0 = L.best[3], bfty = L.best[4];
+            const float4 f0 = L.fit[0], f1 = L.fit[1];
+            const float bfa = f0.x, bfb = f0.y, bfc = f0.z, bfy0 = f0.w, bfty = f1.x;
             const float uT = P->z_T - P->z_ref;
             const float txT = bfb + 2.0f * bfc * uT + 3.0f * bfc * dR * uT * uT;
             const float qo = paper ? (kick_s(txT, bfty) - kick_s(tx_in, ty_in)) / field_F(fc, txT - tx_in)
                                    : (txT - tx_in) / P->kick;
             B.found[t] = found ? 1 : 0;
-            B.nhits[t] = found ? (uint8_t)L.best_n : 0;
+            B.nhits[t] = found ? (uint8_t)__float_as_int(f1.z) : 0;
             B.a[t] = found ? bfa : 0.0f;
             B.b[t] = found ? bfb : 0.0f;
             B.c[t] = found ? bfc : 0.0f;
             B.y0[t] = found ? bfy0 : 0.0f;
             B.ty[t] = found ? bfty : 0.0f;
             B.qop[t] = found ? qo : 0.0f;
-            B.Q[t] = found ? L.best[5] : 0.0f;
+            B.Q[t] = found ? f1.y : 0.0f;
         }
         if (j < NL) {
-            const int h = found ? (int)L.ch[best_r & (MT - 1)][j] : -1;
+            const int h = found ? (int)L.ch[best_r][j] : -1;
             B.hit_idx[(size_t)t * NL + j] = h >= 0 ? first + h : -1;
         }
     }
@@ -505,7 +499,7 @@ struct Pair {
 
     // Triplet x(z) models, one lane per kept triplet, and the extension to
     // the missing layers, two (candidate, layer) items per lane.
-    __device__ __forceinline__ void candidates(int lane, int nL) {
+    __device__ __forceinline__ void candidates(int lane, int nL, float T_uv) {
         const int j = lane & (HALF - 1);
         HalfLds<NW, MT> &L = S.h[lane >> 5];
         if (j < nL) {
@@ -551,7 +545,6 @@ struct Pair {
         }
         wave_sync();
 
-        const float T_uv = L.T_uv;
         const int n_items = nL * NSLOT, n_max = halfmax(n_items);
         struct Item {
             int r, l;
@@ -616,126 +609,141 @@ struct Pair {
         wave_sync();
     }
 
-    // Serial sums over the 12 layer lanes of each 16-lane row, in layer
-    // order from +0, the same in every lane of the row (Track::row_sums_lds).
+    // The serial sum over the 12 layers of a candidate, ((+0 + t_0) + t_1) + ...,
+    // from the n terms each of a quad's lanes 0..2 holds of its station (in
+    // layer order): every lane adds its terms three times, starting from +0 and
+    // then from the lane before it, so that lane 2 ends with the whole sum,
+    // which the quad receives.
     template <int N>
-    __device__ __forceinline__ void row_sums(const float (&t)[N], float (&s)[N], int g, int j) {
-        static_assert(N <= 3, "sums holds three sums per row");
-        float *sums = S.h[g >> 1].sums[g & 1];
-        wave_sync();
-        if (j < NL) {
+    __device__ __forceinline__ static float quad_sum(const float (&t)[N]) {
+        float s = 0.0f;
 #pragma unroll
-            for (int k = 0; k < N; ++k) sums[k * 12 + j] = t[k];
-        }
-        wave_sync();
-        float v = 0.0f;
-        if (j < N) {
-            const float4 *q = reinterpret_cast<const float4 *>(&sums[j * 12]);
-            const float4 q0 = q[0], q1 = q[1], q2 = q[2];
-            v = 0.0f + q0.x;
-            v = v + q0.y; v = v + q0.z; v = v + q0.w;
-            v = v + q1.x; v = v + q1.y; v = v + q1.z; v = v + q1.w;
-            v = v + q2.x; v = v + q2.y; v = v + q2.z; v = v + q2.w;
-        }
+        for (int i = 0; i < N; ++i) s = s + t[i];
 #pragma unroll
-        for (int k = 0; k < N; ++k) s[k] = row_bcast_lane(v, k);
+        for (int k = 0; k < 2; ++k) {
+            s = quad<0x90>(s);   // from the lane before (lane 0: its own)
+#pragma unroll
+            for (int i = 0; i < N; ++i) s = s + t[i];
+        }
+        return quad<0xAA>(s);
+    }
+    template <int PERM>
+    __device__ __forceinline__ static float quad(float v) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), PERM, 0xF, 0xF, true));
+    }
+    template <int PERM>
+    __device__ __forceinline__ static uint32_t quad(uint32_t v) {
+        return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, PERM, 0xF, 0xF, true);
     }
 
-    // Fits and quality: 16 lanes per candidate, four candidates of the two
-    // tracks per pass in (half, rank) order.  Every sum of the layer terms
-    // alone depends only on which layers have a hit: FitRow of that 12-bit
-    // mask, tabulated per context.  Returns the half's best candidate (its
-    // fit is in best[]), or -1.
-    __device__ __forceinline__ int fits(int lane, int nL) {
-        uint64_t fitm;
+    // Fits and quality: four lanes per candidate, eight candidates of each
+    // track per pass in rank order.  Lanes 0..2 of a quad hold the four layers
+    // (x u v x) of a station each, so a sum over the layers is two steps
+    // between lanes, and the x and stereo formulas need no selection.  The
+    // sums of the layer terms alone depend only on which layers have a hit:
+    // FitRow of that 12-bit mask, tabulated per context (hits on the planes).
+    // Returns the half's best candidate (its fit is in fit[]), or -1.
+    __device__ __forceinline__ int fits(int lane, int nL, float T_uv, float y_in, float ty_in) {
+        const int j = lane & (HALF - 1);
+        HalfLds<NW, MT> &L = S.h[lane >> 5];
+        uint32_t mine;   // the half's candidates to fit
         {
-            const int jj = lane & (HALF - 1);
-            const HalfLds<NW, MT> &L = S.h[lane >> 5];
             bool rule = false;
-            if (jj < nL) {
+            if (j < nL) {
                 int n = 0;
                 bool st_ok = true;
 #pragma unroll
                 for (int st = 0; st < 3; ++st) {
-                    const uint32_t pres = ~L.chw[jj][st] & 0x80808080u;
+                    const uint32_t pres = ~L.chw[j][st] & 0x80808080u;
                     n += __popc(pres);
                     st_ok = st_ok && (pres & 0x00808000u) != 0u;
                 }
                 rule = n >= 9 && st_ok;
             }
-            fitm = __ballot(rule);
+            const uint64_t bal = __ballot(rule);
+            mine = lane >= HALF ? (uint32_t)(bal >> HALF) : (uint32_t)bal;
+            if (rule) L.fl[__popc(mine & ((1u << j) - 1u))] = (uint8_t)j;
         }
-        int best0 = -1, best1 = -1;
-        float Q0 = 0.0f, Q1 = 0.0f;
-        const int g = lane >> 4, j = lane & 15;
-        const bool lay = j < NL;
-        const bool uvj = lay && is_uv(j);
-        constexpr int LR = NL - 1;
-        const int jl = lay ? j : 0;
+        const int nf = __popc(mine), nf_max = halfmax(nf);
+        wave_sync();
+        int best_r = -1;
+        float best_Q = 0.0f;
+        const int st = j & 3, sq = st < 3 ? st : 0;   // lane 3 holds no layers
         const float dR = P->dRatio;
-        float u = P->lay_u[jl], gu = P->lay_g[jl], dxy = uvj ? P->dxdy[jl] : 1.0f;
-        float sv = u * INV1024;
-        float h = sv * sv * (1.0f + dR * u);
-        while (fitm) {
-            int id = -1;   // candidate: half * 32 + rank
-            int rq[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                rq[k] = fitm ? (int)__builtin_ctzll(fitm) : -1;
-                if (fitm) fitm &= fitm - 1;
-                if (k == g) id = rq[k];
-            }
-            const int r = id & (HALF - 1);
-            HalfLds<NW, MT> &L = S.h[(id >> 5) & 1];
-            const int hit = id >= 0 && lay ? (int)L.ch[r][j] : -1;
-            const bool pres = hit >= 0;
-            const bool pres_uv = pres && uvj;
+        float u[4], gu[4], sv[4], h[4], cuv[2], dxy[2];
+        if constexpr (PL) {
+            const float4 u4 = *reinterpret_cast<const float4 *>(&P->lay_u[4 * sq]);
+            const float4 g4 = *reinterpret_cast<const float4 *>(&P->lay_g[4 * sq]);
+            const float4 s4 = *reinterpret_cast<const float4 *>(&P->lay_s[4 * sq]);
+            const float4 h4 = *reinterpret_cast<const float4 *>(&P->lay_h[4 * sq]);
+            u[0] = u4.x; u[1] = u4.y; u[2] = u4.z; u[3] = u4.w;
+            gu[0] = g4.x; gu[1] = g4.y; gu[2] = g4.z; gu[3] = g4.w;
+            sv[0] = s4.x; sv[1] = s4.y; sv[2] = s4.z; sv[3] = s4.w;
+            h[0] = h4.x; h[1] = h4.y; h[2] = h4.z; h[3] = h4.w;
+            cuv[0] = L.lay[4 * sq + 1].z; cuv[1] = L.lay[4 * sq + 2].z;
+            dxy[0] = P->dxdy[4 * sq + 1]; dxy[1] = P->dxdy[4 * sq + 2];
+        }
+        for (int f0 = 0; f0 < nf_max; f0 += HALF / 4) {
+            const int k = f0 + (j >> 2);
+            const bool on = k < nf;
+            const int r = on ? (int)L.fl[k] : 0;
             const float a = L.ca[r], b = L.cb[r], c = L.cc[r];
-            const uint32_t mask = (uint32_t)(__ballot(pres) >> (16 * g)) & 0xFFFu;
+            const uint32_t word = on && st < 3 ? L.chw[r][sq] : ~0u;
+            const uint32_t absent = word & 0x80808080u;
+            // the layers with a hit: four bits per station
+            uint32_t mask = (((~word & 0x80808080u) * 0x204081u) >> 28) << (4 * sq);
+            mask |= quad<0xB1>(mask);   // lanes 1 0 3 2
+            mask |= quad<0x4E>(mask);   // lanes 2 3 0 1
             const FitRow *Ft = P->fit_tab + mask;
-            const float T_uv = L.T_uv;
-            float rr = 0.0f;
             FitRow F;
-            float R0, R1, R2;
-            if constexpr (PL) {
-                if (pres) {
-                    const float x = L.wx[j * RS + hit];
-                    const float xm = uvj ? x + L.lay[j].z : x;
-                    rr = xm - (a + b * u + c * gu);
-                }
-                F = *Ft;
-                const float t1[3] = {rr, sv * rr, h * rr};
-                float s1[3];
-                row_sums(t1, s1, g, j);
-                R0 = s1[0]; R1 = s1[1]; R2 = s1[2];
-            } else {
-                const uint32_t eb = (uint32_t)__shfl((int)ebase, id & HALF);
-                sv = h = 0.0f;
-                dxy = 1.0f;
-                if (pres) {
-                    const uint32_t gi = eb + (uint32_t)(L.win[j].x + hit);
-                    const float x = ld32(B.hx, gi), z = ld32(B.hz, gi);
-                    u = z - P->z_ref;
-                    float xm = x;
-                    if (uvj) {
-                        dxy = ld32(B.hd, gi);
-                        xm = x + dxy * (L.yin + L.ty * (z - P->z_in));
-                    }
-                    sv = u * INV1024;
-                    h = sv * sv * (1.0f + dR * u);
-                    rr = xm - (a + b * u + c * g_of(u, dR));
-                }
-                const float t1[10] = {sv, h, sv * sv, sv * h, h * h, rr, sv * rr, h * rr,
-                                      pres_uv ? sv : 0.0f, pres_uv ? sv * sv : 0.0f};
-                float s1[10];
-                chain12(t1, s1);
+            if constexpr (PL) F = *Ft;
+            float rr[4], R0, R1, R2;
+            bool pres[4];
 #pragma unroll
-                for (int k = 0; k < 10; ++k) s1[k] = row_lane11(s1[k]);
+            for (int i = 0; i < 4; ++i) {
+                pres[i] = !(absent & (0x80u << (8 * i)));
+                const int hit = (int)((word >> (8 * i)) & 0x7Fu);
+                const bool st_layer = i == 1 || i == 2;
+                float xm = 0.0f;
+                if constexpr (PL) {
+                    // (an absent hit reads within the row and is dropped)
+                    xm = L.wx[(4 * sq + i) * RS + (hit & (NW - 1))];
+                    if (st_layer) xm = xm + cuv[i - 1];
+                } else {
+                    u[i] = sv[i] = h[i] = gu[i] = 0.0f;
+                    if (st_layer) dxy[i - 1] = 1.0f;
+                    if (pres[i]) {
+                        const uint32_t gi = ebase + (uint32_t)(L.win[4 * sq + i].x + hit);
+                        const float x = ld32(B.hx, gi), z = ld32(B.hz, gi);
+                        u[i] = z - P->z_ref;
+                        xm = x;
+                        if (st_layer) {
+                            dxy[i - 1] = ld32(B.hd, gi);
+                            xm = x + dxy[i - 1] * (y_in + ty_in * (z - P->z_in));
+                        }
+                        sv[i] = u[i] * INV1024;
+                        h[i] = sv[i] * sv[i] * (1.0f + dR * u[i]);
+                        gu[i] = g_of(u[i], dR);
+                    }
+                }
+                const float m = xm - (a + b * u[i] + c * gu[i]);
+                rr[i] = pres[i] ? m : 0.0f;
+            }
+            if constexpr (!PL) {
+                const float q0[4] = {sv[0], sv[1], sv[2], sv[3]}, q1[4] = {h[0], h[1], h[2], h[3]};
+                const float q2[4] = {sv[0] * sv[0], sv[1] * sv[1], sv[2] * sv[2], sv[3] * sv[3]};
+                const float q3[4] = {sv[0] * h[0], sv[1] * h[1], sv[2] * h[2], sv[3] * h[3]};
+                const float q4[4] = {h[0] * h[0], h[1] * h[1], h[2] * h[2], h[3] * h[3]};
+                const float q5[2] = {sv[1], sv[2]}, q6[2] = {q2[1], q2[2]};
+                F.S1 = quad_sum(q0);
+                F.S2 = quad_sum(q1);
+                F.S11 = quad_sum(q2);
+                F.S12 = quad_sum(q3);
+                F.S22 = quad_sum(q4);
+                F.YS1 = quad_sum(q5);
+                F.YS11 = quad_sum(q6);
                 F.S0 = (float)__popc(mask);
                 F.YS0 = (float)__popc(mask & 0x666u);   // the stereo layers 1, 2, 5, 6, 9, 10
-                F.S1 = s1[0]; F.S2 = s1[1]; F.S11 = s1[2]; F.S12 = s1[3]; F.S22 = s1[4];
-                R0 = s1[5]; R1 = s1[6]; R2 = s1[7];
-                F.YS1 = s1[8]; F.YS11 = s1[9];
                 F.m00 = F.S11 * F.S22 - F.S12 * F.S12;
                 F.m01 = F.S1 * F.S22 - F.S12 * F.S2;
                 F.m02 = F.S1 * F.S12 - F.S11 * F.S2;
@@ -743,70 +751,71 @@ struct Pair {
                 F.D = F.YS0 * F.YS11 - F.YS1 * F.YS1;
                 F.C = Ft->C;
             }
-            const float S0 = F.S0, S1 = F.S1, S2 = F.S2, S11 = F.S11, S12 = F.S12, S22 = F.S22;
-            const float m00 = F.m00, m01 = F.m01, m02 = F.m02, det = F.det;
-            const bool ok_x = fabsf(det) > 0.0f;
-            const float det_s = ok_x ? det : 1.0f;
-            const float num_x = j == 0 ? R0 * m00 - S1 * (R1 * S22 - S12 * R2) + S2 * (R1 * S12 - S11 * R2)
-                              : j == 1 ? S0 * (R1 * S22 - S12 * R2) - R0 * m01 + S2 * (S1 * R2 - R1 * S2)
-                                       : S0 * (S11 * R2 - R1 * S12) - S1 * (S1 * R2 - R1 * S2) + R0 * m02;
-            const float q_x = num_x / det_s;
-            const float da = row_bcast_lane(q_x, 0), db = row_bcast_lane(q_x, 1), dc = row_bcast_lane(q_x, 2);
-            const float res = pres ? rr - (da + db * sv + dc * h) : 0.0f;
-            const float eta = pres_uv ? -res / dxy : 0.0f;
-            const float t2[3] = {pres ? res * res / (uvj ? T_uv : P->T_x) : 0.0f, eta, pres_uv ? sv * eta : 0.0f};
-            float s2[3];
-            if constexpr (PL) {
-                row_sums(t2, s2, g, j);
-            } else {
-                chain12(t2, s2);
-#pragma unroll
-                for (int k = 0; k < 3; ++k) s2[k] = row_lane11(s2[k]);
+            {
+                const float q1[4] = {sv[0] * rr[0], sv[1] * rr[1], sv[2] * rr[2], sv[3] * rr[3]};
+                const float q2[4] = {h[0] * rr[0], h[1] * rr[1], h[2] * rr[2], h[3] * rr[3]};
+                R0 = quad_sum(rr);
+                R1 = quad_sum(q1);
+                R2 = quad_sum(q2);
             }
-            const float Qx = s2[0], Y0 = s2[1], Y1 = s2[2];
-            const float YS0 = F.YS0, YS1 = F.YS1, YS11 = F.YS11, D = F.D;
-            const bool ok_y = fabsf(D) > 0.0f;
-            const float D_s = ok_y ? D : 1.0f;
-            const float q_y = (j == 0 ? Y0 * YS11 - YS1 * Y1 : YS0 * Y1 - YS1 * Y0) / D_s;   // lanes 0, 1: dy0, dty
-            const float dy0 = row_bcast_lane(q_y, 0), dty = row_bcast_lane(q_y, 1);
-            const float dslope = dty * INV1024;
-            const float ry = pres_uv ? eta - (dy0 + dty * sv) : 0.0f;
-            const float t3[1] = {pres_uv ? ry * ry / P->T_y : 0.0f};
-            float s3[1];
-            chain12(t3, s3);   // Q_y in lane 11
-            // lane 10 divides Q_x, lane 11 Q_y; lane 11 adds the two
-            const float q_q = j == LR - 1 ? Qx / (S0 - 3.0f) : s3[0] / (YS0 - 2.0f);
-            const float Q = (dpp<0x111, true>(q_q) + q_q) * F.C;
-            const bool acc = id >= 0 && ok_x && ok_y && fabsf(dslope) < P->T_ty && Q < P->T_Q;
-            const uint64_t accm = __ballot(acc && j == LR);
-            // in rank order: the first strict minimum of each half wins
+            const bool ok_x = fabsf(F.det) > 0.0f;
+            const float det_s = ok_x ? F.det : 1.0f;
+            // lanes 0, 1 and 2 divide the numerators of da, db and dc
+            const float A = R1 * F.S22 - F.S12 * R2, E = R1 * F.S12 - F.S11 * R2, G = F.S1 * R2 - R1 * F.S2;
+            const float num_x = st == 0 ? R0 * F.m00 - F.S1 * A + F.S2 * E
+                              : st == 1 ? F.S0 * A - R0 * F.m01 + F.S2 * G
+                                        : F.S0 * (F.S11 * R2 - R1 * F.S12) - F.S1 * G + R0 * F.m02;
+            const float q_x = num_x / det_s;
+            const float da = quad<0x00>(q_x), db = quad<0x55>(q_x), dc = quad<0xAA>(q_x);
+            float chi[4], eta[2], eta_s[2];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int src = 16 * k + LR;
-                if (!((accm >> src) & 1ull)) continue;
-                const float qk = bcast_f(Q, src);
-                if (rq[k] < HALF) {
-                    if (best0 >= 0 && !(qk < Q0)) continue;
-                    best0 = rq[k];
-                    Q0 = qk;
-                } else {
-                    if (best1 >= 0 && !(qk < Q1)) continue;
-                    best1 = rq[k] - HALF;
-                    Q1 = qk;
+            for (int i = 0; i < 4; ++i) {
+                const bool st_layer = i == 1 || i == 2;
+                const float res = rr[i] - (da + db * sv[i] + dc * h[i]);
+                const float q = res * res / (st_layer ? T_uv : P->T_x);
+                chi[i] = pres[i] ? q : 0.0f;
+                if (st_layer) {
+                    const float y = -res / dxy[i - 1];
+                    eta[i - 1] = pres[i] ? y : 0.0f;
+                    eta_s[i - 1] = sv[i] * eta[i - 1];
                 }
             }
-            // the rows that hold a half's best so far keep its fit
-            if (j == LR && id >= 0 && ((accm >> lane) & 1ull) && r == (id < HALF ? best0 : best1)) {
-                L.best[0] = a + da;
-                L.best[1] = b + db * INV1024;
-                L.best[2] = c + dc * INV1024SQ;
-                L.best[3] = L.yr + dy0;
-                L.best[4] = L.ty + dslope;
-                L.best[5] = Q;
-                L.best_n = __popc(mask);
+            const float Qx = quad_sum(chi), Y0 = quad_sum(eta), Y1 = quad_sum(eta_s);
+            const bool ok_y = fabsf(F.D) > 0.0f;
+            const float D_s = ok_y ? F.D : 1.0f;
+            const float q_y = (st == 0 ? Y0 * F.YS11 - F.YS1 * Y1 : F.YS0 * Y1 - F.YS1 * Y0) / D_s;   // dy0, dty
+            const float dy0 = quad<0x00>(q_y), dty = quad<0x55>(q_y);
+            const float dslope = dty * INV1024;
+            float chy[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const float ry = eta[i] - (dy0 + dty * sv[i + 1]);
+                const float q = ry * ry / P->T_y;
+                chy[i] = pres[i + 1] ? q : 0.0f;
+            }
+            const float Qy = quad_sum(chy);
+            const float q_q = (st == 0 ? Qx : Qy) / (st == 0 ? F.S0 - 3.0f : F.YS0 - 2.0f);
+            const float Q = (quad<0x00>(q_q) + quad<0x55>(q_q)) * F.C;
+            const bool acc = on && ok_x && ok_y && fabsf(dslope) < P->T_ty && Q < P->T_Q;
+            // the half's least Q; of equal ones the lowest rank (lane)
+            float m = acc ? Q : INFINITY;
+            m = fminf(m, dpp<0x124, false>(m));   // row_ror:4
+            m = fminf(m, dpp<0x128, false>(m));   // row_ror:8
+            m = fminf(m, __shfl_xor(m, 16));
+            const uint64_t bal = __ballot(acc && Q == m);
+            const uint32_t at = lane >= HALF ? (uint32_t)(bal >> HALF) : (uint32_t)bal;
+            if (at != 0u && (best_r < 0 || m < best_Q)) {
+                const int wl = __builtin_ctz(at);
+                best_r = (int)L.fl[f0 + (wl >> 2)];
+                best_Q = m;
+                if (j == wl) {
+                    L.fit[0] = make_float4(a + da, b + db * INV1024, c + dc * INV1024SQ,
+                                           (y_in + ty_in * (P->z_ref - P->z_in)) + dy0);
+                    L.fit[1] = make_float4(ty_in + dslope, Q, __int_as_float(__popc(mask)), 0.0f);
+                }
             }
         }
         wave_sync();
-        return lane < HALF ? best0 : best1;
+        return best_r;
     }
 };
