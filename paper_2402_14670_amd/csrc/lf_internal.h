@@ -15,12 +15,14 @@ constexpr int MAX_TRIPLETS = 32;  // n_triplets upper bound
 // a hit, for hits on the layer planes: the serial sums over the present layers
 // in ascending order of 1, s, h, s^2, s h, h^2 (x fit) and 1, s, s^2 over the
 // stereo layers (y fit), the x fit's cofactors and determinant, the y fit's
-// determinant, and C(n_hits).
+// determinant, C(n_hits), and the binary64 reciprocals (see div_by) of det and D
+// (of 1 where they are 0), n - 3 and n_uv - 2.
 struct alignas(16) FitRow {
     float S0, S1, S2, S11;
     float S12, S22, m00, m01;
     float m02, det, YS0, YS1;
     float YS11, D, C, unused;
+    double r_det, r_D, r_nx, r_ny;
 };
 
 constexpr uint32_t FIT_ROWS = 1u << NL;   // one for each mask
@@ -46,15 +48,18 @@ struct KParams {
     // Triplet seeding in binary16 (VELO-UT input only)
     int32_t seed_fp16;
     // What hits on the layer planes make constant (two tracks per wavefront,
-    // lf_pair.h): u = z - z_ref and g(u) of each layer, and the fits' s = u / 1024
-    // and h = s^2 (1 + dRatio u); per seed set (layers
-    // l0, l1, l2): z_l2 - z_l0, 1 / (z_mag - z_l0) (bracket only), and the
-    // triplet model's u1 - u0, u2 - u1, G01 and G12 - G01; fit_tab[mask]
-    // for each 12-bit mask of layers with a hit.  pair_ok: the planes allow
-    // that path (lever arms and set lengths above 1 mm).
+    // lf_pair.h): u = z - z_ref and g(u) of each layer, and the fits'
+    // h = s^2 (1 + dRatio u), s = u / 1024; per seed set (layers l0, l1, l2) the triplet
+    // model's u0, g0, u1 - u0, u2 - u1, G01, G12 - G01, then z_l0, z_l1,
+    // z_l2 - z_l0, 1 / (z_mag - z_l0) (bracket only), K and z_mag - z_l0;
+    // fit_tab[mask] for each 12-bit mask of layers with a hit.  pair_ok: the
+    // planes allow that path (lever arms and set lengths above 1 mm).
     alignas(16) float lay_u[NL];
-    float lay_g[NL], lay_s[NL], lay_h[NL];
-    float set_dz[2], set_rlev[2], set_du01[2], set_du12[2], set_G01[2], set_dG[2];
+    float lay_g[NL], lay_h[NL];
+    float set_tab[2][12];
+    // binary64 reciprocals (see div_by): per seed set of z_l2 - z_l0,
+    // u1 - u0, u2 - u1 and G12 - G01; of dxdy of each layer, T_x, T_y and kick
+    double r_set[2][4], r_dxdy[NL], r_Tx, r_Ty, r_kick;
     int32_t pair_ok;
     const FitRow *fit_tab;   // [FIT_ROWS] device memory
 };

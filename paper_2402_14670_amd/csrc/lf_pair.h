@@ -18,16 +18,21 @@
 //  - a fit takes four lanes, one per station, instead of sixteen, one per
 //    layer: the 2.6 fits of a track fill one pass, and its serial sums need two
 //    steps between lanes instead of a transpose through LDS or eleven steps;
+//  - likewise a candidate's model and extension: a lane searches its station's
+//    three layers side by side, and 16 candidates of both tracks share a pass;
+//  - a division whose divisor is a constant of the context multiplies by its
+//    binary64 reciprocal (div_by: 13 cycles of issue instead of 38);
 //  - in events whose hits lie on the layer planes (EV_PLANES) every expression
 //    of the layer z alone is a constant of the context (KParams::lay_*, set_*,
 //    fit_tab), and no z or slope is loaded at all;
 //  - in the others (PL = false) stereo hits are staged moved along their fibre
 //    to the track's y, which is the same for every candidate, and the closest
 //    one is found by a search and a short walk.
-// Launches before (one track per wavefront) and now: 200,000 nominal tracks
-// 0.377 -> 0.226 ms (with sixteen lanes per fit 0.244); 160,000 with per-hit z
-// and slopes 0.445 -> 0.250 (0.265); 121,500 in dense events 0.477 -> 0.364
-// (0.391); 4,800 nominal 0.0204 -> 0.0160 (0.0199).
+// Launches with one track per wavefront and now: 200,000 nominal tracks 0.377
+// -> 0.201 ms (0.244 with the one-track body's sixteen lanes per fit and nine
+// lanes per extension, 0.226 with four lanes per fit); 160,000 with per-hit z
+// and slopes 0.445 -> 0.229; 121,500 in dense events 0.477 -> 0.314; 10,000
+// nominal 0.0315 -> 0.0197.
 
 // One track's LDS: the x of its window hits (row l: layer l, NW slots, +inf
 // past the window's end, so that a sorted search needs no length), per layer
@@ -41,7 +46,7 @@ struct alignas(16) HalfLds {
     uint8_t th1[MT];                 // middle hit of each kept triplet
     uint8_t fl[MT];                  // ranks of the candidates to fit
     float4 fit[2];                   // the best candidate: a, b, c, y0; ty, Q, hits
-    float4 lay[NL];                  // u, g(u), dxdy * y_ext (0 on x layers), unused
+    float4 lay[NL];                  // u, g(u), dxdy * y_ext (0 on x layers), h; off the planes y_ext, slack
     union {
         struct {
             uint64_t nk[HALF];       // this pass's accepted keys, ~0 past them
@@ -62,50 +67,72 @@ struct alignas(16) HalfLds {
 template <int NW, int MT>
 struct PairLds {
     HalfLds<NW, MT> h[2];
+    float4 set[2][3];                // KParams::set_tab
+    double2 rset[2][2];              // KParams::r_set
 };
 
-// Entries of a row (non-decreasing, +inf past its end) that satisfy v < x.
-template <int NW, class Pred>
-__device__ __forceinline__ int row_count(const float *row, Pred pred) {
-    int p = 0;
+// Rows are searched by LDS byte address: a probe at a fixed distance is an
+// offset of the load, and a step is one add, one compare and one select.
+typedef __attribute__((address_space(3))) const float lds_float;
+__device__ __forceinline__ uint32_t lds_addr(const float *p) {
+    return (uint32_t)reinterpret_cast<uintptr_t>((lds_float *)p);
+}
+__device__ __forceinline__ float lds_at(uint32_t a) { return *reinterpret_cast<lds_float *>((uintptr_t)a); }
+
+// Address of the first entry of a row (non-decreasing, +inf past its end) that
+// does not satisfy pred, for N rows side by side.
+template <int NW, int N, class Pred>
+__device__ __forceinline__ void row_lower(uint32_t (&p)[N], Pred pred) {
 #pragma unroll
-    for (int s = NW / 2; s > 0; s >>= 1) p = pred(row[p + s - 1]) ? p + s : p;
-    return pred(row[p]) ? p + 1 : p;
+    for (int s = NW / 2; s > 0; s >>= 1) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const bool t = pred(i, lds_at(p[i] + 4u * (uint32_t)(s - 1)));
+            p[i] = t ? p[i] + 4u * (uint32_t)s : p[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const bool t = pred(i, lds_at(p[i]));
+        p[i] = t ? p[i] + 4u : p[i];
+    }
 }
 
-// Closest entry to xe of row[j] + c given p = #{j: row[j] + c < xe}: the first
-// minimum of a linear scan, or -1 (see closest_finish).  p may equal the
-// window's length: the +inf there is never closest.
-__device__ __forceinline__ int row_closest(const float *row, float c, float xe, int p, float &bd) {
-    const int pm = p > 0 ? p - 1 : 0;
-    const float d = fabsf(row[p] + c - xe), dl = fabsf(row[pm] + c - xe);
-    int best = p;
-    bd = d;
-    if (!(d < dl)) {
-        best = pm;
-        bd = dl;
-        while (best > 0 && fabsf(row[best - 1] + c - xe) == dl) --best;
-    }
-    return bd < INFINITY ? best : -1;
+// Closest entry to xe of a row's values + c, given the address p of the first
+// value + c not below xe (one past the row's last slot at most: there +inf is
+// never closest): the address of the first minimum of a linear scan and its
+// distance, or a distance of +inf or NaN (see closest_finish).
+__device__ __forceinline__ uint32_t row_closest(uint32_t row, float c, float xe, uint32_t p, float &bd) {
+    const uint32_t pm = p > row ? p - 4u : row;
+    const float d = fabsf(lds_at(p) + c - xe), dl = fabsf(lds_at(pm) + c - xe);
+    const bool left = !(d < dl);
+    uint32_t best = left ? pm : p;
+    bd = left ? dl : d;
+    // equal distances before the left neighbour
+    if (left)
+        while (best > row && fabsf(lds_at(best - 4u) + c - xe) == dl) best -= 4u;
+    return best;
 }
 
 // The same for a row whose values are out of order by less than W (row[i] <
 // row[k] + W for i < k < n): from p, where a search ended, outwards until no
 // further value can be as close.  The first minimum of a linear scan.
-__device__ __forceinline__ int row_closest_near(const float *row, int n, float xe, float W, int p, float &bd) {
-    int best = -1;
+__device__ __forceinline__ uint32_t row_closest_near(uint32_t row, uint32_t end, float xe, float W, uint32_t p,
+                                                     float &bd) {
+    uint32_t best = row;
     bd = INFINITY;
-    for (int i = p - 1; i >= 0; --i) {
-        const float v = row[i], d = fabsf(v - xe);
+    for (uint32_t i = p; i > row;) {
+        i -= 4u;
+        const float v = lds_at(i), d = fabsf(v - xe);
         if (d <= bd) { bd = d; best = i; }
         if (v + W < xe - bd) break;
     }
-    for (int i = p; i < n; ++i) {
-        const float v = row[i], d = fabsf(v - xe);
+    for (uint32_t i = p; i < end; i += 4u) {
+        const float v = lds_at(i), d = fabsf(v - xe);
         if (d < bd) { bd = d; best = i; }
         if (v - W > xe + bd) break;
     }
-    return bd < INFINITY ? best : -1;
+    return best;
 }
 
 // (PL: the events' hits lie on the layer planes.)
@@ -136,7 +163,7 @@ struct Pair {
         const float qop = B.tqop[tin];
         const int l = j < NL ? j : (j < 2 * NL ? j - NL : 0);   // lanes 0..11 and 12..23: layer
         const float zl = P->z[l], dxl = P->dxdy[l];
-        const float2 ug = make_float2(P->lay_u[l], P->lay_g[l]);
+        const float4 lz = make_float4(P->lay_u[l], P->lay_g[l], 0.0f, P->lay_h[l]);
         const int zone = ty_in >= 0.0f ? 1 : 0;
         ebase = ld32(B.hit_off, ev * 24u);
         const uint32_t b0 = ld32(B.hit_off, ev * 24u + (uint32_t)(2 * l + zone));
@@ -183,6 +210,9 @@ struct Pair {
 
         // ---- search windows: lane l < 12 searches x_min and the centre of
         // layer l side by side, lane 12 + l its x_max ----
+        // the set constants, one run of 40 words in both places
+        static_assert(offsetof(KParams, r_set) == offsetof(KParams, set_tab) + 96, "set_tab and r_set are one run");
+        if (lane < 40) reinterpret_cast<float *>(&S.set[0][0])[lane] = (&P->set_tab[0][0])[lane];
         const bool uvl = is_uv(l);
         const float ye = y_in + ty_in * (zl - P->z_in);
         const float cuv = uvl ? dxl * ye : 0.0f;
@@ -216,16 +246,21 @@ struct Pair {
             }
             if (!live || j >= 2 * NL) na = 0;
             if (!live || j >= NL) nc = 0;
-            while (__ballot((na | nc) != 0)) {
-                const uint32_t ha = na >> 1, hc = nc >> 1;
-                float va = INFINITY, vc = INFINITY;   // a finished search stays
-                if (na) va = ld32(B.hx, la + ha);
-                if (nc) vc = ld32(B.hx, lc + hc);
-                const bool ta = va < ka, tc = vc < xc;
-                la += ta ? ha + 1 : 0;
-                na = ta ? na - ha - 1 : ha;
-                lc += tc ? hc + 1 : 0;
-                nc = tc ? nc - hc - 1 : hc;
+            // Both searches in the same steps s = 2^k .. 1, from the largest any
+            // lane needs: the start advances by s while the entry before it
+            // stays below the key.
+            const uint32_t most = na > nc ? na : nc;
+            uint32_t s = 1;
+            while (__ballot(most >= 2 * s)) s *= 2;
+            const uint32_t ea = la + na, ec = lc + nc;
+            for (; s > 0; s >>= 1) {
+                const float *at = B.hx + (s - 1);
+                const uint32_t ta = la + s, tc = lc + s;
+                float va = INFINITY, vc = INFINITY;
+                if (ta <= ea) va = ld32(at, la);
+                if (tc <= ec) vc = ld32(at, lc);
+                la = va < ka ? ta : la;
+                lc = vc < xc ? tc : lc;
             }
             const int lo = (int)(la - ebase);
             int c = (int)(lc - ebase);
@@ -245,12 +280,12 @@ struct Pair {
             if (j < NL) {
                 L.win[j] = make_int2(first, len);
                 if constexpr (PL) {
-                    L.lay[j] = make_float4(ug.x, ug.y, cuv, 0.0f);
+                    L.lay[j] = make_float4(lz.x, lz.y, cuv, lz.w);
                 } else {
                     // how far the moved hits of a stereo bucket can be out of
                     // order: the spread of its slopes times y, and far more
                     // than the rounding of the moved values
-                    L.lay[j] = make_float4(ug.x, ug.y, ye, dspread * fabsf(ye) * 1.0001f + (1e-3f + 1e-5f * big));
+                    L.lay[j] = make_float4(lz.x, lz.y, ye, dspread * fabsf(ye) * 1.0001f + (1e-3f + 1e-5f * big));
                     if (j == 8) L.zr[0] = make_float2(zlo, zhi);
                     if (j == 11) L.zr[1] = make_float2(zlo, zhi);
                 }
@@ -299,7 +334,7 @@ struct Pair {
         // pairs of all ranges are laid end to end in the queue.
         const float tolc = P->magtol_const + P->magtol_pscale / p;
         const bool low_p = p < P->p_charge_cut;
-        int nL = 0;    // kept triplets of this half
+        int nA = 0, nB = 0;    // kept triplets of the two halves (uniform)
         const int c1 = L.win[0].y, n_items = c1 + L.win[3].y;
         const int items_max = halfmax(n_items);
         for (int base = 0; base < items_max; base += 2 * HALF) {
@@ -309,16 +344,16 @@ struct Pair {
                 const int item = base + j + HALF * k;
                 const bool s = item >= c1;
                 const int i0 = (s ? item - c1 : item) & (NW - 1);
-                const float x0 = L.wx[(s ? 3 * RS : 0) + i0];
-                const float *row2 = &L.wx[s ? 11 * RS : 8 * RS];
-                const int n2 = s ? L.win[11].y : L.win[8].y;
+                const int ro = s ? 3 * RS : 0;   // the set's rows: layers 0, 4, 8 or three further
+                const float x0 = L.wx[ro + i0];
+                const uint32_t row2 = lds_addr(&L.wx[8 * RS + ro]);
+                const float4 sk = S.set[s ? 1 : 0][2];   // dz, 1 / lever arm, K, lever arm
                 float xlo, xhi;
                 bool all;   // no bracket, or one that overflowed: every pair
                 if constexpr (PL) {
-                    const float rl = s ? P->set_rlev[1] : P->set_rlev[0];
-                    const float dz = s ? P->set_dz[1] : P->set_dz[0];
+                    const float dz = sk.x;
                     float w0;
-                    const float tc = slope_bracket(x0, x_mag, rl, tolc, w0);
+                    const float tc = slope_bracket(x0, x_mag, sk.y, tolc, w0);
                     const float e = x0 + tc * dz;
                     w0 = w0 * dz;
                     const float w = w0 + (0.5f + 2e-5f * (fabsf(e) + w0));
@@ -341,9 +376,10 @@ struct Pair {
                     xhi = e2 + margin;
                     all = !(fabsf(lev) > 1.0f && (dzl > 1.0f || dzh < -1.0f) && fabsf(xlo) < 1e30f && fabsf(xhi) < 1e30f);
                 }
-                int lo = row_count<NW>(row2, [xlo](float v) { return v < xlo; });
-                int hi = row_count<NW>(row2, [xhi](float v) { return v <= xhi; });
-                if (all) { lo = 0; hi = n2; }
+                uint32_t ends[2] = {row2, row2};
+                row_lower<NW>(ends, [xlo, xhi](int i, float v) { return i == 0 ? v < xlo : v <= xhi; });
+                int lo = (int)(ends[0] - row2) >> 2, hi = (int)(ends[1] - row2) >> 2;
+                if (all) { lo = 0; hi = L.win[s ? 11 : 8].y; }
                 jlo[k] = lo;
                 cnt[k] = item < n_items && hi > lo ? hi - lo : 0;
                 code[k] = ((s ? 1 : 0) << 12) | (i0 << 6) | lo;
@@ -371,15 +407,15 @@ struct Pair {
                 const int n_here = total - q0 < QP ? total - q0 : QP;
                 const int n_max = total_max - q0 < QP ? total_max - q0 : QP;
                 for (int f = 0; f < n_max; f += HALF)
-                    triplets(lane, f + j < n_here, L.q[(f + j) & (QP - 1)], nL, tolc, low_p, tx_in, qop, x_mag);
+                    triplets(lane, f + j < n_here, L.q[(f + j) & (QP - 1)], nA, nB, tolc, low_p, tx_in, qop, x_mag);
                 wave_sync();
             }
         }
 
         int best_r = -1;    // this half's best candidate
-        if (halfmax(nL) > 0) {
-            candidates(lane, nL, T_uv);
-            best_r = fits(lane, nL, T_uv, y_in, ty_in);
+        if (nA + nB > 0) {
+            candidates(lane, nA, nB, T_uv);
+            best_r = fits(lane, lane >= HALF ? nB : nA, T_uv, y_in, ty_in);
         }
 
         // ---- output ----
@@ -391,20 +427,20 @@ struct Pair {
             const float uT = P->z_T - P->z_ref;
             const float txT = bfb + 2.0f * bfc * uT + 3.0f * bfc * dR * uT * uT;
             const float qo = paper ? (kick_s(txT, bfty) - kick_s(tx_in, ty_in)) / field_F(fc, txT - tx_in)
-                                   : (txT - tx_in) / P->kick;
-            B.found[t] = found ? 1 : 0;
-            B.nhits[t] = found ? (uint8_t)__float_as_int(f1.z) : 0;
-            B.a[t] = found ? bfa : 0.0f;
-            B.b[t] = found ? bfb : 0.0f;
-            B.c[t] = found ? bfc : 0.0f;
-            B.y0[t] = found ? bfy0 : 0.0f;
-            B.ty[t] = found ? bfty : 0.0f;
-            B.qop[t] = found ? qo : 0.0f;
-            B.Q[t] = found ? f1.y : 0.0f;
+                                   : div_by(txT - tx_in, P->r_kick);
+            st32(B.found, t, (uint8_t)(found ? 1 : 0));
+            st32(B.nhits, t, (uint8_t)(found ? __float_as_int(f1.z) : 0));
+            st32(B.a, t, found ? bfa : 0.0f);
+            st32(B.b, t, found ? bfb : 0.0f);
+            st32(B.c, t, found ? bfc : 0.0f);
+            st32(B.y0, t, found ? bfy0 : 0.0f);
+            st32(B.ty, t, found ? bfty : 0.0f);
+            st32(B.qop, t, found ? qo : 0.0f);
+            st32(B.Q, t, found ? f1.y : 0.0f);
         }
         if (j < NL) {
             const int h = found ? (int)L.ch[best_r][j] : -1;
-            B.hit_idx[(size_t)t * NL + j] = h >= 0 ? first + h : -1;
+            st32(B.hit_idx, t * NL + (uint32_t)j, h >= 0 ? first + h : -1);
         }
     }
 
@@ -425,33 +461,37 @@ struct Pair {
     // Up to 32 seed pairs per half (one per lane, in: the lane has one): the
     // doublet filters, the closest middle hit, the triplet cut, and the merge
     // of the accepted triplets into the half's top-n list.
-    __device__ __forceinline__ void triplets(int lane, bool in, uint32_t e, int &nL, float tolc, bool low_p,
+    __device__ __forceinline__ void triplets(int lane, bool in, uint32_t e, int &nA, int &nB, float tolc, bool low_p,
                                              float tx_in, float qop, float x_mag) {
         const int j = lane & (HALF - 1);
         HalfLds<NW, MT> &L = S.h[lane >> 5];
         const int NT = P->n_triplets;
         const bool s = (e >> 12) & 1u;
         const int i0 = (int)((e >> 6) & 63u), i2 = (int)(e & 63u);
-        const float x0 = L.wx[(s ? 3 * RS : 0) + (i0 & (NW - 1))], x2 = L.wx[(s ? 11 * RS : 8 * RS) + (i2 & (NW - 1))];
-        const float z1 = s ? P->z[7] : P->z[4];
-        float z0 = s ? P->z[3] : P->z[0], dz = s ? P->set_dz[1] : P->set_dz[0];
+        const int ro = s ? 3 * RS : 0;
+        const float x0 = L.wx[ro + (i0 & (NW - 1))], x2 = L.wx[8 * RS + ro + (i2 & (NW - 1))];
+        const float4 sa = S.set[s ? 1 : 0][1], sk = S.set[s ? 1 : 0][2];   // .., z0, z1; dz, .., K, lever arm
+        float z0 = sa.z, dz = sk.x, lev = sk.w;
         if constexpr (!PL) {
             z0 = in ? ld32(B.hz, ebase + (uint32_t)(L.win[s ? 3 : 0].x + i0)) : 0.0f;
             dz = (in ? ld32(B.hz, ebase + (uint32_t)(L.win[s ? 11 : 8].x + i2)) : 1.0f) - z0;
+            lev = P->z_mag - z0;
         }
-        const float txd = (x2 - x0) / dz;
+        const float txd = PL ? div_by(x2 - x0, S.rset[s ? 1 : 0][0].x) : (x2 - x0) / dz;
         bool ok = in && !(low_p && !((txd - tx_in) * qop > 0.0f));
-        const float xm = x0 + txd * (P->z_mag - z0);
+        const float xm = x0 + txd * lev;
         float tol = tolc + P->magtol_txscale * fabsf(txd);
         if (tol < P->magtol_min) tol = P->magtol_min;
         if (tol > P->magtol_max) tol = P->magtol_max;
         if (!(fabsf(xm - x_mag) < tol)) ok = false;
-        const float x1e = z1 * txd + (x0 - txd * z0) * (s ? P->K_last : P->K_first);
-        const float *row1 = &L.wx[s ? 7 * RS : 4 * RS];
+        const float x1e = sa.w * txd + (x0 - txd * z0) * sk.z;
+        const uint32_t row1 = lds_addr(&L.wx[4 * RS + ro]);
+        uint32_t p1[1] = {row1};
+        row_lower<NW>(p1, [x1e](int, float v) { return v < x1e; });
         float bd;
-        const int best = row_closest(row1, 0.0f, x1e, row_count<NW>(row1, [x1e](float v) { return v < x1e; }), bd);
+        const uint32_t best = (row_closest(row1, 0.0f, x1e, p1[0], bd) - row1) >> 2;
         const float chi2 = bd * bd;
-        ok = ok && best >= 0 && chi2 < P->T_triplet;
+        ok = ok && bd < INFINITY && chi2 < P->T_triplet;
         const uint64_t key = ((uint64_t)__float_as_uint(chi2) << 32) | e;
         // a full list only admits keys below its last one
         ok = ok && key < L.tk[NT - 1];
@@ -459,9 +499,10 @@ struct Pair {
         if (bal == 0) return;
 
         // merge: an element's place is its rank among the kept and the new keys
-        const uint32_t mine_bal = lane >= HALF ? (uint32_t)(bal >> HALF) : (uint32_t)bal;
-        const int nb = __popc(mine_bal);
-        const int nb_max = halfmax(nb), nL_max = halfmax(nL);
+        const uint32_t bal_a = (uint32_t)bal, bal_b = (uint32_t)(bal >> HALF);
+        const uint32_t mine_bal = lane >= HALF ? bal_b : bal_a;
+        const int nb_a = __popc(bal_a), nb_b = __popc(bal_b), nb_max = nb_a > nb_b ? nb_a : nb_b;
+        const int nL = lane >= HALF ? nB : nA, nL_max = nA > nB ? nA : nB;
         // (the lists are read four keys at a time, past their ends ~0)
         const uint64_t old = L.tk[j & (MT - 1)];
         const int oh1 = L.th1[j & (MT - 1)];
@@ -470,18 +511,23 @@ struct Pair {
         wave_sync();
         if (ok) L.nk[__popc(mine_bal & ((1u << j) - 1u))] = key;
         wave_sync();
-        for (int i = 0; i < nb_max; i += 4) {
+        if (nL_max == 0) {
+            for (int i = 0; i < nb_max; i += 4) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) r_new += L.nk[i + k] < key ? 1 : 0;
-        }
-        if (nL_max > 0) {
+                for (int k = 0; k < 4; ++k) r_new += L.nk[i + k] < key ? 1 : 0;
+            }
+        } else {
             for (int i = 0; i < nL_max; i += 4) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) r_new += L.tk[i + k] < key ? 1 : 0;
             }
             for (int i = 0; i < nb_max; i += 4) {
 #pragma unroll
-                for (int k = 0; k < 4; ++k) r_old += L.nk[i + k] < old ? 1 : 0;
+                for (int k = 0; k < 4; ++k) {
+                    const uint64_t v = L.nk[i + k];
+                    r_new += v < key ? 1 : 0;
+                    r_old += v < old ? 1 : 0;
+                }
             }
         }
         wave_sync();
@@ -493,118 +539,100 @@ struct Pair {
             L.tk[r_old] = old;
             L.th1[r_old] = (uint8_t)oh1;
         }
-        nL = nL + nb < NT ? nL + nb : NT;
+        nA = nA + nb_a < NT ? nA + nb_a : NT;
+        nB = nB + nb_b < NT ? nB + nb_b : NT;
         wave_sync();
     }
 
-    // Triplet x(z) models, one lane per kept triplet, and the extension to
-    // the missing layers, two (candidate, layer) items per lane.
-    __device__ __forceinline__ void candidates(int lane, int nL, float T_uv) {
-        const int j = lane & (HALF - 1);
-        HalfLds<NW, MT> &L = S.h[lane >> 5];
-        if (j < nL) {
-            const uint32_t lo = (uint32_t)L.tk[j];
-            const int s = (int)((lo >> 12) & 1u), i0 = (int)((lo >> 6) & 63u), i2 = (int)(lo & 63u);
-            const int i1 = L.th1[j];
-            const float X0 = L.wx[(s ? 3 * RS : 0) + i0], X1 = L.wx[(s ? 7 * RS : 4 * RS) + i1],
-                        X2 = L.wx[(s ? 11 * RS : 8 * RS) + i2];
-            float u0, g0, du01, du12, G01, dG;
+    // Triplet x(z) models and the extension to the missing layers: four lanes
+    // per candidate, sixteen candidates per pass, the first track's and then
+    // the second's.  Lanes 0..2 of a quad take a station each: its seed hit, and
+    // the searches of its three other layers side by side.  nA, nB: the tracks'
+    // candidates.
+    __device__ __forceinline__ void candidates(int lane, int nA, int nB, float T_uv_) {
+        const int st = lane & 3, sq = st < 3 ? st : 0;
+        for (int k0 = 0; k0 < nA + nB; k0 += WAVE / 4) {
+            const int kk = k0 + (lane >> 2);
+            const bool on = kk < nA + nB, second = kk >= nA;
+            const int k = second ? kk - nA : kk, r = on ? k : 0;
+            HalfLds<NW, MT> &L = S.h[second ? 1 : 0];
+            const uint32_t rows = lds_addr(&L.wx[4 * sq * RS]);
+            const float T_uv = second ? bcast_f(T_uv_, HALF) : bcast_f(T_uv_, 0);
+            uint32_t eb = 0;
+            if constexpr (!PL)
+                eb = (uint32_t)(second ? __builtin_amdgcn_readlane((int)ebase, HALF) : __builtin_amdgcn_readlane((int)ebase, 0));
+            const uint32_t id = (uint32_t)L.tk[r];
+            const bool s = (id >> 12) & 1u;
+            // (masked: a half without candidates reads within its rows)
+            const int i0 = (int)((id >> 6) & 63u) & (NW - 1), i2 = (int)(id & 63u) & (NW - 1), i1 = L.th1[r] & (NW - 1);
+            const int ro = s ? 3 * RS : 0;
+            const float X0 = L.wx[ro + i0], X1 = L.wx[4 * RS + ro + i1], X2 = L.wx[8 * RS + ro + i2];
+            float u0, g0, du01 = 0.0f, du12 = 0.0f, G01, dG = 0.0f;
             if constexpr (PL) {
-                u0 = s ? P->lay_u[3] : P->lay_u[0];
-                g0 = s ? P->lay_g[3] : P->lay_g[0];
-                du01 = s ? P->set_du01[1] : P->set_du01[0];
-                du12 = s ? P->set_du12[1] : P->set_du12[0];
-                G01 = s ? P->set_G01[1] : P->set_G01[0];
-                dG = s ? P->set_dG[1] : P->set_dG[0];
+                const float4 sm = S.set[s ? 1 : 0][0];
+                u0 = sm.x; g0 = sm.y;
+                G01 = S.set[s ? 1 : 0][1].x;
             } else {
                 const float dR = P->dRatio;
-                u0 = ld32(B.hz, ebase + (uint32_t)(L.win[s ? 3 : 0].x + i0)) - P->z_ref;
-                const float u1 = ld32(B.hz, ebase + (uint32_t)(L.win[s ? 7 : 4].x + i1)) - P->z_ref;
-                const float u2 = ld32(B.hz, ebase + (uint32_t)(L.win[s ? 11 : 8].x + i2)) - P->z_ref;
+                u0 = on ? ld32(B.hz, eb + (uint32_t)(L.win[s ? 3 : 0].x + i0)) - P->z_ref : 0.0f;
+                const float u1 = on ? ld32(B.hz, eb + (uint32_t)(L.win[s ? 7 : 4].x + i1)) - P->z_ref : 0.0f;
+                const float u2 = on ? ld32(B.hz, eb + (uint32_t)(L.win[s ? 11 : 8].x + i2)) - P->z_ref : 0.0f;
                 g0 = g_of(u0, dR);
                 const float g1 = g_of(u1, dR), g2 = g_of(u2, dR);
                 du01 = u1 - u0;
                 du12 = u2 - u1;
-                G01 = (g1 - g0) / du01;
-                dG = (g2 - g1) / du12 - G01;
+                const float G = (st == 0 ? g1 - g0 : g2 - g1) / (st == 0 ? du01 : du12);
+                G01 = quad<0x00>(G);
+                dG = quad<0x55>(G) - G01;
             }
-            const float s01 = (X1 - X0) / du01;
-            const float s12 = (X2 - X1) / du12;
-            const float c = (s12 - s01) / dG;
+            // lanes 0 and 1 divide for the two secant slopes
+            float q, s01, s12, c;
+            if constexpr (PL) {
+                const double2 ra = S.rset[s ? 1 : 0][0], rb = S.rset[s ? 1 : 0][1];   // .., u1 - u0; u2 - u1, dG
+                q = div_by(st == 0 ? X1 - X0 : X2 - X1, st == 0 ? ra.y : rb.x);
+                s01 = quad<0x00>(q);
+                s12 = quad<0x55>(q);
+                c = div_by(s12 - s01, rb.y);
+            } else {
+                q = (st == 0 ? X1 - X0 : X2 - X1) / (st == 0 ? du01 : du12);
+                s01 = quad<0x00>(q);
+                s12 = quad<0x55>(q);
+                c = (s12 - s01) / dG;
+            }
             const float b = s01 - c * G01;
             const float a = X0 - b * u0 - c * g0;
-            L.ca[j] = a;
-            L.cb[j] = b;
-            L.cc[j] = c;
-            // a seed hit is the first (set 0) or last (set 1) layer of its station
-            const uint32_t none = s ? 0x00FFFFFFu : 0xFFFFFF00u;
-            const int sh = s ? 24 : 0;
-            L.chw[j][0] = none | ((uint32_t)i0 << sh);
-            L.chw[j][1] = none | ((uint32_t)i1 << sh);
-            L.chw[j][2] = none | ((uint32_t)i2 << sh);
-        }
-        wave_sync();
-
-        const int n_items = nL * NSLOT, n_max = halfmax(n_items);
-        struct Item {
-            int r, l;
-            bool in, uv;
-            float c, xe, W;
-            const float *row;
-            int n;
-        };
-        auto item = [&](int it) {
-            Item e;
-            e.in = it < n_items;
-            const int k = e.in ? it : 0;
-            e.r = k / NSLOT;
-            const int slot = k - NSLOT * (k / NSLOT);
-            const int s = (int)(((uint32_t)L.tk[e.r] >> 12) & 1u);
-            e.uv = slot >= 3;
-            e.l = e.uv ? 4 * ((slot - 3) >> 1) + 1 + ((slot - 3) & 1) : 4 * slot + (s ? 0 : 3);
-            const float4 y = L.lay[e.l];
-            e.xe = L.ca[e.r] + L.cb[e.r] * y.x + L.cc[e.r] * y.y;
-            e.c = PL ? y.z : 0.0f;
-            e.row = &L.wx[e.l * RS];
-            e.W = 0.0f;
-            e.n = 0;
-            if constexpr (!PL) {
-                e.W = e.uv ? y.w + 1e-6f * fabsf(e.xe) : 0.0f;
-                e.n = L.win[e.l].y;
+            if (on && st == 0) {
+                L.ca[k] = a;
+                L.cb[k] = b;
+                L.cc[k] = c;
             }
-            return e;
-        };
-        auto closest = [](const Item &e, int p, float &bd) {
-            if constexpr (PL) return row_closest(e.row, e.c, e.xe, p, bd);
-            else return e.uv ? row_closest_near(e.row, e.n, e.xe, e.W, p, bd) : row_closest(e.row, e.c, e.xe, p, bd);
-        };
-        auto keep = [&](const Item &e, int best, float bd) {
-            if (e.in && best >= 0 && bd * bd < (e.uv ? T_uv : P->T_x)) L.ch[e.r][e.l] = (int8_t)best;
-        };
-        for (int it = j; it - j < n_max; it += 2 * HALF) {
-            const Item a = item(it);
-            if (it - j + HALF < n_max) {
-                const Item b = item(it + HALF);
-                int pa = 0, pb = 0;
+            // the station's x layer without the seed hit, then u and v
+            const float4 y[3] = {L.lay[4 * sq + (s ? 0 : 3)], L.lay[4 * sq + 1], L.lay[4 * sq + 2]};
+            const float xe[3] = {a + b * y[0].x + c * y[0].y, a + b * y[1].x + c * y[1].y, a + b * y[2].x + c * y[2].y};
+            const float cc[3] = {0.0f, PL ? y[1].z : 0.0f, PL ? y[2].z : 0.0f};
+            const uint32_t row[3] = {rows + (s ? 0u : 12u * RS), rows + 4u * RS, rows + 8u * RS};
+            uint32_t p[3] = {row[0], row[1], row[2]}, hit[3];
+            row_lower<NW>(p, [&](int i, float v) { return (i == 0 ? v : v + cc[i]) < xe[i]; });
 #pragma unroll
-                for (int s = NW / 2; s > 0; s >>= 1) {
-                    const float va = a.row[pa + s - 1] + a.c, vb = b.row[pb + s - 1] + b.c;
-                    pa = va < a.xe ? pa + s : pa;
-                    pb = vb < b.xe ? pb + s : pb;
+            for (int i = 0; i < 3; ++i) {
+                float bd;
+                uint32_t at;
+                if (PL || i == 0) {
+                    at = row_closest(row[i], cc[i], xe[i], p[i], bd);
+                } else {
+                    const float W = y[i].w + 1e-6f * fabsf(xe[i]);
+                    // (a lane without a candidate has nothing to walk)
+                    const uint32_t n4 = on ? 4u * (uint32_t)L.win[4 * sq + i].y : 0u;
+                    at = row_closest_near(row[i], row[i] + n4, xe[i], W, on ? p[i] : row[i], bd);
                 }
-                pa = a.row[pa] + a.c < a.xe ? pa + 1 : pa;
-                pb = b.row[pb] + b.c < b.xe ? pb + 1 : pb;
-                float da, db;
-                const int ba = closest(a, pa, da), bb = closest(b, pb, db);
-                keep(a, ba, da);
-                keep(b, bb, db);
-            } else {
-                const float c = a.c, xe = a.xe;
-                float da;
-                const int pa = row_count<NW>(a.row, [c, xe](float v) { return v + c < xe; });
-                const int ba = closest(a, pa, da);
-                keep(a, ba, da);
+                const bool keep = bd < INFINITY && bd * bd < (i == 0 ? P->T_x : T_uv);
+                hit[i] = keep ? (at - row[i]) >> 2 : 0xFFu;
             }
+            // the station's four hit bytes; a seed hit is the first (set 0) or
+            // last (set 1) layer of its station
+            const uint32_t seed = (uint32_t)(st == 0 ? i0 : st == 1 ? i1 : i2);
+            const uint32_t word = (s ? hit[0] | (seed << 24) : seed | (hit[0] << 24)) | (hit[1] << 8) | (hit[2] << 16);
+            if (on && st < 3) L.chw[k][sq] = word;
         }
         wave_sync();
     }
@@ -670,18 +698,10 @@ struct Pair {
         float best_Q = 0.0f;
         const int st = j & 3, sq = st < 3 ? st : 0;   // lane 3 holds no layers
         const float dR = P->dRatio;
-        float u[4], gu[4], sv[4], h[4], cuv[2], dxy[2];
+        double r_dxy[2] = {1.0, 1.0};
         if constexpr (PL) {
-            const float4 u4 = *reinterpret_cast<const float4 *>(&P->lay_u[4 * sq]);
-            const float4 g4 = *reinterpret_cast<const float4 *>(&P->lay_g[4 * sq]);
-            const float4 s4 = *reinterpret_cast<const float4 *>(&P->lay_s[4 * sq]);
-            const float4 h4 = *reinterpret_cast<const float4 *>(&P->lay_h[4 * sq]);
-            u[0] = u4.x; u[1] = u4.y; u[2] = u4.z; u[3] = u4.w;
-            gu[0] = g4.x; gu[1] = g4.y; gu[2] = g4.z; gu[3] = g4.w;
-            sv[0] = s4.x; sv[1] = s4.y; sv[2] = s4.z; sv[3] = s4.w;
-            h[0] = h4.x; h[1] = h4.y; h[2] = h4.z; h[3] = h4.w;
-            cuv[0] = L.lay[4 * sq + 1].z; cuv[1] = L.lay[4 * sq + 2].z;
-            dxy[0] = P->dxdy[4 * sq + 1]; dxy[1] = P->dxdy[4 * sq + 2];
+            r_dxy[0] = P->r_dxdy[4 * sq + 1];
+            r_dxy[1] = P->r_dxdy[4 * sq + 2];
         }
         for (int f0 = 0; f0 < nf_max; f0 += HALF / 4) {
             const int k = f0 + (j >> 2);
@@ -696,37 +716,41 @@ struct Pair {
             mask |= quad<0x4E>(mask);   // lanes 2 3 0 1
             const FitRow *Ft = P->fit_tab + mask;
             FitRow F;
-            if constexpr (PL) F = *Ft;
-            float rr[4], R0, R1, R2;
+            float rr[4], R0, R1, R2, sv[4], h[4], dxy[2];
             bool pres[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 pres[i] = !(absent & (0x80u << (8 * i)));
                 const int hit = (int)((word >> (8 * i)) & 0x7Fu);
                 const bool st_layer = i == 1 || i == 2;
-                float xm = 0.0f;
+                float xm = 0.0f, u, gu;
                 if constexpr (PL) {
+                    const float4 y = L.lay[4 * sq + i];   // u, g, dxdy y, h
                     // (an absent hit reads within the row and is dropped)
                     xm = L.wx[(4 * sq + i) * RS + (hit & (NW - 1))];
-                    if (st_layer) xm = xm + cuv[i - 1];
+                    if (st_layer) xm = xm + y.z;
+                    u = y.x;
+                    gu = y.y;
+                    sv[i] = u * INV1024;
+                    h[i] = y.w;
                 } else {
-                    u[i] = sv[i] = h[i] = gu[i] = 0.0f;
+                    u = sv[i] = h[i] = gu = 0.0f;
                     if (st_layer) dxy[i - 1] = 1.0f;
                     if (pres[i]) {
                         const uint32_t gi = ebase + (uint32_t)(L.win[4 * sq + i].x + hit);
                         const float x = ld32(B.hx, gi), z = ld32(B.hz, gi);
-                        u[i] = z - P->z_ref;
+                        u = z - P->z_ref;
                         xm = x;
                         if (st_layer) {
                             dxy[i - 1] = ld32(B.hd, gi);
                             xm = x + dxy[i - 1] * (y_in + ty_in * (z - P->z_in));
                         }
-                        sv[i] = u[i] * INV1024;
-                        h[i] = sv[i] * sv[i] * (1.0f + dR * u[i]);
-                        gu[i] = g_of(u[i], dR);
+                        sv[i] = u * INV1024;
+                        h[i] = sv[i] * sv[i] * (1.0f + dR * u);
+                        gu = g_of(u, dR);
                     }
                 }
-                const float m = xm - (a + b * u[i] + c * gu[i]);
+                const float m = xm - (a + b * u + c * gu);
                 rr[i] = pres[i] ? m : 0.0f;
             }
             if constexpr (!PL) {
@@ -750,6 +774,8 @@ struct Pair {
                 F.det = F.S0 * F.m00 - F.S1 * F.m01 + F.S2 * F.m02;
                 F.D = F.YS0 * F.YS11 - F.YS1 * F.YS1;
                 F.C = Ft->C;
+                F.r_nx = Ft->r_nx;
+                F.r_ny = Ft->r_ny;
             }
             {
                 const float q1[4] = {sv[0] * rr[0], sv[1] * rr[1], sv[2] * rr[2], sv[3] * rr[3]};
@@ -758,6 +784,7 @@ struct Pair {
                 R1 = quad_sum(q1);
                 R2 = quad_sum(q2);
             }
+            if constexpr (PL) F = *Ft;
             const bool ok_x = fabsf(F.det) > 0.0f;
             const float det_s = ok_x ? F.det : 1.0f;
             // lanes 0, 1 and 2 divide the numerators of da, db and dc
@@ -765,17 +792,17 @@ struct Pair {
             const float num_x = st == 0 ? R0 * F.m00 - F.S1 * A + F.S2 * E
                               : st == 1 ? F.S0 * A - R0 * F.m01 + F.S2 * G
                                         : F.S0 * (F.S11 * R2 - R1 * F.S12) - F.S1 * G + R0 * F.m02;
-            const float q_x = num_x / det_s;
+            const float q_x = PL ? div_by(num_x, F.r_det) : num_x / det_s;
             const float da = quad<0x00>(q_x), db = quad<0x55>(q_x), dc = quad<0xAA>(q_x);
             float chi[4], eta[2], eta_s[2];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const bool st_layer = i == 1 || i == 2;
                 const float res = rr[i] - (da + db * sv[i] + dc * h[i]);
-                const float q = res * res / (st_layer ? T_uv : P->T_x);
+                const float q = PL && !st_layer ? div_by(res * res, P->r_Tx) : res * res / (st_layer ? T_uv : P->T_x);
                 chi[i] = pres[i] ? q : 0.0f;
                 if (st_layer) {
-                    const float y = -res / dxy[i - 1];
+                    const float y = PL ? div_by(-res, r_dxy[i - 1]) : -res / dxy[i - 1];
                     eta[i - 1] = pres[i] ? y : 0.0f;
                     eta_s[i - 1] = sv[i] * eta[i - 1];
                 }
@@ -783,18 +810,19 @@ struct Pair {
             const float Qx = quad_sum(chi), Y0 = quad_sum(eta), Y1 = quad_sum(eta_s);
             const bool ok_y = fabsf(F.D) > 0.0f;
             const float D_s = ok_y ? F.D : 1.0f;
-            const float q_y = (st == 0 ? Y0 * F.YS11 - F.YS1 * Y1 : F.YS0 * Y1 - F.YS1 * Y0) / D_s;   // dy0, dty
+            const float num_y = st == 0 ? Y0 * F.YS11 - F.YS1 * Y1 : F.YS0 * Y1 - F.YS1 * Y0;   // of dy0, dty
+            const float q_y = PL ? div_by(num_y, F.r_D) : num_y / D_s;
             const float dy0 = quad<0x00>(q_y), dty = quad<0x55>(q_y);
             const float dslope = dty * INV1024;
             float chy[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const float ry = eta[i] - (dy0 + dty * sv[i + 1]);
-                const float q = ry * ry / P->T_y;
+                const float q = div_by(ry * ry, P->r_Ty);
                 chy[i] = pres[i + 1] ? q : 0.0f;
             }
             const float Qy = quad_sum(chy);
-            const float q_q = (st == 0 ? Qx : Qy) / (st == 0 ? F.S0 - 3.0f : F.YS0 - 2.0f);
+            const float q_q = div_by(st == 0 ? Qx : Qy, st == 0 ? F.r_nx : F.r_ny);
             const float Q = (quad<0x00>(q_q) + quad<0x55>(q_q)) * F.C;
             const bool acc = on && ok_x && ok_y && fabsf(dslope) < P->T_ty && Q < P->T_Q;
             // the half's least Q; of equal ones the lowest rank (lane)
