@@ -1,8 +1,8 @@
 // lf_kernels.hip -- Looking Forward track following, gfx950 kernels.
 //
 // One wavefront (64 lanes) carries one upstream input track -- or, in large
-// batches of VELO-UT input seeded in binary32, each half of it one of two
-// (lf_pair.h) -- through every step of the method (arXiv 2402.14670,
+// batches seeded in binary32, each half of it one of two tracks or one of a
+// track's two sides (lf_pair.h) -- through every step of the method (arXiv 2402.14670,
 // "Algorithm logic"):
 //
 //   windows    the kick (linear, or the sqrt-normalised pt-kick with the
@@ -1497,37 +1497,42 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NS =
     }
 }
 
-// Result slots t0 and t0 + 1 (if < n): the two-track body.
-template <int NW, int MT>
+// The two-track body for result slots t0 and t0 + 1 (if < n), or (NS = 2) for
+// slot t0.
+template <int NW, int MT, int NS>
 __device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams *__restrict__ P, PairLds<NW, MT> &lds,
                                                int lane, uint32_t t0, uint32_t n) {
-    const uint32_t t = t0 + (uint32_t)(lane >> 5);
+    const uint32_t t = NS == 1 ? t0 + (uint32_t)(lane >> 5) : t0;
     const bool act = t < n;
     const uint32_t slot = act ? t : t0;
     const uint32_t tin = B.trk_map ? B.trk_map[slot] : slot;
     const uint32_t ev = B.trk_ev[tin];
     const uint32_t evf = B.uni[ev];
     if (__ballot(!(evf & EV_PLANES)) == 0) {
-        Pair<NW, MT, true> pr{B, P, lds};
+        Pair<NW, MT, true, NS> pr{B, P, lds};
         pr.run(lane, slot, ev, evf, tin, act);
     } else {
-        Pair<NW, MT, false> pr{B, P, lds};
+        Pair<NW, MT, false, NS> pr{B, P, lds};
         pr.run(lane, slot, ev, evf, tin, act);
     }
 }
+constexpr uint32_t pair_tracks(int NS) { return NS == 1 ? 2 : 1; }   // tracks per wavefront
 
-// Batched mode, two tracks per wavefront.  (7 waves per SIMD, 72 registers and a
-// few spilled: 0.205 ms for 200,000 nominal tracks and 0.317 ms for 121,500 in
-// dense events, against 0.211 and 0.335 with 80 registers at 6 waves.)
-template <int NW, int MT, int WPB>
-__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NW == 32 && MT == 16 ? 7 : 1))) void k_pair(DevBatch B, const KParams *__restrict__ P) {
+// Batched mode, two tracks per wavefront (or one track's two sides).  32-hit
+// windows: 7 waves per SIMD, 72 registers and a few spilled: 0.205 ms for
+// 200,000 nominal tracks and 0.317 ms for 121,500 in dense events, against
+// 0.211 and 0.335 with 80 registers at 6 waves.  64-hit windows: what LDS allows.
+constexpr int pair_waves(int NW, int MT) { return NW == 32 ? (MT == 16 ? 7 : 5) : (MT == 16 ? 5 : 4); }
+template <int NW, int MT, int WPB, int NS>
+__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(pair_waves(NW, MT)))) void k_pair(
+    DevBatch B, const KParams *__restrict__ P) {
     __shared__ PairLds<NW, MT> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const uint32_t per = gridDim.x / NXCD;
     const uint32_t lb = (blockIdx.x % NXCD) * per + blockIdx.x / NXCD;
-    const uint32_t t0 = 2 * (lb * WPB + w), n = B.trk_map ? B.n_map : B.n_tracks;
+    const uint32_t t0 = pair_tracks(NS) * (lb * WPB + w), n = B.trk_map ? B.n_map : B.n_tracks;
     if (t0 >= n) return;
-    pair_of_tracks<NW, MT>(B, P, lds[w], lane_id(), t0, n);
+    pair_of_tracks<NW, MT, NS>(B, P, lds[w], lane_id(), t0, n);
 }
 
 // Persistent: QUEUE_N work queues, QUEUE_SUB per XCD.  XCD x owns a
@@ -1550,7 +1555,7 @@ static_assert(QUEUE_N == NXCD * QUEUE_SUB, "QUEUE_SUB queues per XCD");
 
 // MT != 0: two tracks at a time (lists of MT triplets), else one.
 template <int NW, int NS, int WPB, bool H16 = false, int MT = 0>
-__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NW == 32 && MT == 16 ? 5 : 1))) void k_persistent(DevBatch B, const KParams *__restrict__ P,
+__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT == 0 ? 1 : NW == 32 && MT == 16 ? 5 : 4))) void k_persistent(DevBatch B, const KParams *__restrict__ P,
                                                             uint32_t items) {
     __shared__ std::conditional_t<MT != 0, PairLds<NW, MT != 0 ? MT : 16>, WaveLds<NW, NS>> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
@@ -1592,12 +1597,12 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NW =
         const uint32_t x = qi / QUEUE_SUB, lo = xlo(x), hi = xlo(x + 1);
         const uint32_t t0 = lo + (k * QUEUE_SUB + qi % QUEUE_SUB) * items;
         const uint32_t t1 = t0 + items < hi ? t0 + items : hi;
-        for (uint32_t t = t0; t < t1; t += MT != 0 ? 2 : 1) {
+        for (uint32_t t = t0; t < t1; t += MT != 0 ? pair_tracks(NS) : 1) {
             // keep per-track loads inside the loop: hoisting them across tracks
             // costs ~30 VGPRs of loop-carried state and two waves per SIMD
             asm volatile("" ::: "memory");
             if constexpr (MT != 0) {
-                pair_of_tracks<NW, MT>(B, opaque_params(P), lds[w], opaque_lane_id(), t, t1);
+                pair_of_tracks<NW, MT, NS>(B, opaque_params(P), lds[w], opaque_lane_id(), t, t1);
             } else {
                 Track<NW, NS, false, H16> tr{B, P, lds[w], 0, {}, 0};
                 tr.ln = opaque_lane_id();
@@ -1855,7 +1860,7 @@ hipError_t launch_nw_wpb(const DevBatch &b, const KParams *P, int mode, const Ex
         const uint32_t need = (b.n_tracks + WPB - 1) / WPB;
         if (grid > need) grid = need;
         if (grid == 0) grid = 1;
-        if constexpr (NS == 1 && !H16) {
+        if constexpr (!H16) {
             if (pair) {
                 const uint32_t items = (uint32_t)cfg.items_per_grab;
                 if (cfg.n_triplets <= 16)
@@ -1868,12 +1873,12 @@ hipError_t launch_nw_wpb(const DevBatch &b, const KParams *P, int mode, const Ex
         hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16>), dim3(grid), block, 0, s, b, P,
                            (uint32_t)cfg.items_per_grab);
     } else {   // batched: one launch, one wavefront per track (or per mapped slot), XCD-ordered
-        if constexpr (NS == 1 && !H16) {
+        if constexpr (!H16) {
             if (pair) {
-                const uint32_t pairs = ((n + 1) / 2 + WPB - 1) / WPB;
-                const dim3 g((pairs + NXCD - 1) / NXCD * NXCD);
-                if (cfg.n_triplets <= 16) hipLaunchKernelGGL((k_pair<NW, 16, WPB>), g, block, 0, s, b, P);
-                else hipLaunchKernelGGL((k_pair<NW, MAX_TRIPLETS, WPB>), g, block, 0, s, b, P);
+                const uint32_t waves = (n + pair_tracks(NS) - 1) / pair_tracks(NS);
+                const dim3 g(((waves + WPB - 1) / WPB + NXCD - 1) / NXCD * NXCD);
+                if (cfg.n_triplets <= 16) hipLaunchKernelGGL((k_pair<NW, 16, WPB, NS>), g, block, 0, s, b, P);
+                else hipLaunchKernelGGL((k_pair<NW, MAX_TRIPLETS, WPB, NS>), g, block, 0, s, b, P);
                 return hipGetLastError();
             }
         }
@@ -2098,7 +2103,12 @@ int occ_wpb(int waves_per_block) {
 
 int persistent_blocks_per_cu(int n_hits_window, int n_sides, const ExecCfg &cfg) {
     const int w = cfg.waves_per_block;
-    if (n_sides == 2) return n_hits_window <= 32 ? occ_wpb<32, 2>(w) : occ_wpb<64, 2>(w);
+    if (n_sides == 2) {
+        if (!cfg.pair_min) return n_hits_window <= 32 ? occ_wpb<32, 2>(w) : occ_wpb<64, 2>(w);
+        if (cfg.n_triplets <= 16)
+            return n_hits_window <= 32 ? occ_wpb<32, 2, false, 16>(w) : occ_wpb<64, 2, false, 16>(w);
+        return n_hits_window <= 32 ? occ_wpb<32, 2, false, MAX_TRIPLETS>(w) : occ_wpb<64, 2, false, MAX_TRIPLETS>(w);
+    }
     if (n_sides == 3) return n_hits_window <= 32 ? occ_wpb<32, 1, true>(w) : occ_wpb<64, 1, true>(w);
     if (!cfg.pair_min) return n_hits_window <= 32 ? occ_wpb<32, 1>(w) : occ_wpb<64, 1>(w);
     if (cfg.n_triplets <= 16)

@@ -2,8 +2,9 @@
 // Included by lf_kernels.hip (namespace lfk, anonymous).
 //
 // Lanes 0..31 carry one track, lanes 32..63 the next one, through the steps
-// described in lf_kernels.hip, for VELO-UT input seeded in binary32.  The
-// arithmetic of every result is the one of Track, in the same order.
+// described in lf_kernels.hip, for VELO-UT input seeded in binary32 (VELO-only
+// input: each half one side of the same track).  The arithmetic of every result
+// is the one of Track, in the same order.
 //
 // The path is bound by vector instruction issue: a plain add, multiply or move
 // of registers issues every 2.2 cycles per SIMD, every other vector
@@ -31,8 +32,8 @@
 // Launches with one track per wavefront and now: 200,000 nominal tracks 0.377
 // -> 0.201 ms (0.244 with the one-track body's sixteen lanes per fit and nine
 // lanes per extension, 0.226 with four lanes per fit); 160,000 with per-hit z
-// and slopes 0.445 -> 0.229; 121,500 in dense events 0.477 -> 0.314; 10,000
-// nominal 0.0315 -> 0.0197.
+// and slopes 0.445 -> 0.229; 121,500 in dense events 0.477 -> 0.314; 100,000
+// VELO-only 0.444 -> 0.307.
 
 // One track's LDS: the x of its window hits (row l: layer l, NW slots, +inf
 // past the window's end, so that a sorted search needs no length), per layer
@@ -50,7 +51,7 @@ struct alignas(16) HalfLds {
     union {
         struct {
             uint64_t nk[HALF];       // this pass's accepted keys, ~0 past them
-            uint16_t q[QP];          // seed pairs: set << 12 | i0 << 6 | i2
+            uint16_t q[QP];          // seed pairs: side << 13 | set << 12 | i0 << 6 | i2
         };
         struct {
             float ca[MT], cb[MT], cc[MT];    // triplet x(z) models
@@ -135,8 +136,11 @@ __device__ __forceinline__ uint32_t row_closest_near(uint32_t row, uint32_t end,
     return best;
 }
 
-// (PL: the events' hits lie on the layer planes.)
-template <int NW, int MT, bool PL>
+// PL: the events' hits lie on the layer planes.  NS = 2 (VELO-only input, two
+// windows per layer): one track per wavefront, a half for each side's windows,
+// seeds and candidates; the halves meet where the top-n pool of both sides is
+// cut and where the best candidate is chosen.
+template <int NW, int MT, bool PL, int NS>
 struct Pair {
     const DevBatch &B;
     const KParams *__restrict__ P;
@@ -146,14 +150,13 @@ struct Pair {
     static constexpr int RS = HalfLds<NW, MT>::RS;
     static constexpr int QP = HalfLds<NW, MT>::QP;
 
-    // Lane k of each half's value, in every lane of the half.
     __device__ __forceinline__ static int halfmax(int v) {   // v uniform in each half
         const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, HALF);
         return a > b ? a : b;
     }
 
     // Track tin of the batch (input state) in event ev, result slot t; all
-    // uniform in each half; act: the half has a track.
+    // uniform in each half (NS = 2: in the wave); act: the half has a track.
     __device__ __forceinline__ void run(int lane, uint32_t t, uint32_t ev, uint32_t evf, uint32_t tin, bool act) {
         const int j = lane & (HALF - 1);
         HalfLds<NW, MT> &L = S.h[lane >> 5];
@@ -181,32 +184,52 @@ struct Pair {
             big = bi->xabs + bi->dabs * fabsf(y_in + ty_in * (zl - P->z_in));
         }
         const float dR = P->dRatio;
-        const float p = 1.0f / fabsf(qop);
-        const int q = qop > 0.0f ? 1 : -1;
+        float p;
+        int q = 0;
+        if constexpr (NS == 2) {   // the assumed minimum momentum (Track::run)
+            const float t2 = tx_in * tx_in + ty_in * ty_in;
+            const float sin_t = sqrtf(t2 / (1.0f + t2));
+            const float p_pt = sin_t > 0.0f ? P->noUT_pt_min / sin_t : 0.0f;
+            p = p_pt > P->noUT_p_min ? p_pt : P->noUT_p_min;
+        } else {
+            p = 1.0f / fabsf(qop);
+            q = qop > 0.0f ? 1 : -1;
+        }
         const float x_mag = x_in + tx_in * (P->z_mag - P->z_in);
         const bool paper = P->field_form == 1;
         float fc[5] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-        float dtx;
+        float dtx = 0.0f;
         bool live = act;
         if (paper) {
             const float cl = field_c_lane(P, tx_in, ty_in, j);
 #pragma unroll
             for (int i = 0; i < 5; ++i) fc[i] = __shfl(cl, (lane & HALF) + i);
-            const float si = kick_s(tx_in, ty_in);
-            float d = 0.0f;
+            if constexpr (NS == 1) {
+                const float si = kick_s(tx_in, ty_in);
+                float d = 0.0f;
 #pragma unroll
-            for (int it = 0; it < 3; ++it) {
-                const float sf = si + qop * field_F(fc, d);
-                if (!(sf * sf < 1.0f)) live = false;
-                d = sf * sqrtf((1.0f + ty_in * ty_in) / (1.0f - sf * sf)) - tx_in;
+                for (int it = 0; it < 3; ++it) {
+                    const float sf = si + qop * field_F(fc, d);
+                    if (!(sf * sf < 1.0f)) live = false;
+                    d = sf * sqrtf((1.0f + ty_in * ty_in) / (1.0f - sf * sf)) - tx_in;
+                }
+                dtx = d;
             }
-            dtx = d;
         } else {
             dtx = P->kick * qop;
         }
         const float T = tx_in + dtx;
         const float kd = P->kappa * dtx;
-        const float xtol = P->xtol_const + P->xtol_pscale / p;
+        float xtol;
+        if constexpr (NS == 2) {
+            const float ip = 1.0f / p;
+            const float ty2 = ty_in * ty_in;
+            const float *c8 = P->noUT_c;
+            xtol = ip * (c8[0] + tx_in * (c8[1] + c8[2] * tx_in) + ty2 * (c8[3] + tx_in * (c8[4] + c8[5] * tx_in)) +
+                         ip * (c8[6] * tx_in + c8[7] * ip));
+        } else {
+            xtol = P->xtol_const + P->xtol_pscale / p;
+        }
 
         // ---- search windows: lane l < 12 searches x_min and the centre of
         // layer l side by side, lane 12 + l its x_max ----
@@ -218,20 +241,30 @@ struct Pair {
         const float cuv = uvl ? dxl * ye : 0.0f;
         int first, len;
         {
-            const float dz = zl - P->z_mag;
-            const float dzT = zl - P->z_T;
-            const float xe = x_mag + T * dz + kd * dzT * dzT * (1.0f + dR * dzT);
             float xc, xmin, xmax;
-            if (uvl) {
-                xc = xe - cuv;
-                xmin = xc - P->uv_halfwidth;
-                xmax = xc + P->uv_halfwidth;
+            if constexpr (NS == 2) {
+                // straight line; two windows per layer sharing an overlap
+                const float xe = x_in + tx_in * (zl - P->z_in);
+                const float x0 = uvl ? xe - cuv : xe;
+                const float tol = uvl ? P->uv_halfwidth : xtol;
+                xmin = x0 - (lane < HALF ? tol : P->noUT_overlap);
+                xmax = x0 + (lane < HALF ? P->noUT_overlap : tol);
+                xc = 0.5f * (xmin + xmax);
             } else {
-                float asymL = 0.0f, asymR = 0.0f;
-                if (q * P->polarity > 0) asymR = P->xasym; else asymL = P->xasym;
-                xc = xe;
-                xmin = xc - xtol - asymL;
-                xmax = xc + xtol + asymR;
+                const float dz = zl - P->z_mag;
+                const float dzT = zl - P->z_T;
+                const float xe = x_mag + T * dz + kd * dzT * dzT * (1.0f + dR * dzT);
+                if (uvl) {
+                    xc = xe - cuv;
+                    xmin = xc - P->uv_halfwidth;
+                    xmax = xc + P->uv_halfwidth;
+                } else {
+                    float asymL = 0.0f, asymR = 0.0f;
+                    if (q * P->polarity > 0) asymR = P->xasym; else asymL = P->xasym;
+                    xc = xe;
+                    xmin = xc - xtol - asymL;
+                    xmax = xc + xtol + asymR;
+                }
             }
             const float ka = j < NL ? xmin : next_up(xmax);
             uint32_t la = b0, lc = b0, na = b1 - b0, nc = na;
@@ -333,12 +366,12 @@ struct Pair {
         // arm and the distance of the planes are the geometry's), and the
         // pairs of all ranges are laid end to end in the queue.
         const float tolc = P->magtol_const + P->magtol_pscale / p;
-        const bool low_p = p < P->p_charge_cut;
+        const bool low_p = NS == 1 && p < P->p_charge_cut;
         int nA = 0, nB = 0;    // kept triplets of the two halves (uniform)
         const int c1 = L.win[0].y, n_items = c1 + L.win[3].y;
         const int items_max = halfmax(n_items);
         for (int base = 0; base < items_max; base += 2 * HALF) {
-            int jlo[2], cnt[2], code[2];
+            int cnt[2], code[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) {
                 const int item = base + j + HALF * k;
@@ -380,9 +413,8 @@ struct Pair {
                 row_lower<NW>(ends, [xlo, xhi](int i, float v) { return i == 0 ? v < xlo : v <= xhi; });
                 int lo = (int)(ends[0] - row2) >> 2, hi = (int)(ends[1] - row2) >> 2;
                 if (all) { lo = 0; hi = L.win[s ? 11 : 8].y; }
-                jlo[k] = lo;
                 cnt[k] = item < n_items && hi > lo ? hi - lo : 0;
-                code[k] = ((s ? 1 : 0) << 12) | (i0 << 6) | lo;
+                code[k] = (NS == 2 ? (lane >> 5) << 13 : 0) | ((s ? 1 : 0) << 12) | (i0 << 6) | lo;
             }
             // offsets: an inclusive scan over the half of both counts at once
             int sc = cnt[0] | (cnt[1] << 16);
@@ -412,14 +444,41 @@ struct Pair {
             }
         }
 
+        if constexpr (NS == 2) {
+            // one pool of n_triplets for both sides: each list is cut where its
+            // entries' ranks among both reach it
+            const uint64_t mine = L.tk[j & (MT - 1)];
+            const HalfLds<NW, MT> &O = S.h[lane < HALF ? 1 : 0];
+            const int n_max = nA > nB ? nA : nB;
+            int r = j;
+            for (int i = 0; i < n_max; i += 4) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) r += O.tk[i + k] < mine ? 1 : 0;
+            }
+            const uint64_t keep = __ballot(j < (lane >= HALF ? nB : nA) && r < P->n_triplets);
+            nA = __popc((uint32_t)keep);
+            nB = __popc((uint32_t)(keep >> HALF));
+        }
+
         int best_r = -1;    // this half's best candidate
+        float best_Q = 0.0f;
         if (nA + nB > 0) {
             candidates(lane, nA, nB, T_uv);
-            best_r = fits(lane, lane >= HALF ? nB : nA, T_uv, y_in, ty_in);
+            best_r = fits(lane, lane >= HALF ? nB : nA, T_uv, y_in, ty_in, best_Q);
+        }
+        bool mine = act;    // this half writes the slot
+        if constexpr (NS == 2) {
+            // the lower Q of the two sides, of equal ones the lower key
+            const int other_r = __shfl_xor(best_r, HALF);
+            const float other_Q = __shfl_xor(best_Q, HALF);
+            const uint64_t key = best_r >= 0 ? L.tk[best_r] : ~0ull;
+            const uint64_t other = __shfl_xor((unsigned long long)key, HALF);
+            if (other_r < 0) mine = best_r >= 0 || lane < HALF;
+            else mine = best_r >= 0 && (best_Q < other_Q || (best_Q == other_Q && key < other));
         }
 
         // ---- output ----
-        if (!act) return;
+        if (!mine) return;
         const bool found = best_r >= 0;
         if (j == 0) {
             const float4 f0 = L.fit[0], f1 = L.fit[1];
@@ -670,8 +729,9 @@ struct Pair {
     // between lanes, and the x and stereo formulas need no selection.  The
     // sums of the layer terms alone depend only on which layers have a hit:
     // FitRow of that 12-bit mask, tabulated per context (hits on the planes).
-    // Returns the half's best candidate (its fit is in fit[]), or -1.
-    __device__ __forceinline__ int fits(int lane, int nL, float T_uv, float y_in, float ty_in) {
+    // Returns the half's best candidate (its fit is in fit[], its
+    // quality in best_Q), or -1.
+    __device__ __forceinline__ int fits(int lane, int nL, float T_uv, float y_in, float ty_in, float &best_Q) {
         const int j = lane & (HALF - 1);
         HalfLds<NW, MT> &L = S.h[lane >> 5];
         uint32_t mine;   // the half's candidates to fit
@@ -695,7 +755,6 @@ struct Pair {
         const int nf = __popc(mine), nf_max = halfmax(nf);
         wave_sync();
         int best_r = -1;
-        float best_Q = 0.0f;
         const int st = j & 3, sq = st < 3 ? st : 0;   // lane 3 holds no layers
         const float dR = P->dRatio;
         double r_dxy[2] = {1.0, 1.0};

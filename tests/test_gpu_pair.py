@@ -170,6 +170,33 @@ def test_equal_hits_and_ties():
     _check(_jitter(dup, 0.0, 0.1, 66), "doubled hits, slopes", {"n_hits_window": 64})
 
 
+@pytest.mark.parametrize("window,triplets", [(64, 20), (32, 12), (8, 32), (50, 3)])
+def test_velo_only_input(window, triplets):
+    """One track per wavefront, a half for each side: list and window lengths,
+    the pool cut across the sides, per-hit z and slopes, shifted planes, the
+    paper-form field, and filters so loose that the pair queues overflow."""
+    ev = lfgen.generate("nominal", n_events=21, seed=74)
+    params = {"velo_only": 1, "n_hits_window": window, "n_triplets": triplets}
+    _check(ev, f"no-UT w{window} t{triplets}", params)
+    _check(_jitter(ev, 1.5, 0.02, 75), f"no-UT w{window} t{triplets} per-hit z and slope", params)
+    shifted = lfgen.Events(**{**ev.__dict__, "hit_z": ev.hit_z + np.float32(1.5)})
+    _check(shifted, "no-UT shifted planes", params, modes=("batched",))
+    _check(ev, "no-UT loose filters", {**params, "magtol_min": 3000.0, "magtol_max": 3000.0, "T_triplet": 50.0},
+           modes=("batched",))
+    paper = lfgen.generate("nominal", field="paper", n_events=21, seed=76)
+    _check(paper, "no-UT paper field", params, lfgen.world("paper"), modes=("batched",))
+
+
+def test_velo_only_dense_and_tied():
+    ev = lfgen.generate("stress", n_events=9, seed=77)
+    _check(ev, "no-UT stress", {"velo_only": 1})
+    rep = np.random.default_rng(78).integers(1, 4, ev.n_hits)
+    cum = np.concatenate([[0], np.cumsum(rep)])
+    dup = lfgen.Events(**{**ev.__dict__, "hit_off": cum[ev.hit_off.astype(np.int64)].astype(np.uint32),
+                          **{k: np.repeat(getattr(ev, k), rep) for k in ("hit_x", "hit_z", "hit_dxdy", "hit_pid")}})
+    _check(dup, "no-UT doubled hits", {"velo_only": 1}, modes=("batched",))
+
+
 def test_noalloc_and_budget_contexts():
     """The caller's device buffers, and a context with a device budget (its
     batches carry no search index), against the plain upload path."""
