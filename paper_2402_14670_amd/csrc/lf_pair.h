@@ -14,7 +14,7 @@
 // triplets, 2.6 fits), so with 32 lanes per track each of those instructions
 // serves two tracks.  What else differs from the one-track body:
 //  - windows are padded with +inf, so a sorted search needs no length;
-//  - the pairs of all brackets are laid end to end in a queue (92% of them
+//  - the pairs of all brackets are laid end to end over the lanes (92% of them
 //    pass the filters), and filter, middle hit and cut run once per pair;
 //  - a fit takes four lanes, one per station, instead of sixteen, one per
 //    layer: the 2.6 fits of a track fill one pass, and its serial sums need two
@@ -30,10 +30,11 @@
 //    to the track's y, which is the same for every candidate, and the closest
 //    one is found by a search and a short walk.
 // Launches with one track per wavefront and now: 200,000 nominal tracks 0.377
-// -> 0.201 ms (0.244 with the one-track body's sixteen lanes per fit and nine
+// -> 0.199 ms (0.244 with the one-track body's sixteen lanes per fit and nine
 // lanes per extension, 0.226 with four lanes per fit); 160,000 with per-hit z
-// and slopes 0.445 -> 0.229; 121,500 in dense events 0.477 -> 0.314; 100,000
-// VELO-only 0.444 -> 0.307.
+// and slopes 0.445 -> 0.226; 121,500 in dense events 0.477 -> 0.274 (0.314 with
+// the pairs written into a queue item by item); 100,000 VELO-only 0.444 ->
+// 0.303; 4,800 nominal 0.0204 -> 0.0155.
 
 // One track's LDS: the x of its window hits (row l: layer l, NW slots, +inf
 // past the window's end, so that a sorted search needs no length), per layer
@@ -41,7 +42,6 @@
 template <int NW, int MT>
 struct alignas(16) HalfLds {
     static constexpr int RS = NW + 1;
-    static constexpr int QP = 64;    // queued seed pairs
     uint64_t tk[MT];                 // top-n keys, sorted; ~0 past the list
     int2 win[NL];                    // first hit (event-local) and length of each window
     uint8_t th1[MT];                 // middle hit of each kept triplet
@@ -51,7 +51,7 @@ struct alignas(16) HalfLds {
     union {
         struct {
             uint64_t nk[HALF];       // this pass's accepted keys, ~0 past them
-            uint16_t q[QP];          // seed pairs: side << 13 | set << 12 | i0 << 6 | i2
+            uint32_t mark[HALF];     // where the items' pairs begin in a pass
         };
         struct {
             float ca[MT], cb[MT], cc[MT];    // triplet x(z) models
@@ -148,8 +148,8 @@ struct Pair {
     uint32_t ebase = 0;   // the event's first hit
 
     static constexpr int RS = HalfLds<NW, MT>::RS;
-    static constexpr int QP = HalfLds<NW, MT>::QP;
 
+    __device__ __forceinline__ static uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
     __device__ __forceinline__ static int halfmax(int v) {   // v uniform in each half
         const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, HALF);
         return a > b ? a : b;
@@ -364,7 +364,8 @@ struct Pair {
         // per lane; each gets the range of third-layer hits that can pass the
         // magnet filter (the bracket explained in Track::run; here the lever
         // arm and the distance of the planes are the geometry's), and the
-        // pairs of all ranges are laid end to end in the queue.
+        // pairs of all ranges are laid end to end: side << 13 | set << 12 |
+        // i0 << 6 | i2.
         const float tolc = P->magtol_const + P->magtol_pscale / p;
         const bool low_p = NS == 1 && p < P->p_charge_cut;
         int nA = 0, nB = 0;    // kept triplets of the two halves (uniform)
@@ -428,19 +429,28 @@ struct Pair {
             const int off0 = (sc - own) & 0xffff, off1 = ((sc - own) >> 16) + (tot2 & 0xffff);
             const int total = (tot2 & 0xffff) + (tot2 >> 16);
             const int total_max = halfmax(total);
-            for (int q0 = 0; q0 < total_max; q0 += QP) {
-                // queue entries q0 .. q0 + QP of the end-to-end pairs
-                for (int k = 0; __ballot(k < cnt[0] || k < cnt[1]); ++k) {
-                    const int a0 = off0 + k - q0, a1 = off1 + k - q0;
-                    if (k < cnt[0] && (unsigned)a0 < (unsigned)QP) L.q[a0] = (uint16_t)(code[0] + k);
-                    if (k < cnt[1] && (unsigned)a1 < (unsigned)QP) L.q[a1] = (uint16_t)(code[1] + k);
-                }
+            // 32 pairs per pass: each item marks where its pairs begin among
+            // them (or that they went on from before), and the last mark at or
+            // before a lane is its item
+            const uint32_t w0 = (uint32_t)code[0] | ((uint32_t)off0 << 16), w1 = (uint32_t)code[1] | ((uint32_t)off1 << 16);
+            for (int f = 0; f < total_max; f += HALF) {
+                L.mark[j] = 0;
                 wave_sync();
-                const int n_here = total - q0 < QP ? total - q0 : QP;
-                const int n_max = total_max - q0 < QP ? total_max - q0 : QP;
-                for (int f = 0; f < n_max; f += HALF)
-                    triplets(lane, f + j < n_here, L.q[(f + j) & (QP - 1)], nA, nB, tolc, low_p, tx_in, qop, x_mag);
+                const int a0 = off0 - f, a1 = off1 - f;
+                if (cnt[0] > 0 && a0 < HALF && a0 + cnt[0] > 0) L.mark[a0 > 0 ? a0 : 0] = (uint32_t)j;
+                if (cnt[1] > 0 && a1 < HALF && a1 + cnt[1] > 0) L.mark[a1 > 0 ? a1 : 0] = (uint32_t)(HALF + j);
                 wave_sync();
+                uint32_t m = L.mark[j];
+                m = umax(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x111, 0xF, 0xF, true));
+                m = umax(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x112, 0xF, 0xF, true));
+                m = umax(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x114, 0xF, 0xF, true));
+                m = umax(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x118, 0xF, 0xF, true));
+                m = umax(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x142, 0xA, 0xF, false));
+                const int src = (lane & HALF) | (int)(m & (HALF - 1));
+                const uint32_t v0 = (uint32_t)__shfl((int)w0, src), v1 = (uint32_t)__shfl((int)w1, src);
+                const uint32_t w = m >= HALF ? v1 : v0;
+                triplets(lane, f + j < total, (w & 0xffffu) + (uint32_t)(f + j) - (w >> 16), nA, nB, tolc, low_p, tx_in,
+                         qop, x_mag);
             }
         }
 
