@@ -35,12 +35,6 @@ struct Batch {
     size_t out_off = 0, out_bytes = 0;   // the result arrays: one run of the allocation
 };
 
-// Least number of result slots for two tracks per wavefront.  Smaller batches
-// leave most of the chip idle, and one track per wavefront takes less time
-// from its first load to its result (200 tracks: 14.6 us against 16.5, 3,200:
-// 17.0 against 18.4; 4,800: 20.3 against 19.9, 10,000: 31.4 against 24.3).
-constexpr uint32_t PAIR_MIN = 4096;
-
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Host threads for validation and staging copies (the host share of one GPU).
@@ -164,7 +158,7 @@ struct lf_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     void *fixed = nullptr;             // this device's fixed scratch (lf_find_tracks_noalloc)
-    lfk::ExecCfg exec{2, 4, 0, 0, 0, 0};
+    lfk::ExecCfg exec{2, 4, 0, 0, false, 0};
     std::map<uint64_t, Batch> batches;
     uint64_t next_id = 1;
     std::string err;
@@ -532,7 +526,7 @@ int lf_create(const lf_geometry *geom, const lf_params *params, size_t device_bu
         lfk::FitRow *tab = reinterpret_cast<lfk::FitRow *>(reinterpret_cast<char *>(c->d_params) + tab_off);
         k.fit_tab = tab;
         c->exec.n_triplets = k.n_triplets;
-        c->exec.pair_min = k.pair_ok ? PAIR_MIN : 0u;
+        c->exec.pair_ok = k.pair_ok != 0;
         e = hipMemcpy(c->d_params, &k, sizeof(k), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = lfk::launch_fit_table(c->d_params, tab, c->stream);
         if (e == hipSuccess) e = hipStreamSynchronize(c->stream);

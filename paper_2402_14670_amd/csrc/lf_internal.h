@@ -120,9 +120,9 @@ struct ExecCfg {
     int items_per_grab;
     int blocks_per_cu;
     int n_cu;
-    // batched and persistent mode: least number of result slots for two
-    // tracks per wavefront (0: never, the geometry's planes do not allow it)
-    uint32_t pair_min;
+    // batched and persistent mode: the geometry's planes allow the two-track
+    // kernel
+    bool pair_ok;
     int n_triplets;   // of the context's parameters
 };
 

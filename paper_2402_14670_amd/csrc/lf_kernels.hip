@@ -1,9 +1,9 @@
 // lf_kernels.hip -- Looking Forward track following, gfx950 kernels.
 //
-// One wavefront (64 lanes) carries one upstream input track -- or, in large
-// batches seeded in binary32, each half of it one of two tracks or one of a
-// track's two sides (lf_pair.h) -- through every step of the method (arXiv 2402.14670,
-// "Algorithm logic"):
+// One wavefront (64 lanes) carries one upstream input track -- or, in the
+// batched and persistent modes without binary16 seeding, each half of it one of
+// two tracks or one of a track's two sides (lf_pair.h) -- through every step of
+// the method (arXiv 2402.14670, "Algorithm logic"):
 //
 //   windows    the kick (linear, or the sqrt-normalised pt-kick with the
 //              momentum parametrisation F), then 36 lanes: (layer, bound)
@@ -1848,7 +1848,11 @@ hipError_t launch_nw_wpb(const DevBatch &b, const KParams *P, int mode, const Ex
                          const uint32_t *trk_off_host, hipStream_t s) {
     const dim3 block(WPB * WAVE);
     const uint32_t n = b.trk_map ? b.n_map : b.n_tracks;
-    const bool pair = cfg.pair_min && n >= cfg.pair_min && b.bidx;
+    // The two-track kernel at every size: from 40 tracks (9.9 -> 9.6 us a
+    // launch) and 200 (14.6 -> 13.9; dense events, 486 tracks, 31.4 -> 29.9;
+    // VELO-only 28.1 -> 16.2) up.  It needs the bucket indexes, which a context
+    // with a device budget goes without, and planes its constants allow.
+    const bool pair = cfg.pair_ok && b.bidx;
     if (mode == 0) {   // plain: one launch per event
         for (uint32_t e = 0; e < b.n_events; ++e) {
             const uint32_t nt = trk_off_host[e + 1] - trk_off_host[e];
@@ -2104,13 +2108,13 @@ int occ_wpb(int waves_per_block) {
 int persistent_blocks_per_cu(int n_hits_window, int n_sides, const ExecCfg &cfg) {
     const int w = cfg.waves_per_block;
     if (n_sides == 2) {
-        if (!cfg.pair_min) return n_hits_window <= 32 ? occ_wpb<32, 2>(w) : occ_wpb<64, 2>(w);
+        if (!cfg.pair_ok) return n_hits_window <= 32 ? occ_wpb<32, 2>(w) : occ_wpb<64, 2>(w);
         if (cfg.n_triplets <= 16)
             return n_hits_window <= 32 ? occ_wpb<32, 2, false, 16>(w) : occ_wpb<64, 2, false, 16>(w);
         return n_hits_window <= 32 ? occ_wpb<32, 2, false, MAX_TRIPLETS>(w) : occ_wpb<64, 2, false, MAX_TRIPLETS>(w);
     }
     if (n_sides == 3) return n_hits_window <= 32 ? occ_wpb<32, 1, true>(w) : occ_wpb<64, 1, true>(w);
-    if (!cfg.pair_min) return n_hits_window <= 32 ? occ_wpb<32, 1>(w) : occ_wpb<64, 1>(w);
+    if (!cfg.pair_ok) return n_hits_window <= 32 ? occ_wpb<32, 1>(w) : occ_wpb<64, 1>(w);
     if (cfg.n_triplets <= 16)
         return n_hits_window <= 32 ? occ_wpb<32, 1, false, 16>(w) : occ_wpb<64, 1, false, 16>(w);
     return n_hits_window <= 32 ? occ_wpb<32, 1, false, MAX_TRIPLETS>(w) : occ_wpb<64, 1, false, MAX_TRIPLETS>(w);

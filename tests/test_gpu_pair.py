@@ -1,6 +1,5 @@
-"""The two-tracks-per-wavefront kernel, which batches of 4,096 or more result
-slots take: every slot against the oracle at the edges of its lists, windows
-and event flags.  Indices and flags bit-exact, parameters within 1e-5 relative
+"""The two-tracks-per-wavefront kernel: every slot against the oracle at the
+edges of its lists, windows and event flags.  Indices and flags bit-exact, parameters within 1e-5 relative
 (the same binary32 expressions in the same order on both sides)."""
 import numpy as np
 import pytest
@@ -41,8 +40,8 @@ def _cut_tracks(ev, n):
     return lfgen.Events(**{**ev.__dict__, "trk_off": off, **cut})
 
 
-@pytest.mark.parametrize("n_tracks", [MIN - 1, MIN, MIN + 1])
-def test_least_and_odd_slot_counts(n_tracks):
+@pytest.mark.parametrize("n_tracks", [1, 2, 3, 63, 64, 65, MIN - 1, MIN, MIN + 1])
+def test_slot_counts(n_tracks):
     ev = _cut_tracks(lfgen.generate("nominal", n_events=21, seed=50), n_tracks)
     ref = oracle_parallel(ev)
     for mode in ("batched", "persistent"):
