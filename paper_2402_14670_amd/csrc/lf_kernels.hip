@@ -1,7 +1,7 @@
 // lf_kernels.hip -- Looking Forward track following, gfx950 kernels.
 //
 // One wavefront (64 lanes) carries one upstream input track -- or, in the
-// batched and persistent modes without binary16 seeding, each half of it one of
+// batched and persistent modes, each half of it one of
 // two tracks or one of a track's two sides (lf_pair.h) -- through every step of
 // the method (arXiv 2402.14670, "Algorithm logic"):
 //
@@ -1499,8 +1499,8 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NS =
 
 // The two-track body for result slots t0 and t0 + 1 (if < n), or (NS = 2) for
 // slot t0.
-template <int NW, int MT, int NS>
-__device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams *__restrict__ P, PairLds<NW, MT> &lds,
+template <int NW, int MT, int NS, bool H16>
+__device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams *__restrict__ P, PairLds<NW, MT, H16> &lds,
                                                int lane, uint32_t t0, uint32_t n) {
     const uint32_t t = NS == 1 ? t0 + (uint32_t)(lane >> 5) : t0;
     const bool act = t < n;
@@ -1509,10 +1509,10 @@ __device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams 
     const uint32_t ev = B.trk_ev[tin];
     const uint32_t evf = B.uni[ev];
     if (__ballot(!(evf & EV_PLANES)) == 0) {
-        Pair<NW, MT, true, NS> pr{B, P, lds};
+        Pair<NW, MT, true, NS, H16> pr{B, P, lds};
         pr.run(lane, slot, ev, evf, tin, act);
     } else {
-        Pair<NW, MT, false, NS> pr{B, P, lds};
+        Pair<NW, MT, false, NS, H16> pr{B, P, lds};
         pr.run(lane, slot, ev, evf, tin, act);
     }
 }
@@ -1522,17 +1522,17 @@ constexpr uint32_t pair_tracks(int NS) { return NS == 1 ? 2 : 1; }   // tracks p
 // windows: 7 waves per SIMD, 72 registers and a few spilled: 0.205 ms for
 // 200,000 nominal tracks and 0.317 ms for 121,500 in dense events, against
 // 0.211 and 0.335 with 80 registers at 6 waves.  64-hit windows: what LDS allows.
-constexpr int pair_waves(int NW, int MT) { return NW == 32 ? (MT == 16 ? 7 : 5) : (MT == 16 ? 5 : 4); }
-template <int NW, int MT, int WPB, int NS>
-__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(pair_waves(NW, MT)))) void k_pair(
+constexpr int pair_waves(int NW, int MT, bool H16) { return NW == 32 ? (MT == 16 ? 7 : 5) : (MT == 16 && !H16 ? 5 : 4); }
+template <int NW, int MT, int WPB, int NS, bool H16>
+__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(pair_waves(NW, MT, H16)))) void k_pair(
     DevBatch B, const KParams *__restrict__ P) {
-    __shared__ PairLds<NW, MT> lds[WPB];
+    __shared__ PairLds<NW, MT, H16> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const uint32_t per = gridDim.x / NXCD;
     const uint32_t lb = (blockIdx.x % NXCD) * per + blockIdx.x / NXCD;
     const uint32_t t0 = pair_tracks(NS) * (lb * WPB + w), n = B.trk_map ? B.n_map : B.n_tracks;
     if (t0 >= n) return;
-    pair_of_tracks<NW, MT, NS>(B, P, lds[w], lane_id(), t0, n);
+    pair_of_tracks<NW, MT, NS, H16>(B, P, lds[w], lane_id(), t0, n);
 }
 
 // Persistent: QUEUE_N work queues, QUEUE_SUB per XCD.  XCD x owns a
@@ -1557,7 +1557,7 @@ static_assert(QUEUE_N == NXCD * QUEUE_SUB, "QUEUE_SUB queues per XCD");
 template <int NW, int NS, int WPB, bool H16 = false, int MT = 0>
 __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT == 0 ? 1 : NW == 32 && MT == 16 ? 5 : 4))) void k_persistent(DevBatch B, const KParams *__restrict__ P,
                                                             uint32_t items) {
-    __shared__ std::conditional_t<MT != 0, PairLds<NW, MT != 0 ? MT : 16>, WaveLds<NW, NS>> lds[WPB];
+    __shared__ std::conditional_t<MT != 0, PairLds<NW, MT != 0 ? MT : 16, H16>, WaveLds<NW, NS>> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     uint32_t *q = B.counter;
     const uint32_t T = B.n_tracks;
@@ -1602,7 +1602,7 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT =
             // costs ~30 VGPRs of loop-carried state and two waves per SIMD
             asm volatile("" ::: "memory");
             if constexpr (MT != 0) {
-                pair_of_tracks<NW, MT, NS>(B, opaque_params(P), lds[w], opaque_lane_id(), t, t1);
+                pair_of_tracks<NW, MT, NS, H16>(B, opaque_params(P), lds[w], opaque_lane_id(), t, t1);
             } else {
                 Track<NW, NS, false, H16> tr{B, P, lds[w], 0, {}, 0};
                 tr.ln = opaque_lane_id();
@@ -1864,27 +1864,23 @@ hipError_t launch_nw_wpb(const DevBatch &b, const KParams *P, int mode, const Ex
         const uint32_t need = (b.n_tracks + WPB - 1) / WPB;
         if (grid > need) grid = need;
         if (grid == 0) grid = 1;
-        if constexpr (!H16) {
-            if (pair) {
-                const uint32_t items = (uint32_t)cfg.items_per_grab;
-                if (cfg.n_triplets <= 16)
-                    hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, 16>), dim3(grid), block, 0, s, b, P, items);
-                else
-                    hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, MAX_TRIPLETS>), dim3(grid), block, 0, s, b, P, items);
-                return hipGetLastError();
-            }
+        if (pair) {
+            const uint32_t items = (uint32_t)cfg.items_per_grab;
+            if (cfg.n_triplets <= 16)
+                hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, 16>), dim3(grid), block, 0, s, b, P, items);
+            else
+                hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, MAX_TRIPLETS>), dim3(grid), block, 0, s, b, P, items);
+            return hipGetLastError();
         }
         hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16>), dim3(grid), block, 0, s, b, P,
                            (uint32_t)cfg.items_per_grab);
     } else {   // batched: one launch, one wavefront per track (or per mapped slot), XCD-ordered
-        if constexpr (!H16) {
-            if (pair) {
-                const uint32_t waves = (n + pair_tracks(NS) - 1) / pair_tracks(NS);
-                const dim3 g(((waves + WPB - 1) / WPB + NXCD - 1) / NXCD * NXCD);
-                if (cfg.n_triplets <= 16) hipLaunchKernelGGL((k_pair<NW, 16, WPB, NS>), g, block, 0, s, b, P);
-                else hipLaunchKernelGGL((k_pair<NW, MAX_TRIPLETS, WPB, NS>), g, block, 0, s, b, P);
-                return hipGetLastError();
-            }
+        if (pair) {
+            const uint32_t waves = (n + pair_tracks(NS) - 1) / pair_tracks(NS);
+            const dim3 g(((waves + WPB - 1) / WPB + NXCD - 1) / NXCD * NXCD);
+            if (cfg.n_triplets <= 16) hipLaunchKernelGGL((k_pair<NW, 16, WPB, NS, H16>), g, block, 0, s, b, P);
+            else hipLaunchKernelGGL((k_pair<NW, MAX_TRIPLETS, WPB, NS, H16>), g, block, 0, s, b, P);
+            return hipGetLastError();
         }
         const uint32_t need = (n + WPB - 1) / WPB;
         const uint32_t grid = (need + NXCD - 1) / NXCD * NXCD;
@@ -2107,17 +2103,18 @@ int occ_wpb(int waves_per_block) {
 
 int persistent_blocks_per_cu(int n_hits_window, int n_sides, const ExecCfg &cfg) {
     const int w = cfg.waves_per_block;
-    if (n_sides == 2) {
-        if (!cfg.pair_ok) return n_hits_window <= 32 ? occ_wpb<32, 2>(w) : occ_wpb<64, 2>(w);
-        if (cfg.n_triplets <= 16)
-            return n_hits_window <= 32 ? occ_wpb<32, 2, false, 16>(w) : occ_wpb<64, 2, false, 16>(w);
-        return n_hits_window <= 32 ? occ_wpb<32, 2, false, MAX_TRIPLETS>(w) : occ_wpb<64, 2, false, MAX_TRIPLETS>(w);
-    }
-    if (n_sides == 3) return n_hits_window <= 32 ? occ_wpb<32, 1, true>(w) : occ_wpb<64, 1, true>(w);
-    if (!cfg.pair_ok) return n_hits_window <= 32 ? occ_wpb<32, 1>(w) : occ_wpb<64, 1>(w);
-    if (cfg.n_triplets <= 16)
-        return n_hits_window <= 32 ? occ_wpb<32, 1, false, 16>(w) : occ_wpb<64, 1, false, 16>(w);
-    return n_hits_window <= 32 ? occ_wpb<32, 1, false, MAX_TRIPLETS>(w) : occ_wpb<64, 1, false, MAX_TRIPLETS>(w);
+    auto waves = [&](auto ns, auto h16) {
+        constexpr int NS = decltype(ns)::value;
+        constexpr bool H16 = decltype(h16)::value;
+        const bool w32 = n_hits_window <= 32;
+        if (!cfg.pair_ok) return w32 ? occ_wpb<32, NS, H16>(w) : occ_wpb<64, NS, H16>(w);
+        if (cfg.n_triplets <= 16) return w32 ? occ_wpb<32, NS, H16, 16>(w) : occ_wpb<64, NS, H16, 16>(w);
+        return w32 ? occ_wpb<32, NS, H16, MAX_TRIPLETS>(w) : occ_wpb<64, NS, H16, MAX_TRIPLETS>(w);
+    };
+    using One = std::integral_constant<int, 1>;
+    if (n_sides == 2) return waves(std::integral_constant<int, 2>{}, std::false_type{});
+    if (n_sides == 3) return waves(One{}, std::true_type{});
+    return waves(One{}, std::false_type{});
 }
 
 }  // namespace lfk

@@ -2,8 +2,8 @@
 // Included by lf_kernels.hip (namespace lfk, anonymous).
 //
 // Lanes 0..31 carry one track, lanes 32..63 the next one, through the steps
-// described in lf_kernels.hip, for VELO-UT input seeded in binary32 (VELO-only
-// input: each half one side of the same track).  The arithmetic of every result
+// described in lf_kernels.hip, for VELO-UT input (VELO-only input: each half one
+// side of the same track).  The arithmetic of every result
 // is the one of Track, in the same order.
 //
 // The path is bound by vector instruction issue: a plain add, multiply or move
@@ -34,13 +34,31 @@
 // lanes per extension, 0.226 with four lanes per fit); 160,000 with per-hit z
 // and slopes 0.445 -> 0.226; 121,500 in dense events 0.477 -> 0.274 (0.314 with
 // the pairs written into a queue item by item); 100,000 VELO-only 0.444 ->
-// 0.303; 4,800 nominal 0.0204 -> 0.0155.
+// 0.303; 160,000 nominal seeded in binary16 0.352 -> 0.187; 4,800 nominal 0.0204 -> 0.0155.
 
 // One track's LDS: the x of its window hits (row l: layer l, NW slots, +inf
 // past the window's end, so that a sorted search needs no length), per layer
 // (u, g(u), dxdy y) and the lists of seeding and candidates.
-template <int NW, int MT>
-struct alignas(16) HalfLds {
+// H16 (binary16 seeding): per track and seed set, coordinates relative to the
+// window centres c and the constants rounded once from binary32, as in
+// Track::run; e: what the bracket of the third layer needs in binary32.
+struct alignas(16) SeedSet16 {
+    float c[3];        // window centres of the set's layers
+    uint32_t on;       // each outer window's hits share one z (else binary32)
+    float E0, C02, rs, S;   // E0, C02; 1 / (RZ L0) and |RZ L0|
+    float rL, err;     // 1 / |L0|, and the part of the rounding bound common to all pairs
+    _Float16 hE0, hC02, hRZ, hL0, hA, hKK, hB, pad;
+    uint32_t pad2[2];
+};
+template <bool H16>
+struct Seeds16 {};
+template <>
+struct Seeds16<true> {
+    SeedSet16 h16[2];
+};
+
+template <int NW, int MT, bool H16 = false>
+struct alignas(16) HalfLds : Seeds16<H16> {
     static constexpr int RS = NW + 1;
     uint64_t tk[MT];                 // top-n keys, sorted; ~0 past the list
     int2 win[NL];                    // first hit (event-local) and length of each window
@@ -65,9 +83,9 @@ struct alignas(16) HalfLds {
     float2 zr[2];                    // z range of each seed set's third bucket (hits off the planes)
 };
 
-template <int NW, int MT>
+template <int NW, int MT, bool H16 = false>
 struct PairLds {
-    HalfLds<NW, MT> h[2];
+    HalfLds<NW, MT, H16> h[2];
     float4 set[2][3];                // KParams::set_tab
     double2 rset[2][2];              // KParams::r_set
 };
@@ -140,14 +158,16 @@ __device__ __forceinline__ uint32_t row_closest_near(uint32_t row, uint32_t end,
 // windows per layer): one track per wavefront, a half for each side's windows,
 // seeds and candidates; the halves meet where the top-n pool of both sides is
 // cut and where the best candidate is chosen.
-template <int NW, int MT, bool PL, int NS>
+template <int NW, int MT, bool PL, int NS, bool H16 = false>
 struct Pair {
+    static_assert(NS == 1 || !H16, "binary16 seeding has one window per layer");
+    using Half = HalfLds<NW, MT, H16>;
     const DevBatch &B;
     const KParams *__restrict__ P;
-    PairLds<NW, MT> &S;
+    PairLds<NW, MT, H16> &S;
     uint32_t ebase = 0;   // the event's first hit
 
-    static constexpr int RS = HalfLds<NW, MT>::RS;
+    static constexpr int RS = Half::RS;
 
     __device__ __forceinline__ static uint32_t umax(uint32_t a, uint32_t b) { return a > b ? a : b; }
     __device__ __forceinline__ static int halfmax(int v) {   // v uniform in each half
@@ -159,7 +179,7 @@ struct Pair {
     // uniform in each half (NS = 2: in the wave); act: the half has a track.
     __device__ __forceinline__ void run(int lane, uint32_t t, uint32_t ev, uint32_t evf, uint32_t tin, bool act) {
         const int j = lane & (HALF - 1);
-        HalfLds<NW, MT> &L = S.h[lane >> 5];
+        Half &L = S.h[lane >> 5];
 
         // ---- state, kinematics ----
         const float x_in = B.tx_[tin], y_in = B.ty_[tin], tx_in = B.ttx[tin], ty_in = B.tty[tin];
@@ -240,8 +260,9 @@ struct Pair {
         const float ye = y_in + ty_in * (zl - P->z_in);
         const float cuv = uvl ? dxl * ye : 0.0f;
         int first, len;
+        float xc;   // lane l: the window centre of layer l
         {
-            float xc, xmin, xmax;
+            float xmin, xmax;
             if constexpr (NS == 2) {
                 // straight line; two windows per layer sharing an overlap
                 const float xe = x_in + tx_in * (zl - P->z_in);
@@ -368,6 +389,10 @@ struct Pair {
         // i0 << 6 | i2.
         const float tolc = P->magtol_const + P->magtol_pscale / p;
         const bool low_p = NS == 1 && p < P->p_charge_cut;
+        if constexpr (H16) {
+            seeds16(lane, xc, x_mag, tolc);
+            wave_sync();
+        }
         int nA = 0, nB = 0;    // kept triplets of the two halves (uniform)
         const int c1 = L.win[0].y, n_items = c1 + L.win[3].y;
         const int items_max = halfmax(n_items);
@@ -384,7 +409,11 @@ struct Pair {
                 const float4 sk = S.set[s ? 1 : 0][2];   // dz, 1 / lever arm, K, lever arm
                 float xlo, xhi;
                 bool all;   // no bracket, or one that overflowed: every pair
-                if constexpr (PL) {
+                bool on16 = false;
+                if constexpr (H16) on16 = PL || L.h16[s ? 1 : 0].on;
+                if (on16) {
+                    if constexpr (H16) all = bracket16(L.h16[s ? 1 : 0], x0, tolc, xlo, xhi);
+                } else if constexpr (PL) {
                     const float dz = sk.x;
                     float w0;
                     const float tc = slope_bracket(x0, x_mag, sk.y, tolc, w0);
@@ -458,7 +487,7 @@ struct Pair {
             // one pool of n_triplets for both sides: each list is cut where its
             // entries' ranks among both reach it
             const uint64_t mine = L.tk[j & (MT - 1)];
-            const HalfLds<NW, MT> &O = S.h[lane < HALF ? 1 : 0];
+            const Half &O = S.h[lane < HALF ? 1 : 0];
             const int n_max = nA > nB ? nA : nB;
             int r = j;
             for (int i = 0; i < n_max; i += 4) {
@@ -527,40 +556,184 @@ struct Pair {
         return tc;
     }
 
+    // The constants of binary16 seeding: lane s of a half computes those of set s.
+    __device__ __forceinline__ void seeds16(int lane, float xc, float x_mag, float tolc) {
+        const int j = lane & (HALF - 1);
+        Half &L = S.h[lane >> 5];
+        bool shared = true;   // lane s: set s's outer windows each share one z
+        if constexpr (!PL) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int l = (k & 1 ? 3 : 0) + (k & 2 ? 8 : 0);   // 0, 3, 8, 11
+                const int2 w = L.win[l];
+                bool differ = false;
+#pragma unroll
+                for (int i = 0; i < NW / HALF; ++i) {
+                    const int h = j + HALF * i;
+                    if (h < w.y && __float_as_uint(ld32(B.hz, ebase + (uint32_t)(w.x + h))) !=
+                                       __float_as_uint(ld32(B.hz, ebase + (uint32_t)w.x)))
+                        differ = true;
+                }
+                const uint64_t bal = __ballot(differ);
+                if ((uint32_t)(bal >> (lane & HALF)) != 0 && (j & 1) == (k & 1)) shared = false;
+            }
+        }
+        const bool s = j & 1;
+        const float c0 = __shfl(xc, (lane & HALF) + (s ? 3 : 0)), c1 = __shfl(xc, (lane & HALF) + (s ? 7 : 4)),
+                    c2 = __shfl(xc, (lane & HALF) + (s ? 11 : 8));
+        const float4 sa = S.set[s ? 1 : 0][1], sk = S.set[s ? 1 : 0][2];   // .., z0, z1; dz, .., K, lever arm
+        float z0 = sa.z, dz = sk.x, lev = sk.w;
+        bool on = true;
+        if constexpr (!PL) {
+            const int2 w0 = L.win[s ? 3 : 0], w2 = L.win[s ? 11 : 8];
+            on = shared && w0.y > 0 && w2.y > 0;
+            z0 = on ? ld32(B.hz, ebase + (uint32_t)w0.x) : 0.0f;
+            dz = on ? ld32(B.hz, ebase + (uint32_t)w2.x) - z0 : 1.0f;
+            lev = P->z_mag - z0;
+        }
+        const float K = sk.z;
+        SeedSet16 h;
+        h.c[0] = c0;
+        h.c[1] = c1;
+        h.c[2] = c2;
+        h.on = on;
+        h.hRZ = (_Float16)(1.0f / dz);
+        h.hC02 = (_Float16)(c2 - c0);
+        h.hE0 = (_Float16)(c0 - x_mag);
+        h.hL0 = (_Float16)lev;
+        h.hA = (_Float16)(sa.w - z0 * K);
+        h.hKK = (_Float16)K;
+        h.hB = (_Float16)(c0 * K - c1);
+        h.pad = (_Float16)0.0f;
+        h.pad2[0] = h.pad2[1] = 0;
+        h.E0 = (float)h.hE0;
+        h.C02 = (float)h.hC02;
+        const float sl = (float)h.hRZ * (float)h.hL0;
+        h.S = fabsf(sl);
+        h.rs = 1.0f / sl;
+        h.rL = 1.0f / fabsf((float)h.hL0);
+        h.err = EPS16 * (6.0f * (float)(_Float16)P->magtol_max + 2.0f * h.S * fabsf(h.C02)) + 0.01f;
+        if (j < 2) L.h16[j] = h;
+    }
+    static constexpr float EPS16 = 5.5e-4f;   // binary16's unit roundoff, 2^-11, and an eighth
+
+    // The third-layer hits that can pass the binary16 magnet filter for first
+    // hit x0; true: there is no bracket.  With m1 = E0 + x0 - c0 and s = RZ L0 of
+    // the rounded constants, M = m1 + (x2 - c2 - (x0 - c0) + C02) s but for the
+    // rounding of eight operations.  Each is off by 2^-11 of its result, and
+    // where |M| < Tm, the largest tolerance, the results after the product with
+    // L0 are bounded by b = Tm + |m1|, the terms before it by b / |s| and the
+    // constants: together by 2^-11 (6 Tm + 6 |m1| + |x0 - c0| + 2 |s| (|C02| +
+    // |x0 - c0|)), taken an eighth larger.
+    __device__ __forceinline__ bool bracket16(const SeedSet16 &h, float x0, float tolc, float &xlo, float &xhi) const {
+        const float x0r = x0 - h.c[0], m1 = h.E0 + x0r, am1 = fabsf(m1), ax0 = fabsf(x0r);
+        const float tmax = (float)(_Float16)P->magtol_max, tmin = (float)(_Float16)P->magtol_min;
+        const float txs = P->magtol_txscale > 0.0f ? (float)(_Float16)P->magtol_txscale : 0.0f;
+        const float raw = (float)(_Float16)tolc + txs * ((tmax + am1) * h.rL);
+        float tolb = raw + (2e-3f * fabsf(raw) + 1e-6f);
+        if (tolb < tmin) tolb = tmin;
+        if (tolb > tmax) tolb = tmax;
+        const float W = tolb + h.err + EPS16 * (6.0f * am1 + ax0 + 2.0f * h.S * ax0);
+        const float q = m1 * h.rs;
+        const float e = h.c[2] + ((x0r - h.C02) - q);
+        const float w0 = W * fabsf(h.rs);
+        const float w = w0 + (0.05f + 1e-5f * (fabsf(e) + w0 + fabsf(q) + fabsf(h.c[2])));
+        xlo = e - w;
+        xhi = e + w;
+        return !(fabsf(e) + w < 1e30f);
+    }
+
+    // Seed pair (x0, x2) in binary16: the filters, the closest middle hit (its
+    // index in the row at row1: best) and its squared distance.  The operations
+    // are Track's, in the same order.
+    __device__ __forceinline__ bool triplet16(const SeedSet16 &h, bool in, float x0, float x2, uint32_t row1, float tolc,
+                                              bool low_p, float tx_in, float qop, uint32_t &best, float &chi2) const {
+        const _Float16 X0 = (_Float16)(x0 - h.c[0]);
+        const _Float16 X2 = (_Float16)(x2 - h.c[2]);
+        const _Float16 u = X2 - X0;
+        const _Float16 v = u + h.hC02;
+        const _Float16 t = v * h.hRZ;
+        const _Float16 w1 = t - (_Float16)tx_in;
+        const _Float16 w2 = w1 * (_Float16)qop;
+        bool ok = in && !(low_p && !(w2 > (_Float16)0.0f));
+        const _Float16 m1 = h.hE0 + X0;
+        const _Float16 m2 = t * h.hL0;
+        const _Float16 M = m1 + m2;
+        const _Float16 r1 = (_Float16)P->magtol_txscale * habs(t);
+        _Float16 tol = (_Float16)tolc + r1;
+        const _Float16 tmin = (_Float16)P->magtol_min, tmax = (_Float16)P->magtol_max;
+        if (tol < tmin) tol = tmin;
+        if (tol > tmax) tol = tmax;
+        if (!(habs(M) < tol)) ok = false;
+        const _Float16 a1 = t * h.hA;
+        const _Float16 a2 = X0 * h.hKK;
+        const _Float16 a3 = a1 + a2;
+        const _Float16 X1e = a3 + h.hB;
+        const float c1 = h.c[1];
+        // the row's binary16 values Y are sorted and +inf past the window's end
+        uint32_t p[1] = {row1};
+        row_lower<NW>(p, [c1, X1e](int, float x) { return (_Float16)(x - c1) < X1e; });
+        auto D = [c1, X1e](uint32_t a) { return habs((_Float16)(lds_at(a) - c1) - X1e); };
+        const uint32_t pm = p[0] > row1 ? p[0] - 4u : row1;
+        const _Float16 d = D(p[0]), dl = D(pm);
+        const bool left = p[0] > row1 && !(dl > d);
+        uint32_t a = left ? pm : p[0];
+        const _Float16 hb = left ? dl : d;
+        const _Float16 c2h = hb * hb;
+        chi2 = (float)c2h;
+        ok = ok && c2h < (_Float16)P->T_triplet;
+        // equal distances before the left neighbour: binary16 has many far from
+        // the prediction, so only where the triplet passes (160,000 tracks 217
+        // -> 187 us, 20 dense events 125 -> 73)
+        if (ok && left)
+            while (a > row1 && D(a - 4u) == dl) a -= 4u;
+        best = (a - row1) >> 2;
+        return ok;
+    }
+
     // Up to 32 seed pairs per half (one per lane, in: the lane has one): the
     // doublet filters, the closest middle hit, the triplet cut, and the merge
     // of the accepted triplets into the half's top-n list.
     __device__ __forceinline__ void triplets(int lane, bool in, uint32_t e, int &nA, int &nB, float tolc, bool low_p,
                                              float tx_in, float qop, float x_mag) {
         const int j = lane & (HALF - 1);
-        HalfLds<NW, MT> &L = S.h[lane >> 5];
+        Half &L = S.h[lane >> 5];
         const int NT = P->n_triplets;
         const bool s = (e >> 12) & 1u;
         const int i0 = (int)((e >> 6) & 63u), i2 = (int)(e & 63u);
         const int ro = s ? 3 * RS : 0;
         const float x0 = L.wx[ro + (i0 & (NW - 1))], x2 = L.wx[8 * RS + ro + (i2 & (NW - 1))];
-        const float4 sa = S.set[s ? 1 : 0][1], sk = S.set[s ? 1 : 0][2];   // .., z0, z1; dz, .., K, lever arm
-        float z0 = sa.z, dz = sk.x, lev = sk.w;
-        if constexpr (!PL) {
-            z0 = in ? ld32(B.hz, ebase + (uint32_t)(L.win[s ? 3 : 0].x + i0)) : 0.0f;
-            dz = (in ? ld32(B.hz, ebase + (uint32_t)(L.win[s ? 11 : 8].x + i2)) : 1.0f) - z0;
-            lev = P->z_mag - z0;
-        }
-        const float txd = PL ? div_by(x2 - x0, S.rset[s ? 1 : 0][0].x) : (x2 - x0) / dz;
-        bool ok = in && !(low_p && !((txd - tx_in) * qop > 0.0f));
-        const float xm = x0 + txd * lev;
-        float tol = tolc + P->magtol_txscale * fabsf(txd);
-        if (tol < P->magtol_min) tol = P->magtol_min;
-        if (tol > P->magtol_max) tol = P->magtol_max;
-        if (!(fabsf(xm - x_mag) < tol)) ok = false;
-        const float x1e = sa.w * txd + (x0 - txd * z0) * sk.z;
+        bool ok, on16 = false;
+        uint32_t best = 0;
+        float chi2 = 0.0f;
         const uint32_t row1 = lds_addr(&L.wx[4 * RS + ro]);
-        uint32_t p1[1] = {row1};
-        row_lower<NW>(p1, [x1e](int, float v) { return v < x1e; });
-        float bd;
-        const uint32_t best = (row_closest(row1, 0.0f, x1e, p1[0], bd) - row1) >> 2;
-        const float chi2 = bd * bd;
-        ok = ok && bd < INFINITY && chi2 < P->T_triplet;
+        if constexpr (H16) {
+            on16 = PL || L.h16[s ? 1 : 0].on;
+            if (on16) ok = triplet16(L.h16[s ? 1 : 0], in, x0, x2, row1, tolc, low_p, tx_in, qop, best, chi2);
+        }
+        if (!on16) {
+            const float4 sa = S.set[s ? 1 : 0][1], sk = S.set[s ? 1 : 0][2];   // .., z0, z1; dz, .., K, lever arm
+            float z0 = sa.z, dz = sk.x, lev = sk.w;
+            if constexpr (!PL) {
+                z0 = in ? ld32(B.hz, ebase + (uint32_t)(L.win[s ? 3 : 0].x + i0)) : 0.0f;
+                dz = (in ? ld32(B.hz, ebase + (uint32_t)(L.win[s ? 11 : 8].x + i2)) : 1.0f) - z0;
+                lev = P->z_mag - z0;
+            }
+            const float txd = PL ? div_by(x2 - x0, S.rset[s ? 1 : 0][0].x) : (x2 - x0) / dz;
+            ok = in && !(low_p && !((txd - tx_in) * qop > 0.0f));
+            const float xm = x0 + txd * lev;
+            float tol = tolc + P->magtol_txscale * fabsf(txd);
+            if (tol < P->magtol_min) tol = P->magtol_min;
+            if (tol > P->magtol_max) tol = P->magtol_max;
+            if (!(fabsf(xm - x_mag) < tol)) ok = false;
+            const float x1e = sa.w * txd + (x0 - txd * z0) * sk.z;
+            uint32_t p1[1] = {row1};
+            row_lower<NW>(p1, [x1e](int, float v) { return v < x1e; });
+            float bd;
+            best = (row_closest(row1, 0.0f, x1e, p1[0], bd) - row1) >> 2;
+            chi2 = bd * bd;
+            ok = ok && bd < INFINITY && chi2 < P->T_triplet;
+        }
         const uint64_t key = ((uint64_t)__float_as_uint(chi2) << 32) | e;
         // a full list only admits keys below its last one
         ok = ok && key < L.tk[NT - 1];
@@ -624,7 +797,7 @@ struct Pair {
             const int kk = k0 + (lane >> 2);
             const bool on = kk < nA + nB, second = kk >= nA;
             const int k = second ? kk - nA : kk, r = on ? k : 0;
-            HalfLds<NW, MT> &L = S.h[second ? 1 : 0];
+            Half &L = S.h[second ? 1 : 0];
             const uint32_t rows = lds_addr(&L.wx[4 * sq * RS]);
             const float T_uv = second ? bcast_f(T_uv_, HALF) : bcast_f(T_uv_, 0);
             uint32_t eb = 0;
@@ -743,7 +916,7 @@ struct Pair {
     // quality in best_Q), or -1.
     __device__ __forceinline__ int fits(int lane, int nL, float T_uv, float y_in, float ty_in, float &best_Q) {
         const int j = lane & (HALF - 1);
-        HalfLds<NW, MT> &L = S.h[lane >> 5];
+        Half &L = S.h[lane >> 5];
         uint32_t mine;   // the half's candidates to fit
         {
             bool rule = false;

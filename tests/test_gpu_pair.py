@@ -1,6 +1,7 @@
 """The two-tracks-per-wavefront kernel: every slot against the oracle at the
-edges of its lists, windows and event flags.  Indices and flags bit-exact, parameters within 1e-5 relative
-(the same binary32 expressions in the same order on both sides)."""
+edges of its lists, windows and event flags.  Indices and flags bit-exact,
+parameters within 1e-5 relative (the same expressions in the same order on both
+sides)."""
 import numpy as np
 import pytest
 
@@ -194,6 +195,32 @@ def test_velo_only_dense_and_tied():
     dup = lfgen.Events(**{**ev.__dict__, "hit_off": cum[ev.hit_off.astype(np.int64)].astype(np.uint32),
                           **{k: np.repeat(getattr(ev, k), rep) for k in ("hit_x", "hit_z", "hit_dxdy", "hit_pid")}})
     _check(dup, "no-UT doubled hits", {"velo_only": 1}, modes=("batched",))
+
+
+@pytest.mark.parametrize("extra", [
+    {}, {"n_hits_window": 64, "n_triplets": 32}, {"n_hits_window": 8, "n_triplets": 3},
+    {"magtol_min": 3000.0, "magtol_max": 3000.0, "T_triplet": 50.0}, {"magtol_max": 1e5, "magtol_txscale": 50.0},
+    {"magtol_txscale": -20.0, "magtol_min": 0.5}, {"p_charge_cut": 50000.0, "T_triplet": 1e5},
+], ids=["default", "w64_t32", "w8_t3", "loose", "tolerance_past_binary16", "falling_tolerance", "charge_filter_loose_cut"])
+def test_binary16_seeding(extra):
+    """The pairs that the bracket leaves out are those that the binary16 filter
+    rejects, whatever its constants; sets whose windows hold one z off the
+    planes, and sets with mixed z, which stay binary32."""
+    params = {"seed_fp16": 1, **extra}
+    ev = lfgen.generate("nominal", n_events=21, seed=80)
+    _check(ev, f"binary16 {extra}", params)
+    shifted = lfgen.Events(**{**ev.__dict__, "hit_z": ev.hit_z + np.float32(1.5)})
+    _check(shifted, f"binary16 shifted {extra}", params, modes=("batched",))
+    rng = np.random.default_rng(81)
+    some = np.isin(ev.hit_z, np.array([lfgen.LAYER_Z[l] for l in (0, 11)], np.float32)) & (rng.random(ev.n_hits) < 0.02)
+    hz = (ev.hit_z + np.where(some, rng.uniform(-3.0, 3.0, ev.n_hits), 0.0)).astype(np.float32)
+    _check(lfgen.Events(**{**ev.__dict__, "hit_z": hz}), f"binary16 mixed {extra}", params, modes=("batched",))
+    _check(lfgen.generate("nominal", field="paper", n_events=21, seed=82), f"binary16 paper {extra}", params,
+           lfgen.world("paper"), modes=("batched",))
+
+
+def test_binary16_dense_events():
+    _check(lfgen.generate("stress", n_events=9, seed=83), "binary16 stress", {"seed_fp16": 1})
 
 
 def test_noalloc_and_budget_contexts():
