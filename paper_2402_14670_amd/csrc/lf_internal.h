@@ -74,7 +74,7 @@ struct alignas(16) BucketIndex {
     float lo, scale;
     // ranges over the bucket: z, max dxdy - min dxdy, max |dxdy|, max |x|
     float zmin, zmax, dspread, dabs, xabs;
-    uint16_t start[IDX_CELLS + 1], pad;
+    uint16_t start[IDX_CELLS + 1], flags;
 };
 static_assert(sizeof(BucketIndex) == 160, "written as 40 words");
 __host__ __device__ inline int index_cell(float x, float lo, float scale) {
@@ -82,10 +82,12 @@ __host__ __device__ inline int index_cell(float x, float lo, float scale) {
 }
 constexpr uint32_t IDX_MAX_BUCKET = 65535;   // hits of a bucket the index can hold
 
-// Flags of an event (DevBatch::uni).
-enum { EV_UNIFORM = 1,    // in every bucket all hits share one z and one dxdy (bit for bit)
-       EV_PLANES = 2,     // and these are the geometry's layer planes (z, and dxdy on stereo layers)
-       EV_NO_INDEX = 4 }; // a bucket is too long for the index
+// Flags of an event: of its buckets six by six in BucketIndex::flags of the
+// first of the six, or, in a batch without indexes, of all in DevBatch::uni.
+enum { EV_MIXED = 1,       // in some bucket the hits differ in z or dxdy (bit for bit)
+       EV_OFF_PLANES = 2,  // some hit is off the geometry's layer planes (z, and dxdy on stereo layers)
+       EV_NO_INDEX = 4 };  // a bucket is too long for the index
+constexpr int EV_PARTS = 4, EV_PART = 24 / EV_PARTS;
 
 // Device view of one resident batch (SoA, all in HBM).
 struct DevBatch {
@@ -94,7 +96,7 @@ struct DevBatch {
     const uint32_t *trk_off;   // [E+1]
     const uint32_t *trk_ev;    // [T] event of each track
     const float *tx_, *ty_, *ttx, *tty, *tqop;  // [T]
-    const uint8_t *uni;        // [E] EV_* flags
+    const uint8_t *uni;        // [E] EV_* flags (without bidx)
     const BucketIndex *bidx;   // [24*E], or nullptr: searches start from the whole bucket
     uint8_t *found, *nhits;    // [T]
     int32_t *hit_idx;          // [12*T]

@@ -214,6 +214,13 @@ __device__ __forceinline__ float field_c_lane(const KParams *__restrict__ P, flo
 // 2^-149, differ).  Three instructions of 4.3 cycles against eleven, 38 cycles.
 __device__ __forceinline__ float div_by(float a, double r) { return (float)((double)a * r); }
 
+// Flags of event ev: of the part that the lane's place in its quad names, so the
+// event's are those of any four lanes.
+__device__ __forceinline__ uint32_t event_flags(const DevBatch &B, uint32_t ev, int lane) {
+    static_assert(EV_PARTS == 4, "a lane of each quad per part");
+    return B.bidx ? (uint32_t)B.bidx[2 * NL * ev + (uint32_t)(EV_PART * (lane & 3))].flags : (uint32_t)B.uni[ev];
+}
+
 // Binary searches over at most NMAX (a power of two) window entries, in a
 // fixed number of steps: p advances by s = NMAX, NMAX/2, .., 1 while the
 // entry before p + s still satisfies the (monotone) predicate, so p ends as
@@ -642,9 +649,9 @@ struct Track {
         const float T = tx_in + dtx;
         const float kd = P->kappa * dtx;
         ebase = (uint32_t)__builtin_amdgcn_readlane((int)ho, 0);
-        const uint32_t evf = B.uni[ev];
-        uni = (evf & EV_UNIFORM) != 0;
-        const bool indexed = B.bidx != nullptr && !(evf & EV_NO_INDEX);
+        const uint32_t evf = event_flags(B, ev, lane);
+        uni = __ballot(evf & EV_MIXED) == 0;
+        const bool indexed = B.bidx != nullptr && __ballot(evf & EV_NO_INDEX) == 0;
         // x tolerance of the x-layer windows
         float xtol;
         if constexpr (NS == 2) {
@@ -1507,13 +1514,14 @@ __device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams 
     const uint32_t slot = act ? t : t0;
     const uint32_t tin = B.trk_map ? B.trk_map[slot] : slot;
     const uint32_t ev = B.trk_ev[tin];
-    const uint32_t evf = B.uni[ev];
-    if (__ballot(!(evf & EV_PLANES)) == 0) {
+    const uint32_t evf = event_flags(B, ev, lane);
+    const bool no_index = (uint32_t)(__ballot(evf & EV_NO_INDEX) >> (lane & HALF)) != 0;
+    if (__ballot(evf & EV_OFF_PLANES) == 0) {
         Pair<NW, MT, true, NS, H16> pr{B, P, lds};
-        pr.run(lane, slot, ev, evf, tin, act);
+        pr.run(lane, slot, ev, no_index, tin, act);
     } else {
         Pair<NW, MT, false, NS, H16> pr{B, P, lds};
-        pr.run(lane, slot, ev, evf, tin, act);
+        pr.run(lane, slot, ev, no_index, tin, act);
     }
 }
 constexpr uint32_t pair_tracks(int NS) { return NS == 1 ? 2 : 1; }   // tracks per wavefront
@@ -1681,85 +1689,78 @@ __global__ void k_track_map(const uint32_t *__restrict__ evs, const uint32_t *__
     map[i] = pool_trk_off[evs[e]] + (i - toff[e]);
 }
 
-// One block per event, two buckets per wavefront: the buckets' indexes
-// (BucketIndex) and the event's flags (EV_*).  EV_UNIFORM: in each of the 24
-// buckets every hit has the z and the stereo tangent of the bucket's first hit
-// (bit for bit).  The block also writes its tracks' trk_ev.  Bound by memory
-// latency: an event's x, z and dxdy are read once (12 B per hit) by three
-// dependent loads (offsets, hits, and the next round of a long bucket), so a
-// wavefront issues the first 256 hits of both its buckets before it waits, and
-// writes each record (160 B) with one store.
-constexpr int EVI_WAVES = 12, EVI_ROUNDS = 4;
-__global__ void __launch_bounds__(EVI_WAVES * WAVE) k_event_index(DevBatch B, const KParams *__restrict__ P,
-                                                                  uint8_t *__restrict__ uni,
-                                                                  BucketIndex *__restrict__ bidx,
-                                                                  uint32_t *__restrict__ trk_ev) {
-    __shared__ BucketIndex rec[EVI_WAVES];
-    const uint32_t e = blockIdx.x;
+// The buckets' indexes (BucketIndex) and the events' flags (EV_*), and trk_ev of
+// the events' tracks; without indexes the flags only.  A bucket per wavefront:
+// a block for every six of an event, whose flags stand in the first's record,
+// or (no indexes) one block per event.  EV_MIXED and EV_OFF_PLANES compare bit
+// for bit.  Bound by memory latency: an event's x, z and dxdy are read once
+// (12 B per hit) by dependent loads (offsets, hits, and the next round of a
+// long bucket, requested a round ahead), and each record (160 B) is one store.
+// (One block per event with two buckets per wavefront: a call with one small
+// event 15.0 us, now 13.0; with one dense event 52.4, now 42.4; 1,000 nominal
+// events 224.3, now 222.2.)
+constexpr int EVI_ROUNDS = 4;
+constexpr int evi_waves(bool IDX) { return IDX ? EV_PART : 2 * EV_PART; }
+template <bool IDX>
+__global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch B, const KParams *__restrict__ P,
+                                                                       uint8_t *__restrict__ uni,
+                                                                       BucketIndex *__restrict__ bidx,
+                                                                       uint32_t *__restrict__ trk_ev) {
+    constexpr int NWV = evi_waves(IDX), PARTS = IDX ? EV_PARTS : 1;
+    __shared__ BucketIndex rec[IDX ? NWV : 1];
+    __shared__ uint32_t fl[NWV];
+    const uint32_t e = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = lane_id();
-    struct Bucket {
-        uint32_t b0, n;
-        float x[EVI_ROUNDS], z[EVI_ROUNDS], d[EVI_ROUNDS], last;
-    } bk[2];
-    auto load = [&](Bucket &b, uint32_t i0) {   // hits i0 + 64 r + lane (past the end: the last one)
+    uint32_t flags = 0;
+    for (uint32_t k = part * EV_PART + (uint32_t)w, k1 = IDX ? k + 1 : 2 * NL; k < k1; k += NWV) {
+        struct Hits {
+            float x[EVI_ROUNDS], z[EVI_ROUNDS], d[EVI_ROUNDS];
+        } h;
+        const uint32_t b0 = B.hit_off[2 * NL * e + k], n = B.hit_off[2 * NL * e + k + 1] - b0;
+        auto load = [&](Hits &v, uint32_t i0) {   // hits i0 + 64 r + lane (past the end: the last one)
 #pragma unroll
-        for (int r = 0; r < EVI_ROUNDS; ++r) {
-            if (i0 + (uint32_t)(r * WAVE) >= b.n) continue;
-            const uint32_t i = i0 + (uint32_t)(r * WAVE + lane), g = b.b0 + (i < b.n ? i : b.n - 1);
-            b.x[r] = ld32(B.hx, g);
-            b.z[r] = ld32(B.hz, g);
-            b.d[r] = ld32(B.hd, g);
-        }
-    };
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const uint32_t k = (uint32_t)(w + q * EVI_WAVES);
-        bk[q].b0 = B.hit_off[2 * NL * e + k];
-        bk[q].n = B.hit_off[2 * NL * e + k + 1] - bk[q].b0;
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        load(bk[q], 0);
-        bk[q].last = bk[q].n ? ld32(B.hx, bk[q].b0 + bk[q].n - 1) : 0.0f;
-    }
-    int odd = 0;      // 1: a hit differs from its bucket's first; 2: a bucket too long; 4: off its plane
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        Bucket &b = bk[q];
-        const int k = w + q * EVI_WAVES;
-        const uint32_t n = b.n;
+            for (int r = 0; r < EVI_ROUNDS; ++r) {
+                if (i0 + (uint32_t)(r * WAVE) >= n) continue;
+                const uint32_t i = i0 + (uint32_t)(r * WAVE + lane), g = b0 + (i < n ? i : n - 1);
+                v.x[r] = ld32(B.hx, g);
+                v.z[r] = ld32(B.hz, g);
+                v.d[r] = ld32(B.hd, g);
+            }
+        };
+        load(h, 0);
+        const float last = n ? ld32(B.hx, b0 + n - 1) : 0.0f;
         float lo = 0.0f, scale = 0.0f, xabs = 0.0f, zmin = 0.0f, zmax = 0.0f, dmin = 0.0f, dmax = 0.0f;
         if (n) {
-            lo = bcast_f(b.x[0], 0);
-            xabs = fmaxf(fabsf(lo), fabsf(b.last));
-            zmin = zmax = bcast_f(b.z[0], 0);
-            dmin = dmax = bcast_f(b.d[0], 0);
+            lo = bcast_f(h.x[0], 0);
+            xabs = fmaxf(fabsf(lo), fabsf(last));
+            zmin = zmax = bcast_f(h.z[0], 0);
+            dmin = dmax = bcast_f(h.d[0], 0);
             // (the scale need not be exact: hits and keys are placed by the same one)
-            scale = (float)IDX_CELLS * __builtin_amdgcn_rcpf(b.last - lo);
-            if (!(b.last > lo) || !(scale < INFINITY)) scale = 0.0f;   // one cell
+            scale = (float)IDX_CELLS * __builtin_amdgcn_rcpf(last - lo);
+            if (!(last > lo) || !(scale < INFINITY)) scale = 0.0f;   // one cell
             if (__float_as_uint(zmin) != __float_as_uint(P->z[k >> 1]) ||
-                (is_uv(k >> 1) && __float_as_uint(dmin) != __float_as_uint(P->dxdy[k >> 1])))
-                odd |= 4;
+                (is_uv((int)(k >> 1)) && __float_as_uint(dmin) != __float_as_uint(P->dxdy[k >> 1])))
+                flags |= EV_OFF_PLANES;
         }
         const uint32_t z0 = __float_as_uint(zmin), d0 = __float_as_uint(dmin);
-        if (n > IDX_MAX_BUCKET) odd |= 2;
-        const bool index = bidx && n <= IDX_MAX_BUCKET;
+        if (n > IDX_MAX_BUCKET) flags |= EV_NO_INDEX;
+        const bool index = IDX && n <= IDX_MAX_BUCKET;
         int before = -1;   // cell of the hit before this round's first
         bool differ = false;
         for (uint32_t i0 = 0; i0 < n; i0 += EVI_ROUNDS * WAVE) {
-            Bucket next = b;   // the following round of a long bucket, loaded while this one is used
+            Hits next = h;   // the following round of a long bucket, loaded while this one is used
             if (i0 + EVI_ROUNDS * WAVE < n) load(next, i0 + EVI_ROUNDS * WAVE);
 #pragma unroll
             for (int r = 0; r < EVI_ROUNDS; ++r) {
                 if (i0 + (uint32_t)(r * WAVE) >= n) continue;
                 const uint32_t i = i0 + (uint32_t)(r * WAVE + lane);
-                if (__float_as_uint(b.z[r]) != z0 || __float_as_uint(b.d[r]) != d0) differ = true;
-                zmin = fminf(zmin, b.z[r]);
-                zmax = fmaxf(zmax, b.z[r]);
-                dmin = fminf(dmin, b.d[r]);
-                dmax = fmaxf(dmax, b.d[r]);
+                if (__float_as_uint(h.z[r]) != z0 || __float_as_uint(h.d[r]) != d0) differ = true;
+                zmin = fminf(zmin, h.z[r]);
+                zmax = fmaxf(zmax, h.z[r]);
+                dmin = fminf(dmin, h.d[r]);
+                dmax = fmaxf(dmax, h.d[r]);
                 if (index) {
-                    const int c = index_cell(b.x[r], lo, scale);
+                    const int c = index_cell(h.x[r], lo, scale);
                     int cp = __shfl_up(c, 1);
                     if (lane == 0) cp = before;
                     if (i < n)
@@ -1767,10 +1768,10 @@ __global__ void __launch_bounds__(EVI_WAVES * WAVE) k_event_index(DevBatch B, co
                     before = __builtin_amdgcn_readlane(c, WAVE - 1);
                 }
             }
-            b = next;
+            h = next;
         }
         if (__ballot(differ)) {
-            odd |= 1;
+            flags |= EV_MIXED | EV_OFF_PLANES;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
                 zmin = fminf(zmin, __shfl_xor(zmin, off));
@@ -1779,7 +1780,7 @@ __global__ void __launch_bounds__(EVI_WAVES * WAVE) k_event_index(DevBatch B, co
                 dmax = fmaxf(dmax, __shfl_xor(dmax, off));
             }
         }
-        if (bidx) {
+        if constexpr (IDX) {
             if (index)
                 for (int p = before + 1 + lane; p <= IDX_CELLS; p += WAVE) rec[w].start[p] = (uint16_t)n;
             if (lane == 0) {
@@ -1791,15 +1792,24 @@ __global__ void __launch_bounds__(EVI_WAVES * WAVE) k_event_index(DevBatch B, co
                 rec[w].dabs = fmaxf(fabsf(dmin), fabsf(dmax));
                 rec[w].xabs = xabs;
             }
-            wave_sync();
-            uint32_t *o = reinterpret_cast<uint32_t *>(bidx + ((size_t)e * 2 * NL + (uint32_t)k));
-            if (lane < (int)sizeof(BucketIndex) / 4) o[lane] = reinterpret_cast<const uint32_t *>(&rec[w])[lane];
-            wave_sync();
         }
     }
-    for (uint32_t t = B.trk_off[e] + threadIdx.x, t1 = B.trk_off[e + 1]; t < t1; t += blockDim.x) trk_ev[t] = e;
-    const int any = __syncthreads_or(odd & 1), lng = __syncthreads_or(odd & 2), off = __syncthreads_or(odd & 5);
-    if (threadIdx.x == 0) uni[e] = (uint8_t)((any ? 0 : EV_UNIFORM) | (off ? 0 : EV_PLANES) | (lng ? EV_NO_INDEX : 0));
+    if (lane == 0) fl[w] = flags;
+    __syncthreads();
+    flags = 0;
+#pragma unroll
+    for (int i = 0; i < NWV; ++i) flags |= fl[i];
+    if constexpr (IDX) {
+        // the record, with the six buckets' flags in the first one's
+        if (lane == 0) rec[w].flags = (uint16_t)flags;
+        wave_sync();
+        uint32_t *o = reinterpret_cast<uint32_t *>(bidx + ((size_t)e * 2 * NL + part * EV_PART + (uint32_t)w));
+        if (lane < (int)sizeof(BucketIndex) / 4) o[lane] = reinterpret_cast<const uint32_t *>(&rec[w])[lane];
+    } else if (threadIdx.x == 0) {
+        uni[e] = (uint8_t)flags;
+    }
+    const uint32_t t1 = B.trk_off[e + 1];
+    for (uint32_t t = B.trk_off[e] + part * (NWV * WAVE) + threadIdx.x; t < t1; t += PARTS * NWV * WAVE) trk_ev[t] = e;
 }
 
 // The rows of KParams::fit_tab, one thread each, from the parameters already
@@ -2027,8 +2037,14 @@ hipError_t launch_track_map(const uint32_t *evs, const uint32_t *toff, uint32_t 
 
 hipError_t launch_event_index(const DevBatch &b, const KParams *P, uint8_t *uni, hipStream_t s) {
     if (b.n_events == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_event_index, dim3(b.n_events), dim3(EVI_WAVES * WAVE), 0, s, b, P, uni,
-                       const_cast<BucketIndex *>(b.bidx), const_cast<uint32_t *>(b.trk_ev));
+    BucketIndex *idx = const_cast<BucketIndex *>(b.bidx);
+    uint32_t *trk_ev = const_cast<uint32_t *>(b.trk_ev);
+    if (idx)
+        hipLaunchKernelGGL(k_event_index<true>, dim3(EV_PARTS * b.n_events), dim3(evi_waves(true) * WAVE), 0, s, b, P,
+                           uni, idx, trk_ev);
+    else
+        hipLaunchKernelGGL(k_event_index<false>, dim3(b.n_events), dim3(evi_waves(false) * WAVE), 0, s, b, P, uni, idx,
+                           trk_ev);
     return hipGetLastError();
 }
 

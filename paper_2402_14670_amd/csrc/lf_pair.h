@@ -23,9 +23,9 @@
 //    three layers side by side, and 16 candidates of both tracks share a pass;
 //  - a division whose divisor is a constant of the context multiplies by its
 //    binary64 reciprocal (div_by: 13 cycles of issue instead of 38);
-//  - in events whose hits lie on the layer planes (EV_PLANES) every expression
-//    of the layer z alone is a constant of the context (KParams::lay_*, set_*,
-//    fit_tab), and no z or slope is loaded at all;
+//  - in events whose hits lie on the layer planes (not EV_OFF_PLANES) every
+//    expression of the layer z alone is a constant of the context
+//    (KParams::lay_*, set_*, fit_tab), and no z or slope is loaded at all;
 //  - in the others (PL = false) stereo hits are staged moved along their fibre
 //    to the track's y, which is the same for every candidate, and the closest
 //    one is found by a search and a short walk.
@@ -177,7 +177,7 @@ struct Pair {
 
     // Track tin of the batch (input state) in event ev, result slot t; all
     // uniform in each half (NS = 2: in the wave); act: the half has a track.
-    __device__ __forceinline__ void run(int lane, uint32_t t, uint32_t ev, uint32_t evf, uint32_t tin, bool act) {
+    __device__ __forceinline__ void run(int lane, uint32_t t, uint32_t ev, bool no_index, uint32_t tin, bool act) {
         const int j = lane & (HALF - 1);
         Half &L = S.h[lane >> 5];
 
@@ -193,7 +193,7 @@ struct Pair {
         const uint32_t b1 = ld32(B.hit_off, ev * 24u + (uint32_t)(2 * l + zone + 1));
         // the bucket's index, fetched while the bounds are computed
         const BucketIndex *bi = B.bidx + (size_t)(ev * 24u + (uint32_t)(2 * l + zone));
-        const bool indexed = B.bidx != nullptr && !(evf & EV_NO_INDEX);
+        const bool indexed = B.bidx != nullptr && !no_index;
         float ilo = 0.0f, iscale = 0.0f;
         if (indexed) { ilo = bi->lo; iscale = bi->scale; }
         float zlo = 0.0f, zhi = 0.0f, dspread = 0.0f, big = 0.0f;   // the bucket's ranges
