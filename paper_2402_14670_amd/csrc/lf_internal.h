@@ -101,7 +101,7 @@ struct DevBatch {
     uint8_t *found, *nhits;    // [T]
     int32_t *hit_idx;          // [12*T]
     float *a, *b, *c, *y0, *ty, *qop, *Q;  // [T]
-    uint32_t *counter;         // [QUEUE_WORDS] persistent-mode queue heads and exited-wave count, zero between launches
+    uint32_t *counter;         // [QUEUE_WORDS] persistent-mode queue heads and exit counts, zero between launches
     unsigned long long *stats; // [32] work counters (counting launch only)
     uint32_t n_events, n_tracks;
     // batched mode over slots of a resident pool: result slot t (< n_map)
@@ -111,7 +111,8 @@ struct DevBatch {
 };
 
 // Work queues of the persistent mode: QUEUE_SUB per XCD (8 XCDs), heads
-// QUEUE_STRIDE words (256 bytes) apart, then the exited-wave count.
+// QUEUE_STRIDE words (256 bytes) apart, each followed by the count of its
+// exited waves, then the count of queues whose waves have all exited.
 constexpr uint32_t QUEUE_SUB = 16;
 constexpr uint32_t QUEUE_N = 8 * QUEUE_SUB;
 constexpr uint32_t QUEUE_STRIDE = 64;

@@ -1544,46 +1544,78 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(pair
 }
 
 // Persistent: QUEUE_N work queues, QUEUE_SUB per XCD.  XCD x owns a
-// contiguous eighth of the tracks, cut into chunks of `items` tracks; chunk j
-// belongs to the XCD's queue j % QUEUE_SUB, whose k-th claim is chunk
-// k QUEUE_SUB + j % QUEUE_SUB, so the XCD's waves move through its eighth
-// together (its events stay in its L2) while their atomics spread over
+// contiguous eighth of the tracks, cut into chunks of `items` tracks; its last
+// tracks, as many as its waves run at once, are cut into chunks of what one
+// wavefront runs at once, so that the waves end close together and small
+// batches spread over all of them.  Chunk j belongs to the XCD's queue
+// j % QUEUE_SUB, as its (j / QUEUE_SUB)-th, so the XCD's waves move through its
+// eighth together (its events stay in its L2) while their atomics spread over
 // QUEUE_SUB words: device-scope atomics on one word are applied one after
-// another, and one word per XCD held one-track claims to ~8 per us.  A wave
-// claims its next chunk before it runs the current one, so the claim's round
-// trip overlaps the track's first loads.  A wave whose queue is drained reads
-// every head in one vector load (two words per lane), moves to a queue with
-// chunks left -- its own XCD's first -- and exits once all are drained.
-// Heads sit QUEUE_STRIDE words apart; word QUEUE_STRIDE QUEUE_N counts exited
-// waves, and the last wave out puts every word back to zero, so the next
-// launch on the batch starts clean without a reset kernel (or a memset node
-// in a captured graph).
+// another, and one word per XCD held one-track claims to ~8 per us.  A queue's
+// first chunks go to the waves whose home it is, one each, without a claim; the
+// head counts those claimed after them.  A wave claims its next chunk before it
+// runs the current one, so the claim's round trip overlaps the track's first
+// loads.  A wave whose queue is drained reads every head in one vector load (two
+// words per lane), moves to a queue with chunks left -- its own XCD's first --
+// and exits once all are drained.
+// The waves count themselves out, those of a home queue on the second word of
+// its line, then the queues on the word past them all, and the last one puts
+// every word back to zero, so the next launch on the batch starts clean without
+// a reset kernel (or a memset node in a captured graph).  Each claim has
+// returned its value, so it is performed before the count is, and no
+// device-scope fence is needed: that one wrote back the XCD's L2, once per wave.
+// 180,000 tracks 329 us with the fence and one word for the count, 257 without
+// the fence, 243 with the count in two stages; 2,000 tracks 56, 43 and 31.5, and
+// 18 with the small chunks and the first ones unclaimed.
 static_assert(QUEUE_N == 2 * WAVE, "the drained-queue scan reads two heads per lane");
 static_assert(QUEUE_N == NXCD * QUEUE_SUB, "QUEUE_SUB queues per XCD");
 
+// The division of a launch's tracks among XCDs and chunks, computed on the host
+// (a division in the kernel is dozens of instructions, and each claim needs some).
+struct Chunks {
+    uint32_t items, lo[NXCD + 1];   // tracks per large chunk; XCD x owns tracks [lo[x], lo[x + 1])
+    uint32_t waves[NXCD];           // its waves,
+    uint32_t big[NXCD], n[NXCD];    // large chunks and chunks
+    uint32_t homes;                 // queues that are some wave's home
+};
+Chunks chunks_of(uint32_t n_tracks, uint32_t items, uint32_t least, uint32_t grid, uint32_t wpb) {
+    Chunks c{};
+    c.items = items < least ? least : items;
+    for (uint32_t x = 0; x <= NXCD; ++x) c.lo[x] = (uint32_t)(((uint64_t)n_tracks * x) / NXCD);
+    for (uint32_t x = 0; x < NXCD; ++x) {
+        c.waves[x] = (grid + NXCD - 1 - x) / NXCD * wpb;
+        const uint32_t n = c.lo[x + 1] - c.lo[x], tail = c.waves[x] * least;
+        c.big[x] = n > tail ? (n - tail) / c.items : 0;
+        c.n[x] = c.big[x] + (n - c.big[x] * c.items + least - 1) / least;
+        c.homes += c.waves[x] < QUEUE_SUB ? c.waves[x] : QUEUE_SUB;
+    }
+    return c;
+}
+
 // MT != 0: two tracks at a time (lists of MT triplets), else one.
 template <int NW, int NS, int WPB, bool H16 = false, int MT = 0>
-__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT == 0 ? 1 : NW == 32 && MT == 16 ? 5 : 4))) void k_persistent(DevBatch B, const KParams *__restrict__ P,
-                                                            uint32_t items) {
+__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT == 0 ? 1 : NW == 32 && MT == 16 ? 5 : 4))) void k_persistent(
+    DevBatch B, const KParams *__restrict__ P, Chunks C) {
     __shared__ std::conditional_t<MT != 0, PairLds<NW, MT != 0 ? MT : 16, H16>, WaveLds<NW, NS>> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     uint32_t *q = B.counter;
-    const uint32_t T = B.n_tracks;
-    auto xlo = [&](uint32_t x) { return (uint32_t)(((uint64_t)T * x) / NXCD); };
-    // chunks of queue i
+    constexpr uint32_t LEAST = MT != 0 ? pair_tracks(NS) : 1;
+    // waves whose home is queue i, and its chunks
+    auto waves_at = [&](uint32_t i) -> uint32_t {
+        return (C.waves[i / QUEUE_SUB] + QUEUE_SUB - 1u - i % QUEUE_SUB) / QUEUE_SUB;
+    };
     auto n_chunks = [&](uint32_t i) -> uint32_t {
-        const uint32_t x = i / QUEUE_SUB, sub = i % QUEUE_SUB;
-        const uint32_t cx = (xlo(x + 1) - xlo(x) + items - 1) / items;
-        return cx > sub ? (cx - sub + QUEUE_SUB - 1) / QUEUE_SUB : 0u;
+        return (C.n[i / QUEUE_SUB] + QUEUE_SUB - 1u - i % QUEUE_SUB) / QUEUE_SUB;
     };
     auto claim = [&](uint32_t i) -> uint32_t {   // lane 0 claims; the value lives in its VGPR
         uint32_t c = 0;
-        if (opaque_lane_id() == 0) c = atomicAdd(&q[QUEUE_STRIDE * i], 1u);
+        if (opaque_lane_id() == 0) c = waves_at(i) + atomicAdd(&q[QUEUE_STRIDE * i], 1u);
         return c;
     };
     // home queue: this block's XCD, waves spread over its QUEUE_SUB queues
-    uint32_t qi = (blockIdx.x % NXCD) * QUEUE_SUB + ((blockIdx.x / NXCD) * WPB + w) % QUEUE_SUB;
-    uint32_t k = __builtin_amdgcn_readfirstlane(claim(qi));
+    const uint32_t at = (blockIdx.x / NXCD) * WPB + w;
+    const uint32_t home = (blockIdx.x % NXCD) * QUEUE_SUB + at % QUEUE_SUB;
+    uint32_t qi = home, k = at / QUEUE_SUB;
     for (;;) {
         if (k >= n_chunks(qi)) {
             // drained: find a queue with chunks left
@@ -1591,7 +1623,8 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT =
             const uint32_t h0 = __hip_atomic_load(&q[QUEUE_STRIDE * lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const uint32_t h1 = __hip_atomic_load(&q[QUEUE_STRIDE * (lane + WAVE)], __ATOMIC_RELAXED,
                                                   __HIP_MEMORY_SCOPE_AGENT);
-            const uint64_t m0 = __ballot(h0 < n_chunks(lane)), m1 = __ballot(h1 < n_chunks(lane + WAVE));
+            const uint64_t m0 = __ballot(waves_at(lane) + h0 < n_chunks(lane));
+            const uint64_t m1 = __ballot(waves_at(lane + WAVE) + h1 < n_chunks(lane + WAVE));
             const uint32_t xb = (qi / QUEUE_SUB) * QUEUE_SUB;   // own XCD's first queue
             const uint64_t own = (xb < WAVE ? m0 >> xb : m1 >> (xb - WAVE)) & ((1ull << QUEUE_SUB) - 1);
             if (own) qi = xb + (uint32_t)__builtin_ctzll(own);
@@ -1602,29 +1635,32 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT =
             continue;
         }
         const uint32_t next = claim(qi);   // in flight while this chunk runs
-        const uint32_t x = qi / QUEUE_SUB, lo = xlo(x), hi = xlo(x + 1);
-        const uint32_t t0 = lo + (k * QUEUE_SUB + qi % QUEUE_SUB) * items;
-        const uint32_t t1 = t0 + items < hi ? t0 + items : hi;
-        for (uint32_t t = t0; t < t1; t += MT != 0 ? pair_tracks(NS) : 1) {
+        const uint32_t x = qi / QUEUE_SUB, j = k * QUEUE_SUB + qi % QUEUE_SUB, big = C.big[x];
+        const uint32_t t0 = C.lo[x] + (j < big ? j * C.items : big * C.items + (j - big) * LEAST);
+        const uint32_t te = t0 + (j < big ? C.items : LEAST), t1 = te < C.lo[x + 1] ? te : C.lo[x + 1];
+        for (uint32_t t = t0; t < t1; t += LEAST) {
             // keep per-track loads inside the loop: hoisting them across tracks
             // costs ~30 VGPRs of loop-carried state and two waves per SIMD
             asm volatile("" ::: "memory");
             if constexpr (MT != 0) {
                 pair_of_tracks<NW, MT, NS, H16>(B, opaque_params(P), lds[w], opaque_lane_id(), t, t1);
             } else {
-                Track<NW, NS, false, H16> tr{B, P, lds[w], 0, {}, 0};
+                Track<NW, NS, false, H16> tr{B, opaque_params(P), lds[w], 0, {}, 0};
                 tr.ln = opaque_lane_id();
                 tr.run(t, B.trk_ev[t], t);
             }
         }
         k = __builtin_amdgcn_readfirstlane(next);
     }
-    const uint32_t waves = gridDim.x * WPB;
     const uint32_t lane = (uint32_t)opaque_lane_id();
     uint32_t last = 0;
     if (lane == 0) {
-        __threadfence();  // this wave's claims are performed before it counts itself out
-        last = atomicAdd(&q[QUEUE_STRIDE * QUEUE_N], 1u) == waves - 1u ? 1u : 0u;
+        uint32_t *out = &q[QUEUE_STRIDE * home + 1];
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (atomicAdd(out, 1u) == waves_at(home) - 1u) {
+            __hip_atomic_store(out, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            last = atomicAdd(&q[QUEUE_STRIDE * QUEUE_N], 1u) == C.homes - 1u ? 1u : 0u;
+        }
     }
     if (__builtin_amdgcn_readfirstlane(last)) {
         __hip_atomic_store(&q[QUEUE_STRIDE * lane], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1870,20 +1906,19 @@ hipError_t launch_nw_wpb(const DevBatch &b, const KParams *P, int mode, const Ex
             hipLaunchKernelGGL((k_plain<NW, NS, WPB, H16>), dim3((nt + WPB - 1) / WPB), block, 0, s, b, P, e);
         }
     } else if (mode == 2) {   // persistent: resident waves, QUEUE_SUB work queues per XCD
+        // no more blocks than an eighth's smallest chunks need, eight times
+        const uint32_t least = pair ? pair_tracks(NS) : 1, eighth = (b.n_tracks + NXCD - 1) / NXCD;
+        const uint32_t need = NXCD * ((eighth + least * WPB - 1) / (least * WPB));
         uint32_t grid = (uint32_t)(cfg.blocks_per_cu * cfg.n_cu);
-        const uint32_t need = (b.n_tracks + WPB - 1) / WPB;
         if (grid > need) grid = need;
         if (grid == 0) grid = 1;
-        if (pair) {
-            const uint32_t items = (uint32_t)cfg.items_per_grab;
-            if (cfg.n_triplets <= 16)
-                hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, 16>), dim3(grid), block, 0, s, b, P, items);
-            else
-                hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, MAX_TRIPLETS>), dim3(grid), block, 0, s, b, P, items);
-            return hipGetLastError();
-        }
-        hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16>), dim3(grid), block, 0, s, b, P,
-                           (uint32_t)cfg.items_per_grab);
+        const Chunks c = chunks_of(b.n_tracks, (uint32_t)cfg.items_per_grab, least, grid, WPB);
+        if (!pair)
+            hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16>), dim3(grid), block, 0, s, b, P, c);
+        else if (cfg.n_triplets <= 16)
+            hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, 16>), dim3(grid), block, 0, s, b, P, c);
+        else
+            hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, MAX_TRIPLETS>), dim3(grid), block, 0, s, b, P, c);
     } else {   // batched: one launch, one wavefront per track (or per mapped slot), XCD-ordered
         if (pair) {
             const uint32_t waves = (n + pair_tracks(NS) - 1) / pair_tracks(NS);

@@ -51,6 +51,26 @@ def test_slot_counts(n_tracks):
             compare(ref, run_gpu(ev, mode, None, exec_cfg), label=f"slots {n_tracks}/{mode}")
 
 
+@pytest.mark.parametrize("waves,items", [(1, 1), (1, 3), (2, 4), (4, 16)])
+def test_persistent_chunks(waves, items):
+    """One block per compute unit: large chunks, then small ones; odd track
+    counts, and launches that find the queue words as the last one left them."""
+    from paper_2402_14670_amd import lf
+    for n in (4199, 4200, 2049, 513):
+        ev = _cut_tracks(lfgen.generate("nominal", n_events=21, seed=58), n)
+        ref = oracle_parallel(ev)
+        say(f"[gpu] persistent chunks n={n} waves={waves} items={items}")
+        ctx = lf.lf_create(W)
+        bid = lf.lf_upload_events(ctx, ev)
+        lf.lf_set_exec(ctx, waves_per_block=waves)
+        lf.lf_set_exec(ctx, items_per_grab=items, blocks_per_cu=1)
+        for launch in range(3):
+            lf.lf_poison_tracks(ctx, bid)
+            lf.lf_find_tracks(ctx, bid, "persistent")
+            compare(ref, lf.lf_copy_tracks(ctx, bid), label=f"chunks {n}/{waves}/{items} launch {launch}")
+        lf.lf_destroy(ctx)
+
+
 @pytest.mark.parametrize("window,triplets", [(1, 1), (8, 16), (31, 17), (32, 32), (33, 12), (64, 16), (64, 32)])
 def test_window_and_list_lengths(window, triplets):
     ev = lfgen.generate("nominal", n_events=21, seed=51)
