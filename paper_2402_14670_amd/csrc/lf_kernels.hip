@@ -1507,21 +1507,22 @@ __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(NS =
 // The two-track body for result slots t0 and t0 + 1 (if < n), or (NS = 2) for
 // slot t0.
 template <int NW, int MT, int NS, bool H16>
-__device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams *__restrict__ P, PairLds<NW, MT, H16> &lds,
+__device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams *__restrict__ P, PairLds<NW, MT> &lds,
                                                int lane, uint32_t t0, uint32_t n) {
     const uint32_t t = NS == 1 ? t0 + (uint32_t)(lane >> 5) : t0;
     const bool act = t < n;
     const uint32_t slot = act ? t : t0;
     const uint32_t tin = B.trk_map ? B.trk_map[slot] : slot;
     const uint32_t ev = B.trk_ev[tin];
-    const uint32_t evf = event_flags(B, ev, lane);
-    const bool no_index = (uint32_t)(__ballot(evf & EV_NO_INDEX) >> (lane & HALF)) != 0;
+    uint32_t evf = event_flags(B, ev, lane);
+    evf |= (uint32_t)__builtin_amdgcn_mov_dpp((int)evf, 0xB1, 0xF, 0xF, true);   // lanes 1 0 3 2 of each quad
+    evf |= (uint32_t)__builtin_amdgcn_mov_dpp((int)evf, 0x4E, 0xF, 0xF, true);   // 2 3 0 1
     if (__ballot(evf & EV_OFF_PLANES) == 0) {
         Pair<NW, MT, true, NS, H16> pr{B, P, lds};
-        pr.run(lane, slot, ev, no_index, tin, act);
+        pr.run(lane, slot, ev, evf, tin, act);
     } else {
         Pair<NW, MT, false, NS, H16> pr{B, P, lds};
-        pr.run(lane, slot, ev, no_index, tin, act);
+        pr.run(lane, slot, ev, evf, tin, act);
     }
 }
 constexpr uint32_t pair_tracks(int NS) { return NS == 1 ? 2 : 1; }   // tracks per wavefront
@@ -1530,11 +1531,11 @@ constexpr uint32_t pair_tracks(int NS) { return NS == 1 ? 2 : 1; }   // tracks p
 // windows: 7 waves per SIMD, 72 registers and a few spilled: 0.205 ms for
 // 200,000 nominal tracks and 0.317 ms for 121,500 in dense events, against
 // 0.211 and 0.335 with 80 registers at 6 waves.  64-hit windows: what LDS allows.
-constexpr int pair_waves(int NW, int MT, bool H16) { return NW == 32 ? (MT == 16 ? 7 : 5) : (MT == 16 && !H16 ? 5 : 4); }
+constexpr int pair_waves(int NW, int MT) { return NW == 32 ? (MT == 16 ? 7 : 5) : (MT == 16 ? 5 : 4); }
 template <int NW, int MT, int WPB, int NS, bool H16>
-__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(pair_waves(NW, MT, H16)))) void k_pair(
+__global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(pair_waves(NW, MT)))) void k_pair(
     DevBatch B, const KParams *__restrict__ P) {
-    __shared__ PairLds<NW, MT, H16> lds[WPB];
+    __shared__ PairLds<NW, MT> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const uint32_t per = gridDim.x / NXCD;
     const uint32_t lb = (blockIdx.x % NXCD) * per + blockIdx.x / NXCD;
@@ -1596,7 +1597,7 @@ Chunks chunks_of(uint32_t n_tracks, uint32_t items, uint32_t least, uint32_t gri
 template <int NW, int NS, int WPB, bool H16 = false, int MT = 0>
 __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT == 0 ? 1 : NW == 32 && MT == 16 ? 5 : 4))) void k_persistent(
     DevBatch B, const KParams *__restrict__ P, Chunks C) {
-    __shared__ std::conditional_t<MT != 0, PairLds<NW, MT != 0 ? MT : 16, H16>, WaveLds<NW, NS>> lds[WPB];
+    __shared__ std::conditional_t<MT != 0, PairLds<NW, MT != 0 ? MT : 16>, WaveLds<NW, NS>> lds[WPB];
     const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     uint32_t *q = B.counter;
     constexpr uint32_t LEAST = MT != 0 ? pair_tracks(NS) : 1;

@@ -36,12 +36,9 @@
 // the pairs written into a queue item by item); 100,000 VELO-only 0.444 ->
 // 0.303; 160,000 nominal seeded in binary16 0.352 -> 0.187; 4,800 nominal 0.0204 -> 0.0155.
 
-// One track's LDS: the x of its window hits (row l: layer l, NW slots, +inf
-// past the window's end, so that a sorted search needs no length), per layer
-// (u, g(u), dxdy y) and the lists of seeding and candidates.
-// H16 (binary16 seeding): per track and seed set, coordinates relative to the
+// Binary16 seeding: per track and seed set, coordinates relative to the
 // window centres c and the constants rounded once from binary32, as in
-// Track::run; e: what the bracket of the third layer needs in binary32.
+// Track::run, and what the bracket of the third layer needs in binary32.
 struct alignas(16) SeedSet16 {
     float c[3];        // window centres of the set's layers
     uint32_t on;       // each outer window's hits share one z (else binary32)
@@ -50,15 +47,12 @@ struct alignas(16) SeedSet16 {
     _Float16 hE0, hC02, hRZ, hL0, hA, hKK, hB, pad;
     uint32_t pad2[2];
 };
-template <bool H16>
-struct Seeds16 {};
-template <>
-struct Seeds16<true> {
-    SeedSet16 h16[2];
-};
 
-template <int NW, int MT, bool H16 = false>
-struct alignas(16) HalfLds : Seeds16<H16> {
+// One track's LDS: the x of its window hits (row l: layer l, NW slots, +inf
+// past the window's end, so that a sorted search needs no length), per layer
+// (u, g(u), dxdy y) and the lists of seeding and candidates.
+template <int NW, int MT>
+struct alignas(16) HalfLds {
     static constexpr int RS = NW + 1;
     uint64_t tk[MT];                 // top-n keys, sorted; ~0 past the list
     int2 win[NL];                    // first hit (event-local) and length of each window
@@ -68,8 +62,11 @@ struct alignas(16) HalfLds : Seeds16<H16> {
     float4 lay[NL];                  // u, g(u), dxdy * y_ext (0 on x layers), h; off the planes y_ext, slack
     union {
         struct {
-            uint64_t nk[HALF];       // this pass's accepted keys, ~0 past them
-            uint32_t mark[HALF];     // where the items' pairs begin in a pass
+            union {
+                uint32_t mark[HALF]; // where the items' pairs begin in a pass
+                uint64_t nk[HALF];   // its accepted keys, ~0 past them
+            };
+            SeedSet16 h16[2];        // (binary16 seeding)
         };
         struct {
             float ca[MT], cb[MT], cc[MT];    // triplet x(z) models
@@ -83,9 +80,9 @@ struct alignas(16) HalfLds : Seeds16<H16> {
     float2 zr[2];                    // z range of each seed set's third bucket (hits off the planes)
 };
 
-template <int NW, int MT, bool H16 = false>
+template <int NW, int MT>
 struct PairLds {
-    HalfLds<NW, MT, H16> h[2];
+    HalfLds<NW, MT> h[2];
     float4 set[2][3];                // KParams::set_tab
     double2 rset[2][2];              // KParams::r_set
 };
@@ -161,10 +158,10 @@ __device__ __forceinline__ uint32_t row_closest_near(uint32_t row, uint32_t end,
 template <int NW, int MT, bool PL, int NS, bool H16 = false>
 struct Pair {
     static_assert(NS == 1 || !H16, "binary16 seeding has one window per layer");
-    using Half = HalfLds<NW, MT, H16>;
+    using Half = HalfLds<NW, MT>;
     const DevBatch &B;
     const KParams *__restrict__ P;
-    PairLds<NW, MT, H16> &S;
+    PairLds<NW, MT> &S;
     uint32_t ebase = 0;   // the event's first hit
 
     static constexpr int RS = Half::RS;
@@ -177,7 +174,7 @@ struct Pair {
 
     // Track tin of the batch (input state) in event ev, result slot t; all
     // uniform in each half (NS = 2: in the wave); act: the half has a track.
-    __device__ __forceinline__ void run(int lane, uint32_t t, uint32_t ev, bool no_index, uint32_t tin, bool act) {
+    __device__ __forceinline__ void run(int lane, uint32_t t, uint32_t ev, uint32_t evf, uint32_t tin, bool act) {
         const int j = lane & (HALF - 1);
         Half &L = S.h[lane >> 5];
 
@@ -193,7 +190,7 @@ struct Pair {
         const uint32_t b1 = ld32(B.hit_off, ev * 24u + (uint32_t)(2 * l + zone + 1));
         // the bucket's index, fetched while the bounds are computed
         const BucketIndex *bi = B.bidx + (size_t)(ev * 24u + (uint32_t)(2 * l + zone));
-        const bool indexed = B.bidx != nullptr && !no_index;
+        const bool indexed = B.bidx != nullptr && !(evf & EV_NO_INDEX);
         float ilo = 0.0f, iscale = 0.0f;
         if (indexed) { ilo = bi->lo; iscale = bi->scale; }
         float zlo = 0.0f, zhi = 0.0f, dspread = 0.0f, big = 0.0f;   // the bucket's ranges
@@ -470,6 +467,7 @@ struct Pair {
                 if (cnt[1] > 0 && a1 < HALF && a1 + cnt[1] > 0) L.mark[a1 > 0 ? a1 : 0] = (uint32_t)(HALF + j);
                 wave_sync();
                 uint32_t m = L.mark[j];
+                wave_sync();
                 m = umax(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x111, 0xF, 0xF, true));
                 m = umax(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x112, 0xF, 0xF, true));
                 m = umax(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x114, 0xF, 0xF, true));
