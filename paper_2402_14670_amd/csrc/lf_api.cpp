@@ -158,7 +158,7 @@ struct lf_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     void *fixed = nullptr;             // this device's fixed scratch (lf_find_tracks_noalloc)
-    lfk::ExecCfg exec{2, 4, 0, 0, false, 0};
+    lfk::ExecCfg exec{1, 4, 0, 0, false, 0};
     std::map<uint64_t, Batch> batches;
     uint64_t next_id = 1;
     std::string err;
