@@ -315,8 +315,9 @@ lfk::KParams to_kparams(const lf_geometry &g, const lf_params &p) {
     return k;
 }
 
-// Host validation of a batch (see lf_batch in lf.h).
-int validate(const lf_batch *b, std::string &why) {
+// Host validation of a batch (see lf_batch in lf.h): first its offsets and
+// pointers, then (validate_values) what the arrays hold.
+int validate_shape(const lf_batch *b, std::string &why) {
     const uint32_t E = b->n_events;
     if (!b->hit_off || !b->trk_off) { why = "batch: NULL offset array"; return 0; }
     if (b->hit_off[0] != 0 || b->trk_off[0] != 0) { why = "batch: offsets must start at 0"; return 0; }
@@ -330,6 +331,12 @@ int validate(const lf_batch *b, std::string &why) {
     if (H >= (1ull << 30) || T >= (1ull << 26)) { why = "batch: 2^30 or more hits, or 2^26 or more tracks"; return 0; }
     if (H && (!b->hit_x || !b->hit_z || !b->hit_dxdy)) { why = "batch: NULL hit array"; return 0; }
     if (T && (!b->trk_x || !b->trk_y || !b->trk_tx || !b->trk_ty || !b->trk_qop)) { why = "batch: NULL track array"; return 0; }
+    return 1;
+}
+
+int validate_values(const lf_batch *b, std::string &why) {
+    const size_t nb = (size_t)b->n_events * 24;
+    const uint64_t H = b->hit_off[nb], T = b->trk_off[b->n_events];
     // the scans below run over slices on several host threads; each reports
     // the first failure a serial scan would.  Hits and buckets in one pass
     // over slices of buckets holding about equal numbers of hits: the first
@@ -387,6 +394,8 @@ int validate(const lf_batch *b, std::string &why) {
     }
     return 1;
 }
+
+int validate(const lf_batch *b, std::string &why) { return validate_shape(b, why) && validate_values(b, why); }
 
 // Device layout of a batch: one allocation, every array 256-byte aligned.
 struct Layout {
@@ -571,12 +580,25 @@ int lf_upload_events(lf_ctx *c, const lf_batch *b, void *hip_stream, uint64_t *b
     if (!c) return LF_ERR_INVALID;
     if (!b || !batch_id) return fail(c, LF_ERR_INVALID, "lf_upload_events: NULL argument");
     std::string why;
-    if (!validate(b, why)) return fail(c, LF_ERR_INVALID, "lf_upload_events: " + why);
+    // The offsets and pointers are checked first, the values while the host link
+    // carries them (a batch of 26 MB: 835 -> 688 us); an error of the values still
+    // comes before those of the steps in between.
+    auto values = [&]() -> int {   // LF_OK, or the error, recorded
+        try {
+            if (validate_values(b, why)) return LF_OK;
+        } catch (...) {
+            return fail(c, LF_ERR_NOMEM, "lf_upload_events: out of host memory");
+        }
+        return fail(c, LF_ERR_INVALID, "lf_upload_events: " + why);
+    };
+    if (!validate_shape(b, why)) return fail(c, LF_ERR_INVALID, "lf_upload_events: " + why);
     const uint32_t E = b->n_events, H = b->hit_off[(size_t)E * 24], T = b->trk_off[E];
     const Layout L = layout(E, H, T);
-    if (c->budget && c->used + L.total > c->budget)
+    if (c->budget && c->used + L.total > c->budget) {
+        if (const int bad = values()) return bad;
         return fail(c, LF_ERR_TOO_LARGE, "lf_upload_events: batch needs " + std::to_string(L.total) +
                                              " device bytes, " + std::to_string(c->budget - c->used) + " left");
+    }
     Batch bt;
     bt.n_events = E; bt.n_tracks = T; bt.n_hits = H;
     bt.out_off = L.found;
@@ -584,10 +606,14 @@ int lf_upload_events(lf_ctx *c, const lf_batch *b, void *hip_stream, uint64_t *b
     try {
         bt.trk_off.assign(b->trk_off, b->trk_off + E + 1);
     } catch (...) {
+        if (const int bad = values()) return bad;
         return fail(c, LF_ERR_NOMEM, "lf_upload_events: out of host memory");
     }
     hipError_t e = take_block(c, L.total, &bt.dmem, &bt.bytes);
-    if (e != hipSuccess) return fail(c, LF_ERR_NOMEM, std::string("lf_upload_events: hipMalloc: ") + hipGetErrorString(e));
+    if (e != hipSuccess) {
+        if (const int bad = values()) return bad;
+        return fail(c, LF_ERR_NOMEM, std::string("lf_upload_events: hipMalloc: ") + hipGetErrorString(e));
+    }
     // the bucket indexes only shorten searches: a context with a device budget
     // goes without, so that its memory is what the budget counts
     if (!c->budget && E) bt.idx = take_idx(c, (size_t)E * 24 * sizeof(lfk::BucketIndex), &bt.idx_bytes);
@@ -649,6 +675,11 @@ int lf_upload_events(lf_ctx *c, const lf_batch *b, void *hip_stream, uint64_t *b
             if (e != hipSuccess) break;
         }
     }
+    if (e == hipSuccess)
+        if (const int bad = values()) {
+            drop_block(c, bt);   // (waits for the copies)
+            return bad;
+        }
     if (e == hipSuccess) e = hipMemsetAsync(d.counter, 0, 4 * (size_t)lfk::QUEUE_WORDS, s);
     if (e == hipSuccess) e = lfk::launch_event_index(d, c->d_params, reinterpret_cast<uint8_t *>(base + L.uni), s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

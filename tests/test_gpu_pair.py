@@ -290,3 +290,23 @@ def test_served_batches_of_mapped_slots():
             assert np.array_equal(dig, ref[req]) and st["result_mismatches"] == 0
     finally:
         lf.lf_destroy(ctx)
+
+
+@pytest.mark.parametrize("budget", [0, 1 << 20, 1 << 30])
+def test_invalid_values_refused_while_the_batch_is_sent(budget):
+    """A bad value is reported whatever else is wrong with the batch (here: its
+    size), and the context goes on."""
+    from paper_2402_14670_amd import lf
+    ev = lfgen.generate("nominal", n_events=21, seed=59)
+    small = lfgen.generate("single", n_events=2, seed=60)
+    ctx = lf.lf_create(W, None, budget)
+    for k, i in (("hit_x", ev.n_hits - 1), ("hit_dxdy", 0), ("trk_tx", ev.n_tracks - 1)):
+        a = getattr(ev, k).copy()
+        a[i] = np.nan
+        with pytest.raises(lf.LFError) as e:
+            lf.lf_upload_events(ctx, lfgen.Events(**{**ev.__dict__, k: a}))
+        assert e.value.code == lf.LF_ERR_INVALID and "non-finite" in str(e.value)
+    bid = lf.lf_upload_events(ctx, small)
+    lf.lf_find_tracks(ctx, bid)
+    compare(oracle_parallel(small), lf.lf_fetch_tracks(ctx, bid, small.n_tracks), label="after refusals")
+    lf.lf_destroy(ctx)
