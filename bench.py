@@ -70,16 +70,16 @@ BYTES_PER_TRACK_OUT = 78
 # HBM traffic of the batched kernel from rocprofv3 FETCH_SIZE + WRITE_SIZE
 # (per launch, scaled by the counters' reading of a known-size copy), valid
 # only for the kernel source and the workload it was measured on.
-TRAFFIC = {"kernel_sha256": "985bb2886f02f49228c45613d199e605f3c3a98cd426572fa0fcbc2bdcc8e45b",
-           "workload": "nominal", "events": 0, "bytes_per_launch": 51952280}
+TRAFFIC = {"kernel_sha256": "1b323ef2d669586c280a7ac1a6901ef8a8ebeb0106072d89c12ee1e8847ad24f",
+           "workload": "nominal", "events": 0, "bytes_per_launch": 54127104}
 WORKLOADS = {
     "nominal": "nominal: 1000 events x 200 input tracks, ~5.4k SciFi hits/event, toy kick field",
     "uneven": "uneven: 20000 events, Poisson(7.6) x 50 particles, 0-13k hits and 0-600 tracks/event",
     "stress": "stress: 5000 events x 486 input tracks (30% fake), ~41.5k hits/event, p 1.5-10 GeV",
     "single": "single: 1 event, 40 particles, p 5-50 GeV",
 }
-KERNEL = "k_grid"   # the batched mode's kernel (one wavefront per input track)
-KERNEL_SRC = os.path.join(ROOT, "paper_2402_14670_amd", "csrc", "lf_kernels.hip")
+KERNEL = "k_pair"   # the batched mode's kernel (two input tracks per wavefront)
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2402_14670_amd", "csrc", f) for f in ("lf_kernels.hip", "lf_pair.h")]
 
 
 def parse():
@@ -619,7 +619,7 @@ def main():
     ops_ex = sum(OPS_PER_UNIT[k] * work[k] for k in OPS_PER_UNIT)
     achieved_ex = ops_ex / (ms * 1e-3) / 1e12
     import hashlib
-    sha = hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()
+    sha = hashlib.sha256(b"".join(open(p, "rb").read() for p in KERNEL_SRCS)).hexdigest()
     traffic = (TRAFFIC["bytes_per_launch"] if (TRAFFIC["kernel_sha256"], TRAFFIC["workload"], TRAFFIC["events"]) ==
                (sha, args.workload, args.events) else None)
     nbytes = algorithmic_bytes(ev)

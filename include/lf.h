@@ -250,7 +250,7 @@ int lf_check_batch(const lf_batch *batch);
  * device.  The batch's device block is the one the context kept from the
  * last batch it freed when that fits (at least the size needed and at most
  * twice it), else a new allocation.  Without a device budget the
- * batch also has a search index (176 bytes per hit bucket, in an allocation of
+ * batch also has a search index (160 bytes per hit bucket, in an allocation of
  * its own that is kept and reused in the same way and not counted in
  * device_bytes).  Errors: LF_ERR_INVALID (malformed batch; nothing is copied),
  * LF_ERR_TOO_LARGE (over budget), LF_ERR_NOMEM, LF_ERR_DEVICE. */
@@ -280,7 +280,7 @@ int lf_find_tracks(lf_ctx *ctx, uint64_t batch_id, int mode, void *hip_stream);
  * lf_upload_events + lf_find_tracks on the same batch.  Enqueues kernels on
  * hip_stream and returns without waiting.
  * Scratch: one fixed device array per GPU, part of the library's code
- * object (50 MiB, held until the process ends): the persistent queue words
+ * object (47 MiB, held until the process ends): the persistent queue words
  * (cleared by a kernel at every call of that mode), one byte per event, one
  * word per track and, for batches of up to 8,192 events, the search index of
  * each hit bucket (larger batches are searched without).  Limits: at most 2^20 events and 2^22 tracks per call

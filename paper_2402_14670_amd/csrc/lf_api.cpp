@@ -158,6 +158,8 @@ struct lf_ctx {
     int device = 0;
     hipStream_t stream = nullptr;
     void *fixed = nullptr;             // this device's fixed scratch (lf_find_tracks_noalloc)
+    // (one wavefront per block: with two, each one's LDS waits for the other's
+    // end; 100,000 tracks with 64-hit windows 162 us against 174)
     lfk::ExecCfg exec{1, 4, 0, 0, false, 0};
     std::map<uint64_t, Batch> batches;
     uint64_t next_id = 1;

@@ -1528,9 +1528,10 @@ __device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams 
 constexpr uint32_t pair_tracks(int NS) { return NS == 1 ? 2 : 1; }   // tracks per wavefront
 
 // Batched mode, two tracks per wavefront (or one track's two sides).  32-hit
-// windows: 7 waves per SIMD, 72 registers and a few spilled: 0.205 ms for
-// 200,000 nominal tracks and 0.317 ms for 121,500 in dense events, against
-// 0.211 and 0.335 with 80 registers at 6 waves.  64-hit windows: what LDS allows.
+// windows: 7 waves per SIMD, 72 registers and a few spilled: 200,000 nominal
+// tracks 0.207 ms, 121,500 in dense events 0.277, against 0.279 and 0.306 with
+// 64 registers at 8 waves, and 3% and 6% more with 80 at 6.  64-hit windows:
+// what LDS allows.
 constexpr int pair_waves(int NW, int MT) { return NW == 32 ? (MT == 16 ? 7 : 5) : (MT == 16 ? 5 : 4); }
 template <int NW, int MT, int WPB, int NS, bool H16>
 __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(pair_waves(NW, MT)))) void k_pair(
@@ -1593,7 +1594,8 @@ Chunks chunks_of(uint32_t n_tracks, uint32_t items, uint32_t least, uint32_t gri
     return c;
 }
 
-// MT != 0: two tracks at a time (lists of MT triplets), else one.
+// MT != 0: two tracks at a time (lists of MT triplets), else one.  (5 waves per
+// SIMD: 180,000 nominal tracks 0.243 ms, at 6 waves 0.273.)
 template <int NW, int NS, int WPB, bool H16 = false, int MT = 0>
 __global__ __launch_bounds__(WPB * WAVE) __attribute__((amdgpu_waves_per_eu(MT == 0 ? 1 : NW == 32 && MT == 16 ? 5 : 4))) void k_persistent(
     DevBatch B, const KParams *__restrict__ P, Chunks C) {
