@@ -206,13 +206,27 @@ __device__ __forceinline__ float field_c_lane(const KParams *__restrict__ P, flo
     return acc;
 }
 
-// a / b for a divisor whose binary64 reciprocal r = 1 / b is at hand: the
-// correctly rounded binary32 quotient.  a r is within 2^-52 of a / b, relative,
-// and a quotient of two 24-bit numbers is never nearer than 2^-49 to a point
-// halfway between two binary32 numbers, so both round alike (zeros, infinities
-// and NaN as in the division; only in a subnormal quotient can the last bit,
-// 2^-149, differ).  Three instructions of 4.3 cycles against eleven, 38 cycles.
-__device__ __forceinline__ float div_by(float a, double r) { return (float)((double)a * r); }
+// a / b for a divisor whose reciprocal r = recip(b) is at hand: the correctly
+// rounded binary32 quotient.  Four instructions against the eleven of a division.
+// a r is at most two binary64 steps above a / b where that is a binary32 number
+// or halfway between two (25 significant bits at most, so the last two bits of
+// its binary64 form are zero), never below: clearing the last two bits gives it
+// back, and a tie rounds to even as in the division, subnormal quotients
+// included.  Any other quotient of two 24-bit numbers is at least 2^-49 away,
+// relative, from a point halfway between two binary32 numbers, and reciprocal,
+// product and clearing move it by less than 2^-50.  Zeros, infinities and NaN are
+// those of the division.
+__device__ __forceinline__ double as_double(uint64_t u) { return __builtin_bit_cast(double, u); }
+__device__ __forceinline__ uint64_t as_bits(double v) { return __builtin_bit_cast(uint64_t, v); }
+__device__ __forceinline__ float div_by(float a, double r) {
+    return (float)as_double(as_bits((double)a * r) & ~3ull);
+}
+
+// 1 / b in binary64, rounded away from zero.
+__host__ __device__ inline double recip(float b) {
+    const double r = 1.0 / (double)b;
+    return fma(r, (double)b, -1.0) < 0.0 ? __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, r) + 1) : r;
+}
 
 // Flags of event ev: of the part that the lane's place in its quad names, so the
 // event's are those of any four lanes.
@@ -1885,10 +1899,10 @@ __global__ void __launch_bounds__(256) k_fit_table(const KParams *__restrict__ P
     r.D = r.YS0 * YS11 - YS1 * YS1;
     r.C = P->C_nhits[n - 9 < 0 ? 0 : (n - 9 > 3 ? 3 : n - 9)];
     r.unused = 0.0f;
-    r.r_det = 1.0 / (double)(fabsf(r.det) > 0.0f ? r.det : 1.0f);
-    r.r_D = 1.0 / (double)(fabsf(r.D) > 0.0f ? r.D : 1.0f);
-    r.r_nx = 1.0 / (double)(n - 3);
-    r.r_ny = 1.0 / (double)(n_uv - 2);
+    r.r_det = recip(fabsf(r.det) > 0.0f ? r.det : 1.0f);
+    r.r_D = recip(fabsf(r.D) > 0.0f ? r.D : 1.0f);
+    r.r_nx = recip((float)(n - 3));
+    r.r_ny = recip((float)(n_uv - 2));
     rows[mask] = r;
 }
 
@@ -2111,10 +2125,10 @@ void plane_constants(KParams &k) {
         const float sv = k.lay_u[l] * INV1024;
         k.lay_h[l] = sv * sv * (1.0f + k.dRatio * k.lay_u[l]);
     }
-    for (int l = 0; l < NL; ++l) k.r_dxdy[l] = 1.0 / (double)k.dxdy[l];
-    k.r_Tx = 1.0 / (double)k.T_x;
-    k.r_Ty = 1.0 / (double)k.T_y;
-    k.r_kick = 1.0 / (double)k.kick;
+    for (int l = 0; l < NL; ++l) k.r_dxdy[l] = recip(k.dxdy[l]);
+    k.r_Tx = recip(k.T_x);
+    k.r_Ty = recip(k.T_y);
+    k.r_kick = recip(k.kick);
     k.pair_ok = 1;
     for (int s = 0; s < 2; ++s) {
         const int l0 = s ? 3 : 0, l1 = s ? 7 : 4, l2 = s ? 11 : 8;
@@ -2124,10 +2138,10 @@ void plane_constants(KParams &k) {
         const float tab[12] = {k.lay_u[l0], k.lay_g[l0], du01, du12, G01, G12 - G01,
                                k.z[l0], k.z[l1], dz, 1.0f / lev, s ? k.K_last : k.K_first, lev};
         for (int i = 0; i < 12; ++i) k.set_tab[s][i] = tab[i];
-        k.r_set[s][0] = 1.0 / (double)dz;
-        k.r_set[s][1] = 1.0 / (double)du01;
-        k.r_set[s][2] = 1.0 / (double)du12;
-        k.r_set[s][3] = 1.0 / (double)tab[5];
+        k.r_set[s][0] = recip(dz);
+        k.r_set[s][1] = recip(du01);
+        k.r_set[s][2] = recip(du12);
+        k.r_set[s][3] = recip(tab[5]);
         if (!((lev > 1.0f || lev < -1.0f) && dz > 1.0f)) k.pair_ok = 0;
     }
 }
