@@ -1861,7 +1861,8 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
     } else if (threadIdx.x == 0) {
         uni[e] = (uint8_t)flags;
     }
-    const uint32_t t1 = B.trk_off[e + 1];
+    // (a caller of the non-allocating entry may pass fewer tracks than trk_off counts)
+    const uint32_t te = B.trk_off[e + 1], t1 = te < B.n_tracks ? te : B.n_tracks;
     for (uint32_t t = B.trk_off[e] + part * (NWV * WAVE) + threadIdx.x; t < t1; t += PARTS * NWV * WAVE) trk_ev[t] = e;
 }
 

@@ -34,3 +34,46 @@ def test_subnormal_quotients(odd, exp):
         compare(ref, got, label=mode)
         for k in PARAM_KEYS:
             assert np.array_equal(ref[k].view(np.uint32), got[k].view(np.uint32)), (mode, k)
+
+
+def _device(ev):
+    """The batch's arrays and result slots in device memory."""
+    import torch
+    from paper_2402_14670_amd import lf
+    src = {k: torch.from_numpy(getattr(ev, k).view(np.int32) if k.endswith("off") else getattr(ev, k)).cuda()
+           for k in lf._IN_FIELDS}
+    out = {k: torch.zeros((ev.n_tracks, 12) if k == "hit_idx" else ev.n_tracks, device="cuda",
+                          dtype=torch.uint8 if k in ("found", "n_hits") else
+                          torch.int32 if k == "hit_idx" else torch.float32) for k in lf._OUT_FIELDS}
+    return src, out
+
+
+def _noalloc(ctx, src, out, mode):
+    import torch
+    from paper_2402_14670_amd import lf
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    lf.lf_find_tracks_noalloc(ctx, src, out, mode, s.cuda_stream)
+    s.synchronize()
+    return {k: v.cpu().numpy() for k, v in out.items()}
+
+
+@pytest.mark.parametrize("mode", ["batched", "persistent"])
+def test_noalloc_with_fewer_tracks_than_the_offsets(mode):
+    """Offsets that count more tracks than the call does (and than the fixed
+    scratch holds): the call's own tracks are found, nothing past them is
+    written."""
+    import torch
+    from paper_2402_14670_amd import lf
+    ev = lfgen.generate("nominal", n_events=3, seed=91)
+    ref = oracle_parallel(ev)
+    src, out = _device(ev)
+    off = ev.trk_off.copy()
+    off[-1] = (1 << 22) + 300000
+    src["trk_off"] = torch.from_numpy(off.view(np.int32)).cuda()
+    ctx = lf.lf_create(W)
+    try:
+        say(f"[gpu] noalloc, offsets past the tracks, mode={mode}")
+        compare(ref, _noalloc(ctx, src, out, mode), label=mode)
+    finally:
+        lf.lf_destroy(ctx)
