@@ -253,7 +253,8 @@ int lf_check_batch(const lf_batch *batch);
  * batch also has a search index (160 bytes per hit bucket, in an allocation of
  * its own that is kept and reused in the same way and not counted in
  * device_bytes).  Errors: LF_ERR_INVALID (malformed batch; nothing is copied),
- * LF_ERR_TOO_LARGE (over budget), LF_ERR_NOMEM, LF_ERR_DEVICE. */
+ * LF_ERR_TOO_LARGE (over budget), LF_ERR_NOMEM, LF_ERR_DEVICE (also for
+ * 44,739,242 events or more, whose hit_off would be 4 GiB). */
 int lf_upload_events(lf_ctx *ctx, const lf_batch *batch, void *hip_stream, uint64_t *batch_id);
 
 /* The whole step of Algorithm logic: search windows (Defining the search

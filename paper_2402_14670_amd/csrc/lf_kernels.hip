@@ -1758,11 +1758,11 @@ template <bool IDX>
 __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch B, const KParams *__restrict__ P,
                                                                        uint8_t *__restrict__ uni,
                                                                        BucketIndex *__restrict__ bidx,
-                                                                       uint32_t *__restrict__ trk_ev) {
+                                                                       uint32_t *__restrict__ trk_ev, uint32_t e0) {
     constexpr int NWV = evi_waves(IDX), PARTS = IDX ? EV_PARTS : 1;
     __shared__ BucketIndex rec[IDX ? NWV : 1];
     __shared__ uint32_t fl[NWV];
-    const uint32_t e = blockIdx.x / PARTS, part = blockIdx.x % PARTS;
+    const uint32_t e = e0 + blockIdx.x / PARTS, part = blockIdx.x % PARTS;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = lane_id();
     uint32_t flags = 0;
     for (uint32_t k = part * EV_PART + (uint32_t)w, k1 = IDX ? k + 1 : 2 * NL; k < k1; k += NWV) {
@@ -2089,16 +2089,24 @@ hipError_t launch_track_map(const uint32_t *evs, const uint32_t *toff, uint32_t 
 }
 
 hipError_t launch_event_index(const DevBatch &b, const KParams *P, uint8_t *uni, hipStream_t s) {
-    if (b.n_events == 0) return hipSuccess;
+    // a launch holds fewer than 2^32 threads (1,536 an event), and the track
+    // kernels reach hit_off by 32-bit byte offsets
+    constexpr uint32_t SLICE = 1u << 20;
+    if (b.n_events >= (1ull << 32) / (4 * 2 * NL)) return hipErrorInvalidValue;
     BucketIndex *idx = const_cast<BucketIndex *>(b.bidx);
     uint32_t *trk_ev = const_cast<uint32_t *>(b.trk_ev);
-    if (idx)
-        hipLaunchKernelGGL(k_event_index<true>, dim3(EV_PARTS * b.n_events), dim3(evi_waves(true) * WAVE), 0, s, b, P,
-                           uni, idx, trk_ev);
-    else
-        hipLaunchKernelGGL(k_event_index<false>, dim3(b.n_events), dim3(evi_waves(false) * WAVE), 0, s, b, P, uni, idx,
-                           trk_ev);
-    return hipGetLastError();
+    for (uint32_t e0 = 0; e0 < b.n_events; e0 += SLICE) {
+        const uint32_t n = b.n_events - e0 < SLICE ? b.n_events - e0 : SLICE;
+        if (idx)
+            hipLaunchKernelGGL(k_event_index<true>, dim3(EV_PARTS * n), dim3(evi_waves(true) * WAVE), 0, s, b, P, uni, idx,
+                               trk_ev, e0);
+        else
+            hipLaunchKernelGGL(k_event_index<false>, dim3(n), dim3(evi_waves(false) * WAVE), 0, s, b, P, uni, idx, trk_ev,
+                               e0);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_find(const DevBatch &b, const KParams *P, int n_hits_window, int n_sides, int mode,

@@ -77,3 +77,33 @@ def test_noalloc_with_fewer_tracks_than_the_offsets(mode):
         compare(ref, _noalloc(ctx, src, out, mode), label=mode)
     finally:
         lf.lf_destroy(ctx)
+
+
+@pytest.mark.parametrize("budget", [0, 1 << 33], ids=["indexed", "budget"])
+def test_upload_of_millions_of_events(budget):
+    """2,900,000 events, nearly all empty: more than one launch of the event
+    kernel can hold; the events with hits and tracks stand at the ends of its
+    slices."""
+    from paper_2402_14670_amd import lf
+    E = 2_900_000
+    at = np.array([0, (1 << 20) - 1, 1 << 20, (1 << 21) - 1, 1 << 21, E - 1])
+    some = lfgen.generate("nominal", n_events=len(at), seed=92)
+    ref = oracle_parallel(some)
+    # buckets and tracks per event of the long batch, from those of the short one
+    nh, nt = np.zeros((E, 24), np.int64), np.zeros(E, np.int64)
+    nh[at] = np.diff(some.hit_off.astype(np.int64)).reshape(-1, 24)
+    nt[at] = np.diff(some.trk_off.astype(np.int64))
+    ev = lfgen.Events(**{**some.__dict__, "n_events": E,
+                         "hit_off": np.concatenate([[0], np.cumsum(nh.ravel())]).astype(np.uint32),
+                         "trk_off": np.concatenate([[0], np.cumsum(nt)]).astype(np.uint32)})
+    assert ev.n_events == E and ev.n_tracks == some.n_tracks
+    ctx = lf.lf_create(W, None, budget)
+    try:
+        say(f"[gpu] upload of {E} events budget={budget}")
+        bid = lf.lf_upload_events(ctx, ev)
+        for mode in ("batched", "persistent"):
+            lf.lf_poison_tracks(ctx, bid)
+            lf.lf_find_tracks(ctx, bid, mode)
+            compare(ref, lf.lf_copy_tracks(ctx, bid), label=mode)
+    finally:
+        lf.lf_destroy(ctx)
