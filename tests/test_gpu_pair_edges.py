@@ -107,3 +107,52 @@ def test_upload_of_millions_of_events(budget):
             compare(ref, lf.lf_copy_tracks(ctx, bid), label=mode)
     finally:
         lf.lf_destroy(ctx)
+
+
+def _with_long_buckets(ev, lengths, odd):
+    """The first event's listed buckets made as long as given by random hits;
+    odd: the hit of each of them (first, middle, last or none) that is off the
+    bucket's z and slope."""
+    rng = np.random.default_rng(93)
+    arr = {k: getattr(ev, k) for k in ("hit_x", "hit_z", "hit_dxdy", "hit_pid")}
+    off = ev.hit_off.astype(np.int64)
+    for b, n in lengths.items():
+        f, l = int(off[b]), int(off[b + 1])
+        x = np.sort(np.concatenate([arr["hit_x"][f:l], rng.uniform(-3000, 3000, n - (l - f)).astype(np.float32)]))
+        z, d = np.full(n, arr["hit_z"][f]), np.full(n, arr["hit_dxdy"][f])
+        if odd is not None:
+            i = {"first": 0, "middle": n // 2, "last": n - 1}[odd]
+            z[i] += np.float32(2.0)
+            d[i] += np.float32(0.01)
+        new = dict(hit_x=x, hit_z=z, hit_dxdy=d, hit_pid=np.full(n, -1, np.int32))
+        arr = {k: np.concatenate([v[:f], new[k], v[l:]]) for k, v in arr.items()}
+        off[b + 1:] += n - (l - f)
+    return lfgen.Events(**{**ev.__dict__, **arr, "hit_off": off.astype(np.uint32)})
+
+
+# a block of the event kernel takes six buckets: one, two and six long ones of
+# a block, some of every block, at the edges of a round, of a piece and of the
+# index
+LONG = [{0: 2048}, {5: 2049}, {3: 3072, 4: 2305}, {b: 2100 + 64 * b for b in range(6)},
+        {0: 65535, 7: 65536, 13: 2047, 23: 4097}, {b: 2500 for b in range(24)}]
+
+
+@pytest.mark.parametrize("odd", [None, "first", "middle", "last"])
+@pytest.mark.parametrize("lengths", LONG, ids=lambda v: "_".join(str(n) for n in list(v.values())[:4]))
+def test_long_buckets(lengths, odd):
+    """Buckets that the whole block shares, with and without the index, beside
+    events whose buckets are short."""
+    from paper_2402_14670_amd import lf
+    ev = _with_long_buckets(lfgen.generate("nominal", n_events=3, seed=94), lengths, odd)
+    ref = oracle_parallel(ev)
+    for budget in (0, 1 << 30):
+        ctx = lf.lf_create(W, None, budget)
+        try:
+            say(f"[gpu] long buckets {lengths} odd={odd} budget={budget}")
+            bid = lf.lf_upload_events(ctx, ev)
+            for mode in ("plain", "batched"):
+                lf.lf_poison_tracks(ctx, bid)
+                lf.lf_find_tracks(ctx, bid, mode)
+                compare(ref, lf.lf_copy_tracks(ctx, bid), label=f"{mode} budget={budget}")
+        finally:
+            lf.lf_destroy(ctx)
