@@ -252,7 +252,11 @@ int lf_check_batch(const lf_batch *batch);
  * twice it), else a new allocation.  Without a device budget the
  * batch also has a search index (160 bytes per hit bucket, in an allocation of
  * its own that is kept and reused in the same way and not counted in
- * device_bytes).  Errors: LF_ERR_INVALID (malformed batch; nothing is copied),
+ * device_bytes).  Offsets and pointers are checked before anything else, the
+ * values (finite, q/p != 0, sorted) while the copy to the device runs: a batch
+ * with a bad value is discarded after its copy, once hip_stream has finished it
+ * (work on other streams is not waited for), and its block is kept as a freed
+ * batch's is.  Errors: LF_ERR_INVALID (malformed batch, whatever else is wrong),
  * LF_ERR_TOO_LARGE (over budget), LF_ERR_NOMEM, LF_ERR_DEVICE (also for
  * 44,739,242 events or more, whose hit_off would be 4 GiB). */
 int lf_upload_events(lf_ctx *ctx, const lf_batch *batch, void *hip_stream, uint64_t *batch_id);

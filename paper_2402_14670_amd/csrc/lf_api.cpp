@@ -247,11 +247,9 @@ void *take_idx(lf_ctx *c, size_t need, size_t *got) {
     return p;
 }
 
-// Frees a batch's block and indexes: kept as the spare (the previous spare is freed).
-// The device is synchronised first, as a free would be, so that no queued
-// work on any stream still uses the block when an upload reuses it.
-void drop_block(lf_ctx *c, const Batch &b) {
-    (void)hipDeviceSynchronize();
+// Keeps a batch's block and indexes, which no queued work uses any more, as the
+// spare (the previous spare is freed).
+void keep_block(lf_ctx *c, const Batch &b) {
     if (c->spare) (void)hipFree(c->spare);
     c->spare = b.dmem;
     c->spare_bytes = b.bytes;
@@ -259,6 +257,14 @@ void drop_block(lf_ctx *c, const Batch &b) {
     if (c->spare_idx) (void)hipFree(c->spare_idx);
     c->spare_idx = b.idx;
     c->spare_idx_bytes = b.idx_bytes;
+}
+
+// Frees a batch's block and indexes.  The device is synchronised first, as a
+// free would be, so that no queued work on any stream still uses the block when
+// an upload reuses it.
+void drop_block(lf_ctx *c, const Batch &b) {
+    (void)hipDeviceSynchronize();
+    keep_block(c, b);
 }
 
 bool finitef(float v) { return std::isfinite(v); }
@@ -677,11 +683,17 @@ int lf_upload_events(lf_ctx *c, const lf_batch *b, void *hip_stream, uint64_t *b
             if (e != hipSuccess) break;
         }
     }
-    if (e == hipSuccess)
-        if (const int bad = values()) {
-            drop_block(c, bt);   // (waits for the copies)
-            return bad;
+    if (const int bad = values()) {
+        // only this stream's copies have touched the block
+        const hipError_t w = hipStreamSynchronize(s);
+        if (e == hipSuccess && w == hipSuccess) {
+            keep_block(c, bt);
+        } else {
+            (void)hipFree(bt.dmem);
+            if (bt.idx) (void)hipFree(bt.idx);
         }
+        return bad;
+    }
     if (e == hipSuccess) e = hipMemsetAsync(d.counter, 0, 4 * (size_t)lfk::QUEUE_WORDS, s);
     if (e == hipSuccess) e = lfk::launch_event_index(d, c->d_params, reinterpret_cast<uint8_t *>(base + L.uni), s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -156,3 +156,32 @@ def test_long_buckets(lengths, odd):
                 compare(ref, lf.lf_copy_tracks(ctx, bid), label=f"{mode} budget={budget}")
         finally:
             lf.lf_destroy(ctx)
+
+
+@pytest.mark.parametrize("budget", [0, 1 << 30])
+def test_refused_upload_waits_for_its_own_stream_only(budget):
+    """A batch with a bad value is refused while another stream still works,
+    and the block that it took serves the next upload."""
+    import torch
+    from paper_2402_14670_amd import lf
+    ev = lfgen.generate("nominal", n_events=5, seed=95)
+    bad = lfgen.Events(**{**ev.__dict__, "trk_tx": ev.trk_tx.copy()})
+    bad.trk_tx[-1] = np.inf
+    ctx = lf.lf_create(W, None, budget)
+    busy, mine, done = torch.cuda.Stream(), torch.cuda.Stream(), torch.cuda.Event()
+    try:
+        lf.lf_release_batch(ctx, lf.lf_upload_events(ctx, ev, mine.cuda_stream))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(busy):
+            torch.cuda._sleep(500_000_000)   # a quarter of a second
+            done.record(busy)
+        with pytest.raises(lf.LFError) as e:
+            lf.lf_upload_events(ctx, bad, mine.cuda_stream)
+        assert not done.query()
+        assert e.value.code == lf.LF_ERR_INVALID and "non-finite track state" in str(e.value)
+        busy.synchronize()
+        bid = lf.lf_upload_events(ctx, ev)
+        lf.lf_find_tracks(ctx, bid)
+        compare(oracle_parallel(ev), lf.lf_fetch_tracks(ctx, bid), label="after a refusal")
+    finally:
+        lf.lf_destroy(ctx)
