@@ -203,6 +203,20 @@ char *staging(lf_ctx *c, size_t bytes) {
     return c->pin;
 }
 
+// Device memory.  The kept bucket indexes only save an allocation: they are given
+// back before a request fails for want of memory.
+hipError_t device_alloc(lf_ctx *c, size_t need, void **p) {
+    hipError_t e = hipMalloc(p, need);
+    if (e != hipSuccess && c->spare_idx) {
+        (void)hipGetLastError();
+        (void)hipFree(c->spare_idx);
+        c->spare_idx = nullptr;
+        c->spare_idx_bytes = 0;
+        e = hipMalloc(p, need);
+    }
+    return e;
+}
+
 // A batch's device block, at least `need` bytes: the spare block when it fits
 // (and is not more than twice the need), else a new allocation, the spare
 // being freed first when it does not fit or when holding it would take the
@@ -222,7 +236,7 @@ hipError_t take_block(lf_ctx *c, size_t need, void **p, size_t *got) {
         c->spare_bytes = 0;
     }
     *got = need;
-    return hipMalloc(p, need);
+    return device_alloc(c, need, p);
 }
 
 // Memory for a batch's bucket indexes, kept and reused as the blocks are;
@@ -442,6 +456,7 @@ int ctx_nhits_window(const lf_ctx *c) { return c->params.n_hits_window; }
 int ctx_sides(const lf_ctx *c) { return c->params.velo_only ? 2 : (c->params.seed_fp16 ? 3 : 1); }
 const lfk::ExecCfg &ctx_exec(const lf_ctx *c) { return c->exec; }
 int check_batch(const lf_batch *b, std::string &why) { return validate(b, why); }
+hipError_t ctx_alloc(lf_ctx *c, size_t need, void **p) { return device_alloc(c, need, p); }
 }  // namespace lfapi
 
 extern "C" {

@@ -43,6 +43,7 @@ const lfk::KParams *ctx_dparams(const lf_ctx *c);
 int ctx_nhits_window(const lf_ctx *c);
 int ctx_sides(const lf_ctx *c);
 const lfk::ExecCfg &ctx_exec(const lf_ctx *c);
+hipError_t ctx_alloc(lf_ctx *c, size_t need, void **p);
 int check_batch(const lf_batch *b, std::string &why);
 }  // namespace lfapi
 
@@ -235,7 +236,7 @@ extern "C" int lf_serve_run(lf_ctx *ctx, const lf_batch *pool_b, uint32_t n_requ
     // ---- device ring, slots ----
     Ring ring;
     ring.cap = cfg.device_budget_bytes;
-    err = hipMalloc(&ring_mem, ring.cap);
+    err = lfapi::ctx_alloc(ctx, ring.cap, &ring_mem);
     if (err != hipSuccess) {
         cleanup();
         return lfapi::ctx_fail(ctx, LF_ERR_NOMEM, "lf_serve_run: device budget allocation failed");
@@ -296,7 +297,7 @@ extern "C" int lf_serve_run(lf_ctx *ctx, const lf_batch *pool_b, uint32_t n_requ
                      o_tr = put((size_t)PT * 20), o_uni = put(PE), o_idx = o;
         // the bucket indexes, if the memory can be had
         const size_t idx = (size_t)PE * 24 * sizeof(lfk::BucketIndex);
-        err = hipMalloc(reinterpret_cast<void **>(&pool_hbm), o + idx);
+        err = lfapi::ctx_alloc(ctx, o + idx, reinterpret_cast<void **>(&pool_hbm));
         const bool indexed = err == hipSuccess;
         if (!indexed) {
             (void)hipGetLastError();
