@@ -1762,6 +1762,7 @@ __global__ void k_track_map(const uint32_t *__restrict__ evs, const uint32_t *__
 constexpr int EVI_ROUNDS = 4;
 constexpr uint32_t EVI_LONG = 2048;
 constexpr int EVI_PIECE = 16;
+constexpr uint32_t IS_LONG = 8, ANY_LONG = 24;   // beside the EV_* flags: a wave's first, second bucket
 constexpr int evi_waves(bool IDX) { return IDX ? EV_PART : 2 * EV_PART; }
 // Unsigned integers in the order of the floats.
 __device__ __forceinline__ uint32_t ordered(float v) {
@@ -1777,7 +1778,7 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
                                                                        BucketIndex *__restrict__ bidx,
                                                                        uint32_t *__restrict__ trk_ev, uint32_t e0) {
     constexpr int NWV = evi_waves(IDX), PARTS = IDX ? EV_PARTS : 1, NB = 2 * NL / PARTS;
-    struct Long {   // a long bucket: its hits (n = 0: it is not long), the z and dxdy of the first, and the ranges
+    struct Long {   // a long bucket: its hits (n = 0: not long), the z and dxdy of the first, and the ranges
         uint32_t b0, n, z0, d0, zmin, zmax, dmin, dmax;
     };
     __shared__ BucketIndex rec[IDX ? NWV : 1];
@@ -1827,8 +1828,10 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
         const uint32_t z0 = __float_as_uint(zmin), d0 = __float_as_uint(dmin);
         if (n > IDX_MAX_BUCKET) flags |= EV_NO_INDEX;
         const bool is_long = n > EVI_LONG;
-        if (lane == 0)
-            lng[k] = Long{b0, is_long ? n : 0u, z0, d0, ordered(zmin), ordered(zmax), ordered(dmin), ordered(dmax)};
+        if (is_long) {
+            flags |= IS_LONG << (k / NWV);
+            if (lane == 0) lng[k] = Long{b0, n, z0, d0, ordered(zmin), ordered(zmax), ordered(dmin), ordered(dmax)};
+        }
         int before = -1;   // cell of the hit before this round's first
         bool differ = false;
         for (uint32_t i0 = 0; i0 < (is_long ? 0u : n); i0 += EVI_ROUNDS * WAVE) {
@@ -1881,12 +1884,16 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
     if (lane == 0) fl[w] = flags;
     __syncthreads();
 
-    // ---- long buckets ----
-    auto pieces = [](uint32_t hits) { return (hits + EVI_PIECE * WAVE - 1) / (EVI_PIECE * WAVE); };
-    uint32_t total = 0;
+    uint32_t all = 0;
 #pragma unroll
-    for (int k = 0; k < NB; ++k) total += pieces(lng[k].n);
-    if (total) {
+    for (int i = 0; i < NWV; ++i) all |= fl[i];
+    if (all & ANY_LONG) {
+        if (threadIdx.x < NB && !(fl[threadIdx.x % NWV] & (IS_LONG << (threadIdx.x / NWV)))) lng[threadIdx.x].n = 0;
+        __syncthreads();
+        auto pieces = [](uint32_t hits) { return (hits + EVI_PIECE * WAVE - 1) / (EVI_PIECE * WAVE); };
+        uint32_t total = 0;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) total += pieces(lng[k].n);
         if constexpr (IDX) {
             if (n > EVI_LONG && n <= IDX_MAX_BUCKET) {
                 // lane p: the first hit of cell >= p, one of a .. a + m (p = 0: hit 0)
@@ -1952,8 +1959,10 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
                 }
             }
         }
-        if (lane == 0) fl[w] = flags;
+        if (lane == 0) fl[w] = flags;   // (read by all waves before the barrier above)
         __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NWV; ++i) all |= fl[i];
         if constexpr (IDX) {
             if (n > EVI_LONG && lane == 0) {
                 const float dmin = from_ordered(lng[w].dmin), dmax = from_ordered(lng[w].dmax);
@@ -1964,17 +1973,14 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
             }
         }
     }
-    flags = 0;
-#pragma unroll
-    for (int i = 0; i < NWV; ++i) flags |= fl[i];
     if constexpr (IDX) {
         // the record, with the six buckets' flags in the first one's
-        if (lane == 0) rec[w].flags = (uint16_t)flags;
+        if (lane == 0) rec[w].flags = (uint16_t)(all & ~ANY_LONG);
         wave_sync();
         uint32_t *o = reinterpret_cast<uint32_t *>(bidx + ((size_t)e * 2 * NL + part * EV_PART + (uint32_t)w));
         if (lane < (int)sizeof(BucketIndex) / 4) o[lane] = reinterpret_cast<const uint32_t *>(&rec[w])[lane];
     } else if (threadIdx.x == 0) {
-        uni[e] = (uint8_t)flags;
+        uni[e] = (uint8_t)(all & ~ANY_LONG);
     }
     // (a caller of the non-allocating entry may pass fewer tracks than trk_off counts)
     const uint32_t te = B.trk_off[e + 1], t1 = te < B.n_tracks ? te : B.n_tracks;
