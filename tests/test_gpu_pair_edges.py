@@ -185,3 +185,55 @@ def test_refused_upload_waits_for_its_own_stream_only(budget):
         compare(oracle_parallel(ev), lf.lf_fetch_tracks(ctx, bid), label="after a refusal")
     finally:
         lf.lf_destroy(ctx)
+
+
+def _jitter(ev, seed):
+    rng = np.random.default_rng(seed)
+    return lfgen.Events(**{**ev.__dict__, "hit_z": ev.hit_z + rng.uniform(-1.5, 1.5, ev.n_hits).astype(np.float32),
+                           "hit_dxdy": ev.hit_dxdy * (1 + rng.uniform(-0.02, 0.02, ev.n_hits)).astype(np.float32)})
+
+
+@pytest.mark.parametrize("params", [
+    {}, {"n_hits_window": 64, "n_triplets": 32}, {"velo_only": 1}, {"velo_only": 1, "n_hits_window": 32},
+    {"seed_fp16": 1}, {"seed_fp16": 1, "n_hits_window": 64}],
+    ids=["default", "w64", "velo_only", "velo_only_w32", "fp16", "fp16_w64"])
+def test_one_track_kernels(params):
+    """A context with a device budget has no search indexes: the one-track
+    batched and persistent kernels, for every kind of input, on the planes and
+    off them, with each number of wavefronts per block."""
+    from paper_2402_14670_amd import lf
+    base = lfgen.generate("uneven", n_events=14, seed=96)
+    ev = lfgen.concat([base, _jitter(lfgen.generate("nominal", n_events=5, seed=97), 98)])
+    ref = oracle_parallel(ev, params)
+    ctx = lf.lf_create(W, params, 1 << 30)
+    try:
+        bid = lf.lf_upload_events(ctx, ev)
+        for waves in (1, 2, 4):
+            lf.lf_set_exec(ctx, waves_per_block=waves)
+            for mode in ("batched", "persistent", "persistent"):
+                say(f"[gpu] one-track kernels {params} waves={waves} mode={mode}")
+                lf.lf_poison_tracks(ctx, bid)
+                lf.lf_find_tracks(ctx, bid, mode)
+                compare(ref, lf.lf_copy_tracks(ctx, bid), label=f"{mode}/{waves}")
+    finally:
+        lf.lf_destroy(ctx)
+
+
+@pytest.mark.parametrize("n_events", [8191, 8192, 8193])
+def test_noalloc_at_the_end_of_the_fixed_indexes(n_events):
+    """The fixed scratch holds the search indexes of 8,192 events; longer calls
+    go without.  Every slot, both modes, after a call of the other kind."""
+    from paper_2402_14670_amd import lf
+    small = lfgen.generate("single", n_events=600, seed=99)
+    ev = lfgen.select_events(small, np.arange(n_events) % 600)
+    ref = oracle_parallel(ev)
+    ctx = lf.lf_create(W)
+    try:
+        src, out = _device(ev)
+        few, few_out = _device(small)
+        for mode in ("batched", "persistent"):
+            say(f"[gpu] noalloc {n_events} events mode={mode}")
+            _noalloc(ctx, few, few_out, mode)
+            compare(ref, _noalloc(ctx, src, out, mode), label=f"{n_events}/{mode}")
+    finally:
+        lf.lf_destroy(ctx)
