@@ -5,8 +5,8 @@ Workload: the nominal batch -- 1,000 synthetic events, each with 350
 particles (p 2-100 GeV, pt > 0.3 GeV), 200 upstream input tracks (170 true,
 30 fake) and ~5.4k SciFi hits -- resident in HBM.  One step is one pass of
 the whole hot path (windows, triplet seeding, extension, fits, selection,
-momentum) over the batch.  ``value`` is events/s of the batched launch (one
-wavefront per input track, XCD-ordered); the persistent (resident waves
+momentum) over the batch.  ``value`` is events/s of the batched launch (two
+input tracks per wavefront, XCD-ordered); the persistent (resident waves
 pulling from per-XCD work queues) and per-event-launch (plain, eager and
 graph-captured) modes are reported beside it, with identical output, and so
 are the serving loop's rates and latencies.

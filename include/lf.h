@@ -56,8 +56,9 @@ enum {
 /* Execution modes of lf_find_tracks (all write identical results). */
 enum {
     LF_MODE_PLAIN = 0,      /* one kernel launch per event */
-    LF_MODE_BATCHED = 1,    /* one launch over the whole batch, one wavefront per input track,
-                               tracks ordered so each XCD takes a contiguous run of events */
+    LF_MODE_BATCHED = 1,    /* one launch over the whole batch, a wavefront for every two input
+                               tracks (VELO-only input: for every one), tracks ordered so each
+                               XCD takes a contiguous run of events */
     LF_MODE_PERSISTENT = 2  /* one launch of resident wavefronts pulling (event, track) work
                                items from per-XCD device queues */
 };
@@ -207,7 +208,8 @@ typedef struct {
  * current value. */
 typedef struct {
     int32_t waves_per_block;   /* 1, 2 or 4 wavefronts per workgroup */
-    int32_t items_per_grab;    /* tracks a wavefront takes per queue claim (persistent mode), 1..16 */
+    int32_t items_per_grab;    /* tracks a wavefront takes per queue claim (persistent mode), 1..16;
+                                  1 acts as 2 where a wavefront runs two tracks at once */
     int32_t blocks_per_cu;     /* persistent grid = blocks_per_cu * compute units (persistent mode) */
 } lf_exec;
 
@@ -288,7 +290,10 @@ int lf_find_tracks(lf_ctx *ctx, uint64_t batch_id, int mode, void *hip_stream);
  * object (47 MiB, held until the process ends): the persistent queue words
  * (cleared by a kernel at every call of that mode), one byte per event, one
  * word per track and, for batches of up to 8,192 events, the search index of
- * each hit bucket (larger batches are searched without).  Limits: at most 2^20 events and 2^22 tracks per call
+ * each hit bucket.  A longer batch, like one of a context with a device budget, is
+ * searched without an index by one wavefront per track, with the same results at
+ * about two thirds of the rate or less: in calls of up to 8,192 events a long
+ * batch runs faster.  Limits: at most 2^20 events and 2^22 tracks per call
  * (LF_ERR_TOO_LARGE beyond, nothing launched), fewer than 2^30 hits.  Every
  * call on a GPU shares that GPU's array: calls that overlap on one GPU (on
  * different streams, or from several contexts or threads) race and must be
@@ -405,7 +410,11 @@ typedef struct {
  * after the start (non-decreasing; open loop: arrivals do not wait for
  * service).  Arrived requests queue on the host and are admitted into a
  * device ring of device_budget_bytes in arrival order (a request that does
- * not fit waits: backpressure, nothing is dropped).  Whenever one of
+ * not fit waits: backpressure, nothing is dropped).  Beside the ring each slot
+ * has search indexes for a batch of up to min(max_batch_events, 8,192) events,
+ * 3,840 bytes an event, for the length of the call and whatever the context's
+ * own budget; they are left out where that memory cannot be had, and batches of
+ * more events run without.  Whenever one of
  * n_slots in-flight slots is free, every admitted request (up to
  * max_batch_events) forms one batch: the host writes one descriptor per
  * event, and on the slot's stream a gather kernel reads the events straight
@@ -417,7 +426,8 @@ typedef struct {
  * 0x9E3779B97F4A7C15) over the event's tracks); req_latency_s[i]
  * (optional) its arrival-to-results-on-host latency.
  * With pool_on_device the pool is copied to device memory once, before the
- * clock (not charged to the budget), and a batch is its list of pool
+ * clock, with 3,840 bytes of search indexes an event if they can be had (not
+ * charged to the budget; the slots then have none), and a batch is its list of pool
  * events: the host uploads the list and the batch's result-slot offsets, a
  * kernel maps each slot to its pool track, and the hot path reads the pool
  * in place (no gather).  With results_on_device a request completes when its

@@ -15,7 +15,7 @@ constexpr int MAX_TRIPLETS = 32;  // n_triplets upper bound
 // a hit, for hits on the layer planes: the serial sums over the present layers
 // in ascending order of 1, s, h, s^2, s h, h^2 (x fit) and 1, s, s^2 over the
 // stereo layers (y fit), the x fit's cofactors and determinant, the y fit's
-// determinant, C(n_hits), and the binary64 reciprocals (see div_by) of det and D
+// determinant, C(n_hits), and the binary64 reciprocals (recip, see div_by) of det and D
 // (of 1 where they are 0), n - 3 and n_uv - 2.
 struct alignas(16) FitRow {
     float S0, S1, S2, S11;
@@ -27,7 +27,7 @@ struct alignas(16) FitRow {
 
 constexpr uint32_t FIT_ROWS = 1u << NL;   // one for each mask
 
-// Geometry and parameters, passed to every kernel by value.
+// Geometry and parameters: one block of device memory per context.
 struct KParams {
     float z[NL], dxdy[NL];
     float z_in, z_mag, z_ref, z_T, kick, kappa, dRatio;
@@ -57,7 +57,7 @@ struct KParams {
     alignas(16) float lay_u[NL];
     float lay_g[NL], lay_h[NL];
     float set_tab[2][12];
-    // binary64 reciprocals (see div_by): per seed set of z_l2 - z_l0,
+    // binary64 reciprocals (recip, see div_by): per seed set of z_l2 - z_l0,
     // u1 - u0, u2 - u1 and G12 - G01; of dxdy of each layer, T_x, T_y and kick
     double r_set[2][4], r_dxdy[NL], r_Tx, r_Ty, r_kick;
     int32_t pair_ok;
@@ -121,10 +121,14 @@ constexpr uint32_t QUEUE_WORDS = QUEUE_STRIDE * (QUEUE_N + 1);
 struct ExecCfg {
     int waves_per_block;
     int items_per_grab;
+    // persistent grid; its default is what is resident of the kernel that pair_ok
+    // names.  A batch without search indexes runs the one-track kernel on the same
+    // grid: 20,000 short events 1,692 us against 1,568 on a grid of its own, 200
+    // nominal events 143 against 155, 300 short ones 69 against 82.
     int blocks_per_cu;
     int n_cu;
     // batched and persistent mode: the geometry's planes allow the two-track
-    // kernel
+    // kernel (which a batch without search indexes does not run all the same)
     bool pair_ok;
     int n_triplets;   // of the context's parameters
 };
@@ -156,16 +160,17 @@ hipError_t launch_gather(const GatherDesc *desc, uint32_t n_events, const BatchI
 hipError_t launch_track_map(const uint32_t *evs, const uint32_t *toff, uint32_t n_events, uint32_t n_slots,
                             const uint32_t *pool_trk_off, uint32_t *map, hipStream_t s);
 // The hot path.  P points to a KParams in device memory.  mode: 0 plain
-// (per-event launches), 1 batched (one wavefront per track), 2 persistent
+// (per-event launches), 1 batched (one launch, two tracks per wavefront), 2 persistent
 // (resident wavefronts pulling from per-XCD work queues).
 // trk_off_host is read by mode 0 only.
 // n_sides: 1 for VELO-UT input, 2 for VELO-only input (two windows per
 // layer), 3 for VELO-UT input with the binary16 seeding build.
 hipError_t launch_find(const DevBatch &b, const KParams *P, int n_hits_window, int n_sides, int mode,
                        const ExecCfg &cfg, const uint32_t *trk_off_host, hipStream_t s);
-// What the hot path needs to know of each event beside its hits (one block per
-// event; the batch's hits and offsets must be in place): the flags uni[E], the
-// bucket indexes b.bidx (if not nullptr) and trk_ev.
+// What the hot path needs to know of each event beside its hits (four blocks per
+// event, or one without indexes; the batch's hits and offsets must be in place):
+// the bucket indexes b.bidx with the event's flags or, where b.bidx is nullptr, the
+// flags uni[E], and trk_ev.
 hipError_t launch_event_index(const DevBatch &b, const KParams *P, uint8_t *uni, hipStream_t s);
 // Fills the parts of k that follow from its geometry (lay_*, set_*, pair_ok).
 void plane_constants(KParams &k);

@@ -216,6 +216,8 @@ __device__ __forceinline__ float field_c_lane(const KParams *__restrict__ P, flo
 // relative, from a point halfway between two binary32 numbers, and reciprocal,
 // product and clearing move it by less than 2^-50.  Zeros, infinities and NaN are
 // those of the division.
+// (The clearing: 160,000 tracks seeded in binary16 178 -> 180 us, the others
+// within 0.5%.)
 __device__ __forceinline__ double as_double(uint64_t u) { return __builtin_bit_cast(double, u); }
 __device__ __forceinline__ uint64_t as_bits(double v) { return __builtin_bit_cast(uint64_t, v); }
 __device__ __forceinline__ float div_by(float a, double r) {
@@ -1542,7 +1544,8 @@ __device__ __forceinline__ void pair_of_tracks(const DevBatch &B, const KParams 
 constexpr uint32_t pair_tracks(int NS) { return NS == 1 ? 2 : 1; }   // tracks per wavefront
 
 // Batched mode, two tracks per wavefront (or one track's two sides).  32-hit
-// windows: 7 waves per SIMD, 72 registers and a few spilled: 200,000 nominal
+// windows: 7 waves per SIMD, 72 registers and 12 spilled (VELO-only input 4,
+// binary16 seeding 19): 200,000 nominal
 // tracks 0.207 ms, 121,500 in dense events 0.277, against 0.279 and 0.306 with
 // 64 registers at 8 waves, and 3% and 6% more with 80 at 6.  64-hit windows:
 // what LDS allows.
@@ -2058,7 +2061,7 @@ hipError_t launch_nw_wpb(const DevBatch &b, const KParams *P, int mode, const Ex
             hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, 16>), dim3(grid), block, 0, s, b, P, c);
         else
             hipLaunchKernelGGL((k_persistent<NW, NS, WPB, H16, MAX_TRIPLETS>), dim3(grid), block, 0, s, b, P, c);
-    } else {   // batched: one launch, one wavefront per track (or per mapped slot), XCD-ordered
+    } else {   // batched: one launch, XCD-ordered, two tracks (or mapped slots) per wavefront, or one
         if (pair) {
             const uint32_t waves = (n + pair_tracks(NS) - 1) / pair_tracks(NS);
             const dim3 g(((waves + WPB - 1) / WPB + NXCD - 1) / NXCD * NXCD);

@@ -22,19 +22,19 @@
 //  - likewise a candidate's model and extension: a lane searches its station's
 //    three layers side by side, and 16 candidates of both tracks share a pass;
 //  - a division whose divisor is a constant of the context multiplies by its
-//    binary64 reciprocal (div_by: 13 cycles of issue instead of 38);
+//    binary64 reciprocal (div_by: 15 cycles of issue instead of 38);
 //  - in events whose hits lie on the layer planes (not EV_OFF_PLANES) every
 //    expression of the layer z alone is a constant of the context
 //    (KParams::lay_*, set_*, fit_tab), and no z or slope is loaded at all;
 //  - in the others (PL = false) stereo hits are staged moved along their fibre
 //    to the track's y, which is the same for every candidate, and the closest
 //    one is found by a search and a short walk.
-// Launches with one track per wavefront and now: 200,000 nominal tracks 0.377
-// -> 0.199 ms (0.244 with the one-track body's sixteen lanes per fit and nine
+// Launches with one track per wavefront and now: 200,000 nominal tracks 0.383
+// -> 0.201 ms (0.244 with the one-track body's sixteen lanes per fit and nine
 // lanes per extension, 0.226 with four lanes per fit); 160,000 with per-hit z
-// and slopes 0.445 -> 0.226; 121,500 in dense events 0.477 -> 0.274 (0.314 with
-// the pairs written into a queue item by item); 100,000 VELO-only 0.444 ->
-// 0.303; 160,000 nominal seeded in binary16 0.352 -> 0.187; 4,800 nominal 0.0204 -> 0.0155.
+// and slopes 0.443 -> 0.228; 121,500 in dense events 0.488 -> 0.276 (0.314 with
+// the pairs written into a queue item by item); 100,000 VELO-only 0.471 ->
+// 0.305; 160,000 nominal seeded in binary16 0.363 -> 0.180; 4,800 nominal 0.0207 -> 0.0156.
 
 // Binary16 seeding: per track and seed set, coordinates relative to the
 // window centres c and the constants rounded once from binary32, as in
