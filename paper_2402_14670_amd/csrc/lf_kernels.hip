@@ -1791,28 +1791,46 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
     const uint32_t e = e0 + blockIdx.x / PARTS, part = blockIdx.x % PARTS;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE), lane = lane_id();
     uint32_t flags = 0;
-    uint32_t b0 = 0, n = 0;
     float lo = 0.0f, scale = 0.0f;
     if (threadIdx.x == 0) claimed = 0;
-    for (uint32_t k = (uint32_t)w; k < NB; k += NWV) {
-        struct Hits {
-            float x[EVI_ROUNDS], z[EVI_ROUNDS], d[EVI_ROUNDS];
-        } h;
-        const uint32_t *off = B.hit_off + (2 * NL * e + part * NB + k);
-        b0 = off[0];
-        n = off[1] - b0;
-        auto load = [&](Hits &v, uint32_t i0) {   // hits i0 + 64 r + lane (past the end: the last one)
+    // a wave's buckets w, w + NWV: the first rounds of all are requested together
+    // (20,000 short events without indexes, the whole call 1,339 -> 1,327 us)
+    constexpr int PER = NB / NWV;
+    struct Hits {
+        float x[EVI_ROUNDS], z[EVI_ROUNDS], d[EVI_ROUNDS];
+    } first[PER];
+    uint32_t b0s[PER], ns[PER], b0 = 0, n = 0;
+    float lasts[PER];
+    auto load = [&](Hits &v, uint32_t i0) {   // hits i0 + 64 r + lane of b0, n (past the end: the last one)
 #pragma unroll
-            for (int r = 0; r < EVI_ROUNDS; ++r) {
-                if (i0 + (uint32_t)(r * WAVE) >= n) continue;
-                const uint32_t i = i0 + (uint32_t)(r * WAVE + lane), g = b0 + (i < n ? i : n - 1);
-                v.x[r] = ld32(B.hx, g);
-                v.z[r] = ld32(B.hz, g);
-                v.d[r] = ld32(B.hd, g);
-            }
-        };
-        load(h, 0);
-        const float last = n ? ld32(B.hx, b0 + n - 1) : 0.0f;
+        for (int r = 0; r < EVI_ROUNDS; ++r) {
+            if (i0 + (uint32_t)(r * WAVE) >= n) continue;
+            const uint32_t i = i0 + (uint32_t)(r * WAVE + lane), g = b0 + (i < n ? i : n - 1);
+            v.x[r] = ld32(B.hx, g);
+            v.z[r] = ld32(B.hz, g);
+            v.d[r] = ld32(B.hd, g);
+        }
+    };
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const uint32_t *off = B.hit_off + (2 * NL * e + part * NB + (uint32_t)(w + t * NWV));
+        b0s[t] = off[0];
+        ns[t] = off[1] - b0s[t];
+    }
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        b0 = b0s[t];
+        n = ns[t];
+        load(first[t], 0);
+        lasts[t] = n ? ld32(B.hx, b0 + n - 1) : 0.0f;
+    }
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const uint32_t k = (uint32_t)(w + t * NWV);
+        b0 = b0s[t];
+        n = ns[t];
+        Hits h = first[t];
+        const float last = lasts[t];
         float xabs = 0.0f, zmin = 0.0f, zmax = 0.0f, dmin = 0.0f, dmax = 0.0f;
         lo = scale = 0.0f;
         if (n) {
