@@ -1817,6 +1817,9 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
         b0s[t] = off[0];
         ns[t] = off[1] - b0s[t];
     }
+    // (a caller of the non-allocating entry may pass fewer tracks than trk_off counts;
+    // the stores overlap the loads: one small event, the whole call, 13.1 -> 12.9 us)
+    const uint32_t ta = B.trk_off[e], te = B.trk_off[e + 1], t1 = te < B.n_tracks ? te : B.n_tracks;
 #pragma unroll
     for (int t = 0; t < PER; ++t) {
         b0 = b0s[t];
@@ -1824,6 +1827,7 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
         load(first[t], 0);
         lasts[t] = n ? ld32(B.hx, b0 + n - 1) : 0.0f;
     }
+    for (uint32_t t = ta + part * (NWV * WAVE) + threadIdx.x; t < t1; t += PARTS * NWV * WAVE) trk_ev[t] = e;
 #pragma unroll
     for (int t = 0; t < PER; ++t) {
         const uint32_t k = (uint32_t)(w + t * NWV);
@@ -2003,9 +2007,6 @@ __global__ void __launch_bounds__(evi_waves(IDX) * WAVE) k_event_index(DevBatch 
     } else if (threadIdx.x == 0) {
         uni[e] = (uint8_t)(all & ~ANY_LONG);
     }
-    // (a caller of the non-allocating entry may pass fewer tracks than trk_off counts)
-    const uint32_t te = B.trk_off[e + 1], t1 = te < B.n_tracks ? te : B.n_tracks;
-    for (uint32_t t = B.trk_off[e] + part * (NWV * WAVE) + threadIdx.x; t < t1; t += PARTS * NWV * WAVE) trk_ev[t] = e;
 }
 
 // The rows of KParams::fit_tab, one thread each, from the parameters already
