@@ -70,8 +70,8 @@ BYTES_PER_TRACK_OUT = 78
 # HBM traffic of the batched kernel from rocprofv3 FETCH_SIZE + WRITE_SIZE
 # (per launch, scaled by the counters' reading of a known-size copy), valid
 # only for the kernel source and the workload it was measured on.
-TRAFFIC = {"kernel_sha256": "bf1fdd91180a9605ee5702bad83aaee763c51995d0cda956b6497d1159a84f63",
-           "workload": "nominal", "events": 0, "bytes_per_launch": 54054810}
+TRAFFIC = {"kernel_sha256": "1814e70bb3fed94d6c064381f7d5b3179e8aea8690aa8021536f543d7d3c4e44",
+           "workload": "nominal", "events": 0, "bytes_per_launch": 54055936}
 WORKLOADS = {
     "nominal": "nominal: 1000 events x 200 input tracks, ~5.4k SciFi hits/event, toy kick field",
     "uneven": "uneven: 20000 events, Poisson(7.6) x 50 particles, 0-13k hits and 0-600 tracks/event",
